@@ -467,10 +467,12 @@ spl_status spl_spadd3_numeric(spl_context *ctx, const spl_sparse *B, const spl_s
  * matrix A as the n x m CSR of A^T gives A's CSR (m x n), which every CSR
  * leaf takes.  Outputs (device, caller-owned): T_pos m + 1 entries, T_crd
  * and T_vals nnz entries, rows of B^T with strictly increasing coordinates.
- * A stable LSD radix sort of the entries by column (8-bit digits, integer
- * counts and ranks only): deterministic and exact.  Workspace: NULL for the
- * context's pool, else at least spl_transpose_workspace_query bytes (about
- * 16 bytes per nonzero). */
+ * A stable LSD radix sort of the entries by column (digits of at most 8
+ * bits, integer counts and ranks only): deterministic and exact.  T_crd and
+ * T_vals also hold intermediate passes, so they overlap none of B's arrays.
+ * Workspace: NULL for the context's pool, else at least
+ * spl_transpose_workspace_query bytes (about 12 bytes and a value per
+ * nonzero). */
 spl_status spl_transpose_workspace_query(spl_context *ctx, const spl_sparse *B, size_t *bytes);
 spl_status spl_transpose(spl_context *ctx, const spl_sparse *B, int32_t *T_pos, int32_t *T_crd,
                          void *T_vals, void *workspace, size_t workspace_bytes,

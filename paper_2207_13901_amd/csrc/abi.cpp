@@ -1747,7 +1747,7 @@ spl_status spl_transpose_workspace_query(spl_context *ctx, const spl_sparse *B, 
     SPL_GUARD_BEGIN
     if (!ctx || !bytes) return fail(ctx, SPL_ERR_ARG, "NULL argument");
     SPL_CHECK(check_sparse(ctx, B, 2));
-    *bytes = spl::transpose_ws_bytes(B->nnz, B->dims[1]);
+    *bytes = spl::transpose_ws_bytes(B->vtype, B->nnz);
     return SPL_OK;
     SPL_GUARD_END
 }
@@ -1764,7 +1764,7 @@ spl_status spl_transpose(spl_context *ctx, const spl_sparse *B, int32_t *T_pos, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     void *ws = nullptr;
     SPL_CHECK(get_workspace(ctx, workspace, workspace_bytes,
-                            spl::transpose_ws_bytes(B->nnz, B->dims[1]), &ws));
+                            spl::transpose_ws_bytes(B->vtype, B->nnz), &ws));
     SPL_HIP(spl::launch_transpose(B->vtype, B->dims[0], B->dims[1], B->nnz, B->pos[1], B->crd[1],
                                   B->vals, T_pos, T_crd, T_vals, ws, s),
             "transpose launch");

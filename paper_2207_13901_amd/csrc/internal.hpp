@@ -209,10 +209,12 @@ hipError_t launch_validate_level(int64_t parents, const int32_t *pos, const int3
                                  hipStream_t s);
 
 // ---- transpose.hip -------------------------------------------------------
-// Radix passes for column indices below m (8 bits each).
+// Bits of the column indices below m, and the radix passes over them (at
+// most 8 bits each).
+int transpose_bits(int64_t m);
 int transpose_passes(int64_t m);
-// Workspace of launch_transpose for nnz entries and m columns.
-size_t transpose_ws_bytes(int64_t nnz, int64_t m);
+// Workspace of launch_transpose for nnz entries.
+size_t transpose_ws_bytes(int vtype, int64_t nnz);
 // CSR arrays of B^T (m + 1 pos, nnz crd and vals) from B's (n x m).
 hipError_t launch_transpose(int vtype, int64_t n, int64_t m, int64_t nnz, const int32_t *pos,
                             const int32_t *crd, const void *vals, int32_t *tpos, int32_t *tcrd,

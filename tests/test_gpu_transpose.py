@@ -82,6 +82,34 @@ def test_transpose_full_size_power_law():
     _check(spl, B, "power law full size")
 
 
+@pytest.mark.parametrize("nnz,n,m,cols", [
+    # one tile of 4,096 entries and its edges; 16 tiles (offsets summed by the
+    # scatter) and 17 (by their own kernel); a ragged last tile
+    (4095, 500, 130, "any"), (4096, 500, 130, "any"), (4097, 500, 130, "any"),
+    (65536, 9000, 2000, "any"), (65537, 9000, 2000, "any"), (200_003, 9000, 70_000, "any"),
+    # four passes and gaps of millions of columns; every entry in one column;
+    # one row holding every entry; runs of thousands of empty rows in a tile
+    (3000, 2900, 40_000_000, "any"), (70_000, 70_000, 300, "one"), (9000, 1, 70_000, "any"),
+    (5000, 400_000, 257, "any"),
+])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32, torch.bfloat16])
+def test_transpose_tile_edges(nnz, n, m, cols, dtype):
+    spl = _spl()
+    rs = np.random.RandomState(nnz + n)
+    if cols == "one":
+        row, col = np.arange(nnz), np.full(nnz, m - 1)
+    elif n == 1:
+        row, col = np.zeros(nnz, np.int64), np.sort(rs.choice(m, nnz, replace=False))
+    else:
+        key = np.unique(rs.randint(0, n * m, 2 * nnz, dtype=np.int64))
+        key = np.sort(rs.choice(key, nnz, replace=False))
+        row, col = key // m, key % m
+    pos = np.zeros(n + 1, np.int64)
+    np.cumsum(np.bincount(row, minlength=n), out=pos[1:])
+    print(f"transpose nnz={nnz} n={n} m={m} {cols} {dtype}", flush=True)
+    _check(spl, _csr(spl, pos, col, rs.uniform(-1, 1, nnz), (n, m), dtype), (nnz, n, m, dtype))
+
+
 @pytest.mark.parametrize("kind", ["float", "int"])
 def test_csc_spmv(kind):
     # A (n x m) given by columns: its CSR comes from the transposition, then
