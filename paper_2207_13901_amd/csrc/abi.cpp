@@ -768,11 +768,11 @@ spl_status tin_prepare(spl_context *ctx, const char *stmt, int nops, const spl_t
 }
 
 hipError_t tin_launch(hipFunction_t f, int64_t rows, std::vector<unsigned long long> &slots,
-                      hipStream_t s) {
+                      hipStream_t s, unsigned block = 256, unsigned lds = 0) {
     if (rows == 0) return hipSuccess;
     void *args[] = {slots.data()};
-    return hipModuleLaunchKernel(f, static_cast<unsigned>((rows + 255) / 256), 1, 1, 256, 1, 1,
-                                 0, s, args, nullptr);
+    return hipModuleLaunchKernel(f, static_cast<unsigned>((rows + block - 1) / block), 1, 1, block,
+                                 1, 1, lds, s, args, nullptr);
 }
 
 }  // namespace
@@ -1824,8 +1824,10 @@ spl_status spl_tin_symbolic(spl_context *ctx, const char *tin, int nops, const s
     int64_t *total = reinterpret_cast<int64_t *>(
         static_cast<char *>(ws) + align_up(static_cast<size_t>(spl::spadd3_scan_tiles(prog.rows)) * 8));
     std::vector<unsigned long long> slots;
-    spl::tin::fill_slots(prog, b, ob, A_pos, nullptr, nullptr, slots);
-    SPL_HIP(tin_launch(cp->f_count, prog.rows, slots, s), "generated count launch");
+    unsigned block = 256, lds = 0;
+    spl::tin::stage_shape(prog, b, -1, block, lds);
+    spl::tin::fill_slots(prog, b, ob, A_pos, nullptr, nullptr, lds, slots);
+    SPL_HIP(tin_launch(cp->f_count, prog.rows, slots, s, block, lds), "generated count launch");
     SPL_HIP(spl::launch_pos_scan(prog.rows, A_pos, tile_sum, total, s), "scan launch");
     SPL_HIP(hipMemcpyAsync(ctx->readback, total, sizeof(int64_t), hipMemcpyDeviceToHost, s),
             "hipMemcpyAsync");
@@ -1870,9 +1872,12 @@ spl_status spl_tin_eval(spl_context *ctx, const char *tin, int nops, const spl_t
     if (prog.scratch_rows) scratch = wp;
     std::vector<unsigned long long> slots;
     const int32_t *apos = prog.out_kind == spl::tin::kOutCsr ? out->sparse->pos[1] : nullptr;
-    spl::tin::fill_slots(prog, b, ob, apos, partials, scratch, slots);
+    unsigned block = 256, lds = 0;
+    if (prog.out_kind == spl::tin::kOutCsr)
+        spl::tin::stage_shape(prog, b, out->sparse->nnz, block, lds);
+    spl::tin::fill_slots(prog, b, ob, apos, partials, scratch, lds, slots);
     hipFunction_t f = prog.out_kind == spl::tin::kOutCsr ? cp->f_fill : cp->f_eval;
-    SPL_HIP(tin_launch(f, prog.rows, slots, s), "generated leaf launch");
+    SPL_HIP(tin_launch(f, prog.rows, slots, s, block, lds), "generated leaf launch");
     if (prog.out_kind == spl::tin::kOutScalar)
         SPL_HIP(spl::launch_inner_final(prog.rows, static_cast<const double *>(partials),
                                         static_cast<double *>(out->dense->data), s),

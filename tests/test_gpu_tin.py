@@ -106,3 +106,46 @@ def test_tin_scalar_on_a_larger_pattern():
     got = spl.tin(stmt, **lib)
     want, S = T.evaluate(stmt, ref)
     assert_close(host64(got), np.reshape(want, 1), np.reshape(S, 1), 1e-12, stmt)
+
+
+# CSR outputs of CSR operands: the workgroups' rows staged in LDS, and in the
+# same launch a row too long for the stage (entries of 20 times the mean)
+@pytest.mark.parametrize("n,m,deg,long", [(1, 1, 1, ()), (128, 700, 3, ()), (129, 700, 3, ()),
+                                          (700, 9000, 2, (0, 130, 699)), (1000, 400, 60, ()),
+                                          (300, 3000, 900, ()), (257, 50, 0, (200,))])
+@pytest.mark.parametrize("stmt", ["A(i,j) = B(i,j) - C(i,j)", "A(i,j) = B(i,j) * C(i,j)",
+                                  "A(i,j) = B(i,j) * c(j) - C(i,j) * d(i)"])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_tin_csr_outputs_staged_and_direct_rows(n, m, deg, long, stmt, dtype):
+    spl = _spl()
+    dev = torch.device("cuda", 0)
+    rs = np.random.RandomState(n + m)
+    print(f"tin staged: {stmt} n={n} m={m} deg={deg} {dtype}", flush=True)
+
+    def operand():
+        dense = np.where(rs.rand(n, m) < deg / m, rs.uniform(-1, 1, (n, m)), 0.0)
+        for i in long:
+            dense[i] = rs.uniform(0.5, 1, m)
+        dense = torch.as_tensor(dense).to(dtype)
+        mask = dense != 0
+        pos = torch.zeros(n + 1, dtype=torch.int32)
+        pos[1:] = mask.sum(1).cumsum(0)
+        crd = mask.nonzero()[:, 1].to(torch.int32)
+        return dense.double(), mask, spl.CSR(pos.to(dev), crd.to(dev), dense[mask].to(dev), (n, m))
+
+    (Bd, Bm, B), (Cd, Cm, C) = operand(), operand()
+    c, d = (torch.as_tensor(rs.uniform(-1, 1, k)).to(dtype) for k in (m, n))
+    args = dict(B=B, C=C)
+    if "*" not in stmt:
+        want, S, mask = Bd - Cd, Bd.abs() + Cd.abs(), Bm | Cm
+    elif "c(j)" not in stmt:
+        want, S, mask = Bd * Cd, (Bd * Cd).abs(), Bm & Cm
+    else:
+        args.update(c=c.to(dev), d=d.to(dev))
+        tb, tc = Bd * c.double(), Cd * d.double()[:, None]
+        want, S, mask = tb - tc, tb.abs() + tc.abs(), Bm | Cm
+    A = spl.tin(stmt, shape=(n, m), **args)
+    pos = np.concatenate([[0], mask.sum(1).cumsum(0).numpy()])
+    assert np.array_equal(A.pos.cpu().numpy(), pos)
+    assert np.array_equal(A.crd.cpu().numpy(), mask.nonzero()[:, 1].numpy())
+    assert_close(host64(A.vals), want[mask].numpy(), S[mask].numpy(), RTOL[dtype], stmt)
