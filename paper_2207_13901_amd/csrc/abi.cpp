@@ -162,6 +162,7 @@ struct Plan {
     int col_tile = 0;
     int variant = 0;
     int vec = 1;  // SpMM: dense columns per lane
+    bool small = false;  // SpMV, SpTTV: the one-launch leaf
 };
 
 int lanes_for_mean(double mean) {
@@ -193,6 +194,9 @@ spl_status resolve_spmv(spl_context *ctx, const spl_sparse *B, const spl_schedul
     if (s->variant != 0 && p.kind != SPL_MERGE)
         return fail(ctx, SPL_ERR_ARG, "SpMV variants 1 and 2 need the MERGE schedule");
     p.variant = s->variant;
+    // the library's own choice with nothing asked for
+    p.small = s->kind == SPL_SCHED_DEFAULT && !s->lanes_per_row && !s->tile && !s->items_per_lane &&
+              !s->variant && spl::spmv_is_small(n, B->dims[1], B->nnz);
     p.tile = s->tile ? s->tile : (p.kind == SPL_ROW ? 256 / p.lanes : spmv_chunk(p));
     if (p.tile < 1) return fail(ctx, SPL_ERR_ARG, "tile must be positive");
     return SPL_OK;
@@ -399,6 +403,14 @@ size_t spmm_ws(const spl_sparse *B, int64_t N, const Plan &p) {
     if (p.kind == SPL_ROW) return 0;
     return tiled_ws(pieces_for(p, B->dims[0], B->nnz, spmm_chunk(p)), N,
                     B->vtype == SPL_F64 ? 8 : 4, B->pos_type == SPL_I64 ? 8 : 4);
+}
+
+// The one-launch leaf needs no workspace; one that the caller passes is held
+// to the queried size all the same.
+spl_status check_workspace(spl_context *ctx, const void *user, size_t user_bytes, size_t need) {
+    if (user && user_bytes < need)
+        return fail(ctx, SPL_ERR_WORKSPACE, "workspace of %zu bytes, %zu needed", user_bytes, need);
+    return SPL_OK;
 }
 
 // SpTTV runs the SpMV leaf on the fiber level: a CSR view whose rows are the
@@ -1143,6 +1155,15 @@ spl_status spl_spmv(spl_context *ctx, const spl_sparse *B, const spl_dense *c, s
         tm.stop();
         return SPL_OK;
     }
+    if (p.small) {
+        SPL_CHECK(check_workspace(ctx, workspace, workspace_bytes, spmv_ws(B, p)));
+        LeafTimer tm(ctx, SPL_OP_SPMV, s);
+        SPL_HIP(spl::launch_spmv_small(B->vtype, pos64, n, B->nnz, B->pos[1], B->crd[1], B->vals, c->data,
+                                       a->data, s),
+                "SpMV launch");
+        tm.stop();
+        return SPL_OK;
+    }
     void *ws = nullptr;
     SPL_CHECK(get_workspace(ctx, workspace, workspace_bytes, spmv_ws(B, p), &ws));
     const Pieces q = pieces_for(p, n, B->nnz, spmv_chunk(p));
@@ -1383,6 +1404,15 @@ spl_status spl_spttv(spl_context *ctx, const spl_sparse *B, const spl_dense *c, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t F = B->nfibers;
     if (F == 0) return SPL_OK;
+    if (p.small) {
+        SPL_CHECK(check_workspace(ctx, workspace, workspace_bytes, spmv_ws(&v, p)));
+        LeafTimer tm(ctx, SPL_OP_SPTTV, s);
+        SPL_HIP(spl::launch_spmv_small(B->vtype, pos64, F, B->nnz, v.pos[1], v.crd[1], B->vals, c->data,
+                                       A->data, s),
+                "SpTTV launch");
+        tm.stop();
+        return SPL_OK;
+    }
     if (pos64) {
         // the fiber level's int64 positions: the SpMV flag leaf over fibers
         void *ws = nullptr;

@@ -47,8 +47,9 @@ hipError_t launch_spmv_row(int dtype, int lanes, int64_t n, const int32_t *pos_b
 // Tiled leaves: one workgroup per `stride` consecutive partition pieces of
 // `t`; carries are one per workgroup.
 // exact_chunks: every piece of `t` is at most one chunk of 256 * items merged
-// items (merge split): the row-end flag leaf k_spmv_flag (variant 0) or the
-// row-end search leaf k_spmv_pipe (variant 1).
+// items (merge split): the row-end flag leaf (variant 0; k_spmv_once at one
+// piece per workgroup, else k_spmv_flag) or the row-end search leaf
+// k_spmv_pipe (variant 1).
 // The row-end flag leaf over exact merge chunks of a CSR with int64
 // positions (tile bounds in t.row / t.pos64).
 hipError_t launch_spmv_flag64(int dtype, int items, int64_t n, const int64_t *pos,
@@ -58,6 +59,13 @@ hipError_t launch_spmv_tiles(int dtype, int items, int64_t n, const int32_t *pos
                              const int32_t *crd, const void *vals, const void *x, void *y,
                              const Tiles &t, int64_t stride, bool exact_chunks, int variant,
                              double *carry, hipStream_t s);
+// Matrices whose default schedule is the one-launch leaf (no partition, no
+// carries, no workspace).
+bool spmv_is_small(int64_t n, int64_t m, int64_t nnz);
+// pos: int64 positions when pos64, else int32.
+hipError_t launch_spmv_small(int dtype, bool pos64, int64_t n, int64_t nnz, const void *pos,
+                             const int32_t *crd, const void *vals, const void *x, void *y,
+                             hipStream_t s);
 // Adds workgroup carries into the rows left open (after the leaf).
 // Merge split over position windows [begin[i], end[i]): vpos holds the
 // scanned window lengths (n + 1 entries, from launch_window_offsets).

@@ -34,6 +34,9 @@
 //    ends staged as flags in the merged sequence, so that no lane searches
 //    or reads row ends (see below).
 //
+//  * k_spmv_once: the flag leaf for workgroups of one chunk (the default
+//    tile); k_spmv_small: small matrices in one launch.
+//
 //  * k_spmv_window_flag: the flag leaf over position windows (one color of
 //    a coordinate-value partition), whose lengths are scanned into the
 //    positions of a virtual CSR; each position maps back to its stored
@@ -41,6 +44,7 @@
 //
 // Accumulation is in double for both double and float data (a float output
 // is rounded once from the double sum, then once more if a carry lands on it).
+#include <algorithm>
 #include <type_traits>
 
 #include "carry.hpp"
@@ -480,6 +484,42 @@ __device__ __forceinline__ double block_segmented_scan_dpp(double v, int key, in
     return v;
 }
 
+// The walk of one chunk, shared by the flag leaves: this lane's ITEMS merged
+// items (flags `fl`, `steps` of them inside the chunk) from row a and product
+// b on; finished rows' sums to s_out[row], the sums that cross lanes combined
+// over the workgroup, the open row's to *s_open.  Contains the barriers of the
+// two scans; the caller's next barrier publishes s_out and *s_open.
+template <int ITEMS, typename Flags>
+__device__ __forceinline__ void flag_walk(Flags fl, int d0, int steps, int nr, double open,
+                                          const double *sprod, double *s_out, double *spare,
+                                          int *s_wave_total, int *s_first_key, int *s_last_key,
+                                          double *s_last_val, double *s_open) {
+    const int tid = threadIdx.x;
+    int a = block_exclusive_sum(static_cast<int>(__builtin_popcountll(fl)), s_wave_total);
+    int b = d0 - a;
+    double acc = tid == 0 ? open : 0.0;
+#pragma unroll
+    for (int st = 0; st < ITEMS; ++st) {
+        const bool fin = (fl >> (8 * st)) & 1;
+        const bool add = !fin && st < steps;
+        const double pv = sprod[b];
+        *(fin ? s_out + a : spare) = acc;
+        acc = (fin ? 0.0 : acc) + (add ? pv : 0.0);
+        a += fin ? 1 : 0;
+        b += add ? 1 : 0;
+    }
+    double v = block_segmented_scan_dpp(acc, a, s_first_key, s_last_key, s_last_val);
+    int next_key = __shfl_down(a, 1);
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    if (lane == kWave - 1) next_key = wave + 1 < kBlock / kWave ? s_first_key[wave + 1] : -1;
+    if (next_key != a) {
+        if (a < nr)
+            s_out[a] += v;
+        else
+            *s_open = v;
+    }
+}
+
 // Merge-split leaf with row-end flags (the default; k_spmv_pipe is schedule
 // variant 1).  The same pieces, pipeline and carries as k_spmv_pipe, but
 // instead of the row ends
@@ -586,31 +626,10 @@ __global__ __launch_bounds__(kBlock) void k_spmv_flag(
         const int steps = min(d0 + ITEMS, total) - d0;
         const Flags fl = flag_word(buf);
         flag_word(buf) = 0;  // cleared for the chunk after next
-        int a = block_exclusive_sum(static_cast<int>(__builtin_popcountll(fl)), s_wave_total);
-        int b = d0 - a;
-        const double *sprod = s_prod[buf];
         double *s_out = s_prod[buf ^ 1];  // finished rows until written out
-        double acc = tid == 0 ? open : 0.0;
-#pragma unroll
-        for (int st = 0; st < ITEMS; ++st) {
-            const bool fin = (fl >> (8 * st)) & 1;
-            const bool add = !fin && st < steps;
-            const double pv = sprod[b];  // b <= np; slot kChunk is the spare
-            s_out[fin ? a : kChunk] = acc;
-            acc = (fin ? 0.0 : acc) + (add ? pv : 0.0);
-            a += fin ? 1 : 0;
-            b += add ? 1 : 0;
-        }
-        double v = block_segmented_scan_dpp(acc, a, s_first_key, s_last_key, s_last_val);
-        int next_key = __shfl_down(a, 1);
-        const int lane = tid & (kWave - 1), wave = tid / kWave;
-        if (lane == kWave - 1) next_key = wave + 1 < kBlock / kWave ? s_first_key[wave + 1] : -1;
-        if (next_key != a) {
-            if (a < nr)
-                s_out[a] += v;
-            else
-                s_open = v;
-        }
+        // (product b <= np is read; slot kChunk is the spare)
+        flag_walk<ITEMS>(fl, d0, steps, nr, open, s_prod[buf], s_out, s_out + kChunk, s_wave_total,
+                         s_first_key, s_last_key, s_last_val, &s_open);
         __syncthreads();
         for (int k = tid; k < nr; k += kBlock) store_stream(y + bi0 + k, static_cast<V>(s_out[k]));
         open = s_open;
@@ -627,6 +646,199 @@ __global__ __launch_bounds__(kBlock) void k_spmv_flag(
         buf ^= 1;
     }
     if (tid == 0) carry[blockIdx.x] = open;
+}
+
+// The flag leaf for workgroups of one chunk: no second buffer and no
+// pipeline, and the finished rows' sums follow the products in the one LDS
+// array (a chunk's rows and positions are at most kChunk together).  18 KB of
+// LDS instead of 37 and 64 registers instead of 141 (FP64) let more
+// workgroups share a CU, which overlap each other's loads, gathers and walks;
+// the pipeline's prologue was exposed at every chunk, and loaded two chunks
+// that one-chunk workgroups do not have.
+//
+// Four workgroups a CU are asked for (kOnceLds more bytes of LDS): a banded
+// matrix, bound by its stream, would take up to eight, but with every
+// workgroup more in flight the streamed lines leave less of L2 to the
+// gathered vector (2e6-row power law, FP64: 24.0e6 gather misses of 32e6 with
+// eight, 23.5e6 with three).  Whole calls in us, start (pipelined leaf) / 8 /
+// 4 / 3 workgroups: FP64 band of 2e6 rows 284 / 184 / 195 / 221, power law
+// 460 / 471 / 465 / 464, SpTTV on 1e8 nonzeros 855 / 716 / 652 / 646; FP32
+// 177 / 116 / 154 / 182, 313 / 316 / 308 / 305 and 598 / 569 / 531 / 549.  The
+// band of 2e7 rows (FP64, 8.8 GB): 2,795 -> 1,959 us, 4.5 TB/s.
+constexpr int kOnceLds = 21000;
+
+template <typename V, int ITEMS, typename P = int32_t, typename TP = int32_t>
+__global__ __launch_bounds__(kBlock) void k_spmv_once(
+    int64_t n, const P *__restrict__ pos, const int32_t *__restrict__ crd,
+    const V *__restrict__ vals, const V *__restrict__ x, V *__restrict__ y,
+    const int32_t *__restrict__ trow, const TP *__restrict__ tpos, double *__restrict__ carry) {
+    static_assert(ITEMS == 4 || ITEMS == 8, "flags are read as one 4- or 8-byte word");
+    using Flags = typename std::conditional<ITEMS == 4, uint32_t, uint64_t>::type;
+    constexpr int kChunk = kBlock * ITEMS;
+    __shared__ double s_prod[kChunk + 1];  // products, then row sums; + a spare slot
+    __shared__ __align__(8) uint8_t s_flag[kChunk + 8];
+    __shared__ __align__(16) int s_wave_total[kBlock / kWave];
+    __shared__ int s_first_key[kBlock / kWave], s_last_key[kBlock / kWave];
+    __shared__ double s_last_val[kBlock / kWave];
+    __shared__ double s_open;
+    const int tid = threadIdx.x;
+    const int64_t c = blockIdx.x;
+    const int64_t bi = trow[c], bp = tpos[c];
+    const int nr = static_cast<int>(trow[c + 1] - bi), np = static_cast<int>(tpos[c + 1] - bp);
+    const auto rp = chunk_rsrc(pos + bi + 1, static_cast<int>(sizeof(P)) * nr);
+    const auto rc = chunk_rsrc(crd + bp, 4 * np);
+    const auto rv = chunk_rsrc(vals + bp, static_cast<int>(sizeof(V)) * np);
+    int k[ITEMS], e[ITEMS];
+    V v[ITEMS], xv[ITEMS];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+        k[j] = static_cast<int32_t>(__builtin_amdgcn_raw_buffer_load_b32(
+            rc, static_cast<uint32_t>(tid + j * kBlock) * 4, 0, kNtAux));
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const uint32_t q = static_cast<uint32_t>(tid + j * kBlock);
+        v[j] = chunk_load<V>(rv, q * static_cast<uint32_t>(sizeof(V)));
+        e[j] = static_cast<int32_t>(__builtin_amdgcn_raw_buffer_load_b32(
+            rp, q * static_cast<uint32_t>(sizeof(P)), 0, 0));  // low word
+    }
+    Flags &flag_word = reinterpret_cast<Flags *>(s_flag)[tid];
+    flag_word = 0;
+    if (np > 0) {  // lanes past the positions gather x[0]
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) xv[j] = x[k[j]];
+    }
+    __syncthreads();  // flags cleared
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const int q = tid + j * kBlock;
+        const int rel = static_cast<int>(static_cast<uint32_t>(e[j]) - static_cast<uint32_t>(bp));
+        s_flag[q < nr ? q + rel : kChunk] = 1;
+        s_prod[q < np ? q : kChunk] = to_f64(v[j]) * to_f64(xv[j]);
+    }
+    __syncthreads();
+    const int total = nr + np;
+    const int d0 = min(tid * ITEMS, total);
+    flag_walk<ITEMS>(flag_word, d0, min(d0 + ITEMS, total) - d0, nr, 0.0, s_prod, s_prod + np,
+                     s_prod + kChunk, s_wave_total, s_first_key, s_last_key, s_last_val, &s_open);
+    __syncthreads();
+    for (int q = tid; q < nr; q += kBlock) store_stream(y + bi + q, static_cast<V>(s_prod[np + q]));
+    if (tid == 0) carry[c] = s_open;
+}
+
+// Small matrices in one launch, with no partition and no carries.  Row r
+// starts at merged item r + pos[r]; workgroup t owns the rows that start in
+// its kSmallChunk items [t * kSmallChunk, (t + 1) * kSmallChunk), found by two
+// searches of 64 probes a step, and sums them whole.  All its rows but the
+// last lie within those items, so one flag walk sums them and what it has
+// room for of the last one; the rest of that row is summed by the whole
+// workgroup, kSmallDeep positions a lane at a time.  For calls so small that
+// the launches (partition, leaf, fix-up) are what they cost: 4,096 rows of 10
+// FP64 entries take 9.7 us a call against 16.4 (host included).
+constexpr int kSmallItems = 4;
+constexpr int kSmallChunk = kBlock * kSmallItems;
+constexpr int kSmallDeep = 16;
+
+// First row r in [0, n] with r + pos[r] >= d (n if none), by one wave.
+template <typename P>
+__device__ __forceinline__ int64_t wave_first_row(const P *__restrict__ pos, int64_t n, int64_t d) {
+    const int lane = threadIdx.x & (kWave - 1);
+    int64_t lo = -1, hi = n;  // row lo starts before d (or lo == -1); row hi does not, or hi == n
+    while (hi - lo > 1) {
+        const int64_t step = (hi - lo + kWave - 1) / kWave;
+        const int64_t at = lo + (lane + 1) * step;
+        const bool before = at < hi && at + static_cast<int64_t>(pos[at]) < d;
+        const int k = __popcll(__ballot(before));
+        hi = lo + (k + 1) * step < hi ? lo + (k + 1) * step : hi;
+        lo += k * step;
+    }
+    return hi;
+}
+
+template <typename V, typename P>
+__global__ __launch_bounds__(kBlock) void k_spmv_small(
+    int64_t n, const P *__restrict__ pos, const int32_t *__restrict__ crd,
+    const V *__restrict__ vals, const V *__restrict__ x, V *__restrict__ y) {
+    constexpr int ITEMS = kSmallItems, kChunk = kSmallChunk;
+    __shared__ double s_prod[kChunk + 1];  // products, then row sums; + a spare slot
+    __shared__ __align__(8) uint8_t s_flag[kChunk + 8];
+    __shared__ __align__(16) int s_wave_total[kBlock / kWave];
+    __shared__ int s_first_key[kBlock / kWave], s_last_key[kBlock / kWave];
+    __shared__ double s_last_val[kBlock / kWave];
+    __shared__ double s_open;
+    __shared__ int64_t s_row[2];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    uint32_t &flag_word = reinterpret_cast<uint32_t *>(s_flag)[tid];
+    flag_word = 0;
+    if (wave < 2) {
+        const int64_t r = wave_first_row(pos, n, (static_cast<int64_t>(blockIdx.x) + wave) * kChunk);
+        if (lane == 0) s_row[wave] = r;
+    }
+    __syncthreads();
+    const int64_t r0 = s_row[0];
+    const int rows = static_cast<int>(s_row[1] - r0);  // at most kChunk
+    if (rows == 0) return;
+    const int32_t p0 = static_cast<int32_t>(pos[r0]), p1 = static_cast<int32_t>(pos[r0 + rows]);
+    // the walk takes the whole of every row, or the last row's first positions
+    const bool whole = rows + (p1 - p0) <= kChunk;
+    const int nr = whole ? rows : rows - 1;
+    const int np = whole ? p1 - p0 : kChunk - nr;
+    const auto rp = chunk_rsrc(pos + r0 + 1, static_cast<int>(sizeof(P)) * nr);
+    const auto rc = chunk_rsrc(crd + p0, 4 * np);
+    const auto rv = chunk_rsrc(vals + p0, static_cast<int>(sizeof(V)) * np);
+    int k[ITEMS], e[ITEMS];
+    V v[ITEMS], xv[ITEMS];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const uint32_t q = static_cast<uint32_t>(tid + j * kBlock);
+        k[j] = static_cast<int32_t>(__builtin_amdgcn_raw_buffer_load_b32(rc, q * 4, 0, 0));
+        v[j] = chunk_load<V>(rv, q * static_cast<uint32_t>(sizeof(V)));
+        e[j] = static_cast<int32_t>(__builtin_amdgcn_raw_buffer_load_b32(
+            rp, q * static_cast<uint32_t>(sizeof(P)), 0, 0));  // low word
+    }
+    if (np > 0) {  // lanes past the positions gather x[0]
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) xv[j] = x[k[j]];
+    }
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const int q = tid + j * kBlock;
+        s_flag[q < nr ? q + (e[j] - p0) : kChunk] = 1;
+        s_prod[q < np ? q : kChunk] = to_f64(v[j]) * to_f64(xv[j]);
+    }
+    __syncthreads();
+    const int total = nr + np, d0 = min(tid * ITEMS, total);
+    flag_walk<ITEMS>(flag_word, d0, min(d0 + ITEMS, total) - d0, nr, 0.0, s_prod, s_prod + np,
+                     s_prod + kChunk, s_wave_total, s_first_key, s_last_key, s_last_val, &s_open);
+    __syncthreads();
+    for (int q = tid; q < nr; q += kBlock) store_stream(y + r0 + q, static_cast<V>(s_prod[np + q]));
+    if (whole) return;
+    double part = 0.0;
+    for (int32_t q0 = p0 + np; q0 < p1; q0 += kSmallDeep * kBlock) {
+        const int left = p1 - q0;
+        const auto lc = chunk_rsrc(crd + q0, 4 * min(left, kSmallDeep * kBlock));
+        const auto lv = chunk_rsrc(vals + q0, static_cast<int>(sizeof(V)) * min(left, kSmallDeep * kBlock));
+        int c[kSmallDeep];
+        V w[kSmallDeep], z[kSmallDeep];
+#pragma unroll
+        for (int j = 0; j < kSmallDeep; ++j) {
+            const uint32_t q = static_cast<uint32_t>(tid + j * kBlock);
+            c[j] = static_cast<int32_t>(__builtin_amdgcn_raw_buffer_load_b32(lc, q * 4, 0, 0));
+            w[j] = chunk_load<V>(lv, q * static_cast<uint32_t>(sizeof(V)));
+        }
+#pragma unroll
+        for (int j = 0; j < kSmallDeep; ++j) z[j] = x[c[j]];  // past the row: x[0], not added
+#pragma unroll
+        for (int j = 0; j < kSmallDeep; ++j)
+            part += tid + j * kBlock < left ? to_f64(w[j]) * to_f64(z[j]) : 0.0;
+    }
+    part = group_sum<kWave>(part);
+    if (lane == 0) s_last_val[wave] = part;
+    __syncthreads();
+    if (tid == 0) {
+        double sum = s_open;
+        for (int w = 0; w < kBlock / kWave; ++w) sum += s_last_val[w];
+        store_stream(y + r0 + nr, static_cast<V>(sum));
+    }
 }
 
 // Merge-split leaf that sums whole rows per lane (schedule variant 2).  The
@@ -822,29 +1034,8 @@ __global__ __launch_bounds__(kBlock) void k_spmv_window_flag(
         const int steps = min(d0 + ITEMS, total) - d0;
         const Flags fl = flag_word;
         flag_word = 0;  // cleared for the next chunk
-        int a = block_exclusive_sum(static_cast<int>(__builtin_popcountll(fl)), s_wave_total);
-        int b = d0 - a;
-        double acc = tid == 0 ? open : 0.0;
-#pragma unroll
-        for (int st = 0; st < ITEMS; ++st) {
-            const bool fin = (fl >> (8 * st)) & 1;
-            const bool add = !fin && st < steps;
-            const double pv = s_prod[b];  // b <= np <= kChunk
-            s_out[fin ? a : kChunk] = acc;
-            acc = (fin ? 0.0 : acc) + (add ? pv : 0.0);
-            a += fin ? 1 : 0;
-            b += add ? 1 : 0;
-        }
-        double v = block_segmented_scan_dpp(acc, a, s_first_key, s_last_key, s_last_val);
-        int next_key = __shfl_down(a, 1);
-        const int lane = tid & (kWave - 1), wave = tid / kWave;
-        if (lane == kWave - 1) next_key = wave + 1 < kBlock / kWave ? s_first_key[wave + 1] : -1;
-        if (next_key != a) {
-            if (a < nr)
-                s_out[a] += v;
-            else
-                s_open = v;
-        }
+        flag_walk<ITEMS>(fl, d0, steps, nr, open, s_prod, s_out, s_out + kChunk, s_wave_total,
+                         s_first_key, s_last_key, s_last_val, &s_open);
         __syncthreads();
         for (int k = tid; k < nr; k += kBlock) store_stream(y + bi + k, static_cast<V>(s_out[k]));
         open = s_open;
@@ -885,6 +1076,15 @@ hipError_t spmv_tiles_dispatch(int items, int64_t n, const int32_t *pos, const i
         else
             k_spmv_rows<V, 8><<<grid, kBlock, 0, s>>>(n, pos, crd, vals, x, y, t.row, t.pos,
                                                        t.ntiles, stride, carry);
+        return hipGetLastError();
+    }
+    if (exact && variant == 0 && stride == 1) {
+        if (items <= 4)
+            k_spmv_once<V, 4><<<grid, kBlock, kOnceLds, s>>>(n, pos, crd, vals, x, y, t.row, t.pos,
+                                                              carry);
+        else
+            k_spmv_once<V, 8><<<grid, kBlock, kOnceLds, s>>>(n, pos, crd, vals, x, y, t.row, t.pos,
+                                                              carry);
         return hipGetLastError();
     }
     if (exact && variant == 0) {
@@ -930,6 +1130,33 @@ hipError_t launch_spmv_fixup(int dtype, int64_t n, const Tiles &t, int64_t strid
     return spmv_fixup_dispatch<float>(n, t, stride, carry, static_cast<float *>(y), s);
 }
 
+// Items that the small-matrix leaf takes, and the longest row (a bound is
+// enough) that one of its workgroups should be left with: 256 workgroups, one
+// per CU, and eight rounds of a long row's positions, about what the
+// partition and fix-up launches take on the GPU.
+bool spmv_is_small(int64_t n, int64_t m, int64_t nnz) {
+    return n + nnz <= 256 * kSmallChunk && std::min(m, nnz) <= 8 * kSmallDeep * kBlock;
+}
+
+hipError_t launch_spmv_small(int dtype, bool pos64, int64_t n, int64_t nnz, const void *pos,
+                             const int32_t *crd, const void *vals, const void *x, void *y,
+                             hipStream_t s) {
+    // row n - 1 starts at most at item n - 1 + nnz
+    const dim3 grid(static_cast<unsigned>(ceil_div(n + nnz, kSmallChunk)));
+    auto go = [&](auto *v, auto *p) {
+        using V = std::remove_const_t<std::remove_pointer_t<decltype(v)>>;
+        using P = std::remove_const_t<std::remove_pointer_t<decltype(p)>>;
+        k_spmv_small<V, P><<<grid, kBlock, 0, s>>>(n, p, crd, v, static_cast<const V *>(x),
+                                                   static_cast<V *>(y));
+        return hipGetLastError();
+    };
+    auto typed = [&](auto *v) {
+        return pos64 ? go(v, static_cast<const int64_t *>(pos)) : go(v, static_cast<const int32_t *>(pos));
+    };
+    if (dtype == SPL_F64) return typed(static_cast<const double *>(vals));
+    return typed(static_cast<const float *>(vals));
+}
+
 hipError_t launch_spmv_row(int dtype, int lanes, int64_t n, const int32_t *pos_b,
                            const int32_t *pos_e, const int32_t *crd, const void *vals,
                            const void *x, void *y, hipStream_t s) {
@@ -970,6 +1197,15 @@ hipError_t launch_spmv_flag64(int dtype, int items, int64_t n, const int64_t *po
     dim3 grid(static_cast<unsigned>(ceil_div(t.ntiles, stride)));
     auto go = [&](auto *v, auto *xx, auto *yy) {
         using V = std::remove_const_t<std::remove_pointer_t<decltype(v)>>;
+        if (stride == 1) {
+            if (items <= 4)
+                k_spmv_once<V, 4, int64_t, int64_t><<<grid, kBlock, kOnceLds, s>>>(
+                    n, pos, crd, v, xx, yy, t.row, t.pos64, carry);
+            else
+                k_spmv_once<V, 8, int64_t, int64_t><<<grid, kBlock, kOnceLds, s>>>(
+                    n, pos, crd, v, xx, yy, t.row, t.pos64, carry);
+            return hipGetLastError();
+        }
         if (items <= 4)
             k_spmv_flag<V, 4, int64_t, int64_t><<<grid, kBlock, 0, s>>>(
                 n, pos, crd, v, xx, yy, t.row, t.pos64, t.ntiles, stride, carry);

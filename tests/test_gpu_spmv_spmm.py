@@ -263,6 +263,45 @@ def test_spmv_deterministic():
         assert torch.equal(y1, y2), sc
 
 
+# The one-launch leaf of small matrices: chunks of 1,024 merged items, rows
+# summed by the workgroup in whose chunk they start.  Row lengths that end at,
+# before and after a chunk's edge; a last row far past the walk (its rounds of
+# 4,096 positions ragged and whole); empty rows filling chunks; the largest
+# total that takes this leaf and one above it; the longest row that does and
+# one above.
+SMALL_ROWS = {
+    "edges": [1023, 0, 1022, 1, 1024, 0, 1025, 2047, 3, 0, 0],
+    "long_after_short": [1] * 511 + [9000] + [2] * 5, "long_first": [4096 + 1023, 0, 7],
+    "whole_rounds": [1023 + 3 * 4096], "empty_chunks": [0] * 5000 + [3] + [0] * 3000,
+    "trailing_long": [5] * 200 + [32768], "largest": [15] * 16384, "above": [15] * 16384 + [0],
+    "longest": [32768], "above_longest": [32769],
+}
+
+
+@pytest.mark.parametrize("name", list(SMALL_ROWS))
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_spmv_default_on_small_matrices(name, dtype):
+    spl = _spl()
+    deg = np.array(SMALL_ROWS[name])
+    n, m = deg.size, max(40, int(deg.max()))
+    pos = np.concatenate([[0], np.cumsum(deg)])
+    crd = np.concatenate([np.arange(d) for d in deg]) if pos[-1] else np.zeros(0)
+    rs = np.random.RandomState(n)
+    print(f"small spmv {name} n={n} nnz={pos[-1]} {dtype}", flush=True)
+    for kind in ("float", "int"):
+        draw = (lambda k: rs.randint(-4, 5, k)) if kind == "int" else (lambda k: rs.uniform(-1, 1, k))
+        B = _csr(spl, pos, crd, draw(int(pos[-1])), (n, m), dtype)
+        x = torch.as_tensor(draw(m), device=dev()).to(dtype)
+        ref, S = oracle.spmv(pos.astype(np.int32), crd.astype(np.int32), host64(B.vals), host64(x))
+        y = spl.spmv(B, x, a=torch.full((n,), float("nan"), dtype=dtype, device=dev()))
+        B64 = spl.CSR(B.pos.to(torch.int64), B.crd, B.vals, B.shape)
+        assert torch.equal(y, spl.spmv(B64, x)), "int64 positions"
+        if kind == "int":
+            assert np.array_equal(host64(y), ref)
+        else:
+            assert_close(host64(y), ref, S, RTOL[dtype], name)
+
+
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("N", [32, 5, 70])
 def test_spmm_powerlaw_scaled(dtype, N):
