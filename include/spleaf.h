@@ -337,12 +337,14 @@ spl_status spl_spmv_window(spl_context *ctx, const spl_sparse *B, const int32_t 
  * NNZ and MERGE splits a row that spans tiles is the finishing tile's
  * partial plus the other tiles' carries, added by the fix-up).  Schedules:
  * ROW, NNZ, MERGE (default MERGE); col_tile 8..64 columns per lane group.
- * sched->variant (MERGE): 0 = each lane reads and writes 4 F32, 2 F64 or 8
- * BF16 consecutive columns (16 bytes of C) with one vector access when N,
- * C->ld, A->ld and the C and A pointers are multiples of that, col_tile
- * leaves 4 to 32 lanes per group and items_per_lane is 8 or 16 (otherwise
- * one column per lane); 1 = one column per lane; 2 (BF16 only) = as 0 with
- * 4 BF16 columns (8 bytes) per lane.
+ * sched->variant (MERGE): 0 = each lane reads and writes v = 4 F32, 2 F64 or
+ * 8 BF16 consecutive columns (16 bytes of C) with one vector access when N is
+ * at least v, col_tile leaves 4 to 32 lanes per group and items_per_lane is 8
+ * or 16 (otherwise one column per lane, as for F64 columns that fill three
+ * quarters of such lanes without being a multiple of v); with int64 positions
+ * N, C->ld, A->ld and the C and A pointers must be multiples of v; 1 = one
+ * column per lane; 2 (BF16 only) = 4 BF16 columns (8 bytes) per lane when N
+ * and the others are multiples of that.
  * The workspace query returns the one-column-per-lane size, enough for
  * both.  SPL_SCHED_LEARNED / SPL_SCHED_AUTOTUNE as for spl_spmv. */
 spl_status spl_spmm(spl_context *ctx, const spl_sparse *B, const spl_dense *C,

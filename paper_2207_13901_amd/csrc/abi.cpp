@@ -210,14 +210,22 @@ spl_status resolve_spmm(spl_context *ctx, const spl_sparse *B, int64_t N, const 
     if (p.kind != SPL_ROW && p.kind != SPL_NNZ && p.kind != SPL_MERGE)
         return fail(ctx, SPL_ERR_ARG, "unknown schedule kind %d", s->kind);
     int ct = s->col_tile;
+    p.items = s->items_per_lane ? s->items_per_lane : 16;
     if (!ct) {
         ct = 8;
+        // the fewest columns that leave vector lanes a group of four, when
+        // the columns fill at least one of them: the idle lanes cost less
+        // than one column per lane (1e6 rows of 16 entries, BF16: 8 columns
+        // 278 us against 309, 16 columns 294 against 491; FP32, 1e5 rows: 8
+        // columns 31.6 against 38.5)
+        const int v = spl::spmm_vec_width(B->vtype);
+        if (p.kind == SPL_MERGE && s->variant == 0 && p.items <= 16 && B->pos_type == SPL_I32 && N >= v)
+            ct = 4 * v;
         while (ct < 64 && ct < N) ct <<= 1;
     }
     if (ct != 8 && ct != 16 && ct != 32 && ct != 64)
         return fail(ctx, SPL_ERR_ARG, "col_tile must be 8, 16, 32 or 64");
     p.col_tile = ct;
-    p.items = s->items_per_lane ? s->items_per_lane : 16;
     if (p.items != 8 && p.items != 16 && p.items != 32)
         return fail(ctx, SPL_ERR_ARG, "SpMM items_per_lane must be 8, 16 or 32");
     p.tile = s->tile ? s->tile : (p.kind == SPL_ROW ? 256 / ct : 4 * (256 / ct) * p.items);
@@ -370,21 +378,40 @@ int64_t spmm_chunk(const Plan &p) { return (256 / (p.col_tile / p.vec)) * p.item
 
 size_t dtype_bytes(int dt) { return dt == SPL_F64 ? 8 : dt == SPL_F32 ? 4 : 2; }
 
+// Whether every row element that a vector lane starts at is 4-byte aligned,
+// as the buffer-descriptor gathers need: always but for BF16 rows of an odd
+// column count or leading dimension.
+bool dword_rows(const spl_dense *d) {
+    return d->dtype != SPL_BF16 || (d->dims[1] % 2 == 0 && d->ld % 2 == 0 &&
+                                    reinterpret_cast<uintptr_t>(d->data) % 4 == 0);
+}
+
 // Vector lanes for the merge-split SpMM leaf: each lane reads and writes v
 // columns with one vector access (variant 0: spl::spmm_vec_width, 16 bytes;
-// variant 2: 4 BF16 columns, 8 bytes), when the columns, leading dimensions
-// and pointers allow it and a lane group still has 4 to 32 lanes and walks
-// 8 or 16 items; otherwise one column per lane.
-int spmm_vec(const Plan &p, int vtype, const spl_dense *C, const spl_dense *A) {
+// variant 2: 4 BF16 columns, 8 bytes), when a lane group still has 4 to 32
+// lanes and walks 8 or 16 items and the columns, leading dimensions and
+// pointers allow it; otherwise one column per lane.  With int64 positions and
+// for variant 2 they have to be multiples of v; else any will do from v
+// columns on, a last vector that would reach past the row starting earlier
+// (lane_col).  One column per lane leaves
+// lanes idle when the columns do not fill them and loads 2 to 8 bytes a lane:
+// 100,000 rows of 16 entries against 33 columns take 123 us in FP64, 103 in
+// FP32 and 170 in BF16 that way, 95, 64 and 49 with vectors.
+int spmm_vec(const Plan &p, int vtype, bool pos64, const spl_dense *C, const spl_dense *A) {
     if (p.kind != SPL_MERGE || p.variant == 1 || p.items > 16) return 1;
     const int v = p.variant == 2 ? 4 : spl::spmm_vec_width(vtype);
     const int64_t lanes = p.col_tile / v;
+    if (lanes < 4 || lanes > 32) return 1;
     const int64_t N = C->dims[1];
     const size_t cb = v * dtype_bytes(C->dtype), ab = v * dtype_bytes(A->dtype);
-    const bool ok = lanes >= 4 && lanes <= 32 && N % v == 0 && C->ld % v == 0 &&
-                    A->ld % v == 0 && reinterpret_cast<uintptr_t>(C->data) % cb == 0 &&
-                    reinterpret_cast<uintptr_t>(A->data) % ab == 0;
-    return ok ? v : 1;
+    const bool even = N % v == 0 && C->ld % v == 0 && A->ld % v == 0 &&
+                      reinterpret_cast<uintptr_t>(C->data) % cb == 0 &&
+                      reinterpret_cast<uintptr_t>(A->data) % ab == 0;
+    if (even) return v;
+    // FP64 columns fill three quarters of one-column lanes: nothing to gain (31
+    // columns, C of 248 MB: 845 us with one column per lane, 867 with vectors)
+    if (C->dtype == SPL_F64 && (N + p.col_tile - 1) / p.col_tile * p.col_tile * 3 < N * 4) return 1;
+    return !pos64 && p.variant == 0 && N >= v ? v : 1;
 }
 
 size_t tiled_ws(const Pieces &q, int64_t ncols, size_t elem, size_t pos_bytes = 4) {
@@ -1265,7 +1292,7 @@ spl_status spl_spmm(spl_context *ctx, const spl_sparse *B, const spl_dense *C, s
         return SPL_OK;
     }
     // the workspace query assumed one column per lane: the larger size
-    p.vec = spmm_vec(p, B->vtype, C, A);
+    p.vec = spmm_vec(p, B->vtype, pos64, C, A);
     if (pos64 && p.vec != spl::spmm_vec_width(B->vtype))
         return fail(ctx, SPL_ERR_UNSUPPORTED,
                     "int64 positions: 16-byte vector lanes only (variant 0; N, every ld and the "
@@ -1275,9 +1302,9 @@ spl_status spl_spmm(spl_context *ctx, const spl_sparse *B, const spl_dense *C, s
     const Pieces q = pieces_for(p, n, B->nnz, spmm_chunk(p));
     Carved cv = carve(ws, q.count, pos64);
     // branch-free row gathers when C's rows span at most a descriptor's range
-    const bool buf = static_cast<double>(C->dims[0]) * static_cast<double>(C->ld) *
-                         static_cast<double>(dtype_bytes(C->dtype)) <=
-                     spl::kBufRange;
+    const bool buf = dword_rows(C) && static_cast<double>(C->dims[0]) * static_cast<double>(C->ld) *
+                                              static_cast<double>(dtype_bytes(C->dtype)) <=
+                                          spl::kBufRange;
     if (pos64) {
         const int64_t *pos = reinterpret_cast<const int64_t *>(B->pos[1]);
         SPL_HIP(spl::launch_merge_bounds64(n, pos, B->nnz, q.size, cv.tiles, s),

@@ -54,11 +54,24 @@ __device__ __forceinline__ void store_stream(T *p, T v) {
 }
 
 // Rows of a dense operand read and written VEC consecutive elements per lane
-// (VEC > 1: one vector access of VEC elements, 16 bytes except for 4 BF16;
-// the address must be aligned to the access size).
-typedef float vf32x4 __attribute__((ext_vector_type(4)));
-typedef double vf64x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t vu32x4 __attribute__((ext_vector_type(4)));
+// (VEC > 1: one vector access of VEC elements, 16 bytes except for 4 BF16,
+// whose address must be 8-byte aligned).
+// The vectors below may sit at any element's address (the compiler's 16-byte
+// global accesses need no more), so rows of any column count and leading
+// dimension are read whole vectors at a time (lane_col).
+typedef float vf32x4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef double vf64x2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef uint32_t vu32x4 __attribute__((ext_vector_type(4), aligned(2)));  // 8 BF16
+
+// First of the VEC consecutive columns of vector lane `lane` of a row of N:
+// lane * VEC, or N - VEC for a last lane that would reach past the row (N at
+// least VEC).  Such a lane repeats columns of the one before it, with the
+// same operands in the same order, so what both store is the same.
+template <int VEC>
+__device__ __forceinline__ int64_t lane_col(int64_t lane, int64_t N) {
+    const int64_t c = lane * VEC;
+    return VEC > 1 && c + VEC > N ? N - VEC : c;
+}
 
 template <int VEC, typename Acc>
 __device__ __forceinline__ void load_row(const float *p, Acc (&o)[VEC]) {

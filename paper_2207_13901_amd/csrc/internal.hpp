@@ -83,12 +83,13 @@ hipError_t launch_spmm_row(int vtype, int otype, int col_tile, int64_t n, int64_
 // exact_chunks: every piece of `t` holds at most one leaf chunk
 // ((256 / lanes) * items merged items, lanes = col_tile / vec), as the merge
 // split is cut here; the leaf then pipelines its staging loads (k_spmm_pipe).
-// vec: 1, or spmm_vec_width(vtype) columns per lane (merge split only; N,
-// the leading dimensions and both dense pointers aligned to it, and
-// col_tile / vec in {8, 16, 32}).
+// vec: 1, or spmm_vec_width(vtype) columns per lane (merge split only; N at
+// least that and col_tile / vec in {4, 8, 16, 32}); 4 for BF16's narrow lanes
+// (N, the leading dimensions and both dense pointers aligned to it).
 int spmm_vec_width(int vtype);
 // buf: the pipelined leaf's 16-byte row gathers go through a buffer
-// descriptor (B's rows * ldb span at most kBufRange bytes).
+// descriptor (B's rows * ldb span at most kBufRange bytes and every row
+// starts, and ends, on 4 bytes).
 hipError_t launch_spmm_tiles(int vtype, int col_tile, int items, int vec, int64_t n, int64_t N,
                              const int32_t *pos, const int32_t *crd, const void *vals,
                              const void *B, int64_t ldb, void *C, int64_t ldc, const Tiles &t,

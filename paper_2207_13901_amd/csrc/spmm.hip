@@ -25,7 +25,8 @@
 //    (carry.hpp) adds carries into their rows in a fixed order.  Deterministic, no atomics.
 //
 //  * k_spmm_pipe: the merge-split form of k_spmm_tiles, with the staging
-//    loads of the next chunk software-pipelined behind the current walk.
+//    loads of the next chunk software-pipelined behind the current walk and
+//    16 bytes of columns per lane, whatever the column count (lane_col).
 #include "carry.hpp"
 #include "device.hpp"
 #include "internal.hpp"
@@ -219,9 +220,10 @@ __global__ __launch_bounds__(kBlock) void k_spmm_pipe(
 
     const int tid = threadIdx.x;
     const int g = tid / W, lane = tid % W;
-    // this lane's columns: col0 .. col0 + VEC - 1 (N is a multiple of VEC)
-    const int64_t col0 = (static_cast<int64_t>(blockIdx.y) * W + lane) * VEC;
-    const bool colok = col0 < N;
+    // this lane's columns: col0 .. col0 + VEC - 1
+    const int64_t vlane = static_cast<int64_t>(blockIdx.y) * W + lane;
+    const bool colok = vlane * VEC < N;
+    const int64_t col0 = lane_col<VEC>(vlane, N);
     const int64_t p0 = static_cast<int64_t>(blockIdx.x) * stride;
     const int64_t pend = p0 + stride < npieces ? p0 + stride : npieces;
     auto bound_i = [&](int64_t c) { return static_cast<int64_t>(trow[c < pend ? c : pend]); };
@@ -351,7 +353,9 @@ __global__ __launch_bounds__(kBlock) void k_spmm_pipe(
         // groups, then starts from the partials of the parts before it.
         {
             const int cc = tid % NC, part = tid / NC;
-            const int64_t gcol = static_cast<int64_t>(blockIdx.y) * NC + cc;
+            const int64_t clane = static_cast<int64_t>(blockIdx.y) * W + cc / VEC;
+            const bool gok = clane * VEC < N;
+            const int64_t gcol = lane_col<VEC>(clane, N) + cc % VEC;
             int pa = 1;
             Acc pb = 0;
             for (int k = 0; k < kGroupsPerPart; ++k) {
@@ -368,7 +372,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_pipe(
             for (int k = 0; k < kGroupsPerPart; ++k) {
                 const int gg = part * kGroupsPerPart + k;
                 if (s_done[gg] > 0) {
-                    if (gcol < N)
+                    if (gok)
                         store_stream(Out + (ci + s_a0[gg]) * ldo + gcol, narrow<OT>(o + s_head[gg][cc]));
                     o = s_tail[gg][cc];
                 } else {
@@ -390,8 +394,9 @@ __global__ __launch_bounds__(kBlock) void k_spmm_pipe(
     }
     __syncthreads();  // the last part's s_open
     if (tid < NC) {
-        const int64_t gcol = static_cast<int64_t>(blockIdx.y) * NC + tid;
-        if (gcol < N) carry[static_cast<int64_t>(blockIdx.x) * N + gcol] = s_open[tid];
+        const int64_t clane = static_cast<int64_t>(blockIdx.y) * W + tid / VEC;
+        const int64_t gcol = lane_col<VEC>(clane, N) + tid % VEC;
+        if (clane * VEC < N) carry[static_cast<int64_t>(blockIdx.x) * N + gcol] = s_open[tid];
     }
 }
 

@@ -445,3 +445,33 @@ def test_spmm_int64_positions_match_int32(dtype):
     for bad in (dict(kind="nnz", tile=512), dict(kind="row"), dict(kind="merge", variant=1)):
         with pytest.raises(spl.SpleafError, match="SPL_ERR_UNSUPPORTED"):
             spl.spmm(B64, Bd, sched=spl.schedule(**bad))
+
+
+# Vector lanes on any column count, leading dimension and element alignment:
+# edges of a lane, of a group and of a block of groups; C and A contiguous, or
+# views of wider arrays one element in (A's other entries must stay as they
+# were).  Small integers: every schedule's sums are exact.
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 7, 8, 9, 15, 16, 17, 31, 33, 63, 65, 127, 130])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32, torch.bfloat16])
+def test_spmm_ragged_columns(dtype, N):
+    spl = _spl()
+    rs = np.random.RandomState(N)
+    pos, crd, _ = tiny.csr(rs, 90, 70, 0.1, empty_rows={0, 50, 89}, full_rows={3, 4})
+    for kind in ("int", "float"):
+        draw = (lambda s: rs.randint(-4, 5, s)) if kind == "int" else (lambda s: rs.uniform(-1, 1, s))
+        B = _csr(spl, pos, crd, draw(crd.size), (90, 70), dtype)
+        C = torch.as_tensor(draw((70, N)), device=dev()).to(dtype)
+        ref, S = oracle.spmm(pos, crd, host64(B.vals), host64(C))
+        wide = torch.zeros(70, N + 3, dtype=dtype, device=dev())
+        wide[:, 1:N + 1] = C
+        odt = torch.float32 if dtype == torch.bfloat16 else dtype
+        for Cv in (C, wide[:, 1:N + 1]):
+            for sc in (None, dict(kind="merge", items_per_lane=8), dict(kind="merge", col_tile=64, tile=700)):
+                out = torch.full((90, N + 5), float("nan"), dtype=odt, device=dev())
+                print(f"spmm ragged {dtype} N={N} ld={Cv.stride(0)} {kind} {sc}", flush=True)
+                A = spl.spmm(B, Cv, A=out[:, 2:N + 2], sched=spl.schedule(**sc) if sc else None)
+                assert torch.isnan(out[:, :2]).all() and torch.isnan(out[:, N + 2:]).all()
+                if kind == "int":
+                    assert np.array_equal(host64(A), ref), sc
+                else:
+                    assert_close(host64(A), ref, S, RTOL[dtype], f"{dtype} N={N} {sc}")
