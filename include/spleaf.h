@@ -422,8 +422,8 @@ spl_status spl_inner(spl_context *ctx, const spl_sparse *B, const spl_sparse *C,
  * (Sec. V-B): A is the vector of B->nnz output values (A.pos = B.pos,
  * A.crd = B.crd).  dtypes (vals, C, D, A): all F64; all F32; or
  * (F32, BF16, BF16, F32) with F32 accumulation.  sched->variant: 0 = vector
- * ALU dot products (default; 16-byte factor accesses when K and both ld are
- * multiples of 2 F64, 4 F32 or 8 BF16 and the factors are 16-byte aligned),
+ * ALU dot products (default; 16-byte factor accesses from K = 2 F64, 4 F32
+ * or 8 BF16 on),
  * 1 = matrix cores (BF16 factors only, K a multiple of 32, ld a multiple of
  * 8, 16-byte aligned factors).  Schedules: MERGE (default), NNZ, ROW. */
 spl_status spl_sddmm(spl_context *ctx, const spl_sparse *B, const spl_dense *C,

@@ -166,9 +166,9 @@ hipError_t launch_inner_general(int vtype, int order, int64_t n, int64_t units,
 int64_t sddmm_chunk();
 // Factor elements per 16-byte access (2 F64, 4 F32, 8 BF16).
 int sddmm_vec_width(int ftype);
-// vec_lanes (variant 0): 0 = one element per lane access; 8, 16 or 32 =
-// lanes per position reading sddmm_vec_width(ftype) elements each (K, ldc,
-// ldd multiples of it, factors 16-byte aligned).
+// vec_lanes (variant 0): 0 = one element per lane access; 4, 8, 16 or 32 =
+// lanes per position reading sddmm_vec_width(ftype) elements each (K at
+// least that).
 hipError_t launch_sddmm(int vtype, int ftype, int variant, int vec_lanes, int64_t K,
                         const int32_t *pos, const int32_t *crd, const void *bv, const void *C,
                         int64_t ldc, const void *D, int64_t ldd, void *out, const Tiles &t,

@@ -11,15 +11,17 @@
 //    C(i,k) D(j,k) for k = l, l+32, ... (every row access is coalesced), then
 //    a 32-lane butterfly.  FP64, FP32, or BF16 factors with FP32
 //    accumulation.
-//  * k_sddmm_vec: the same with vector lanes (16-byte factor accesses) and
-//    8, 16 or 32 lanes per position, two positions per lane group in
-//    flight.
+//  * k_sddmm_vec: the same with vector lanes (16-byte factor accesses, any K
+//    of at least one vector and any alignment) and 4, 8, 16 or 32 lanes per
+//    position, two positions per lane group in flight.
 //  * k_sddmm_mfma: BF16 factors on the matrix cores.  A wave takes 16
 //    positions; v_mfma_f32_16x16x32_bf16 multiplies the 16 gathered C rows
 //    (as A, 16 x 32 per step) by the 16 gathered D rows (as B, 32 x 16) and
 //    the diagonal of the 16 x 16 FP32 result holds the 16 dot products.
 //    Only 1/16 of the MFMA work is kept, but the operation is bound by the
 //    D-row gathers, not by arithmetic.
+#include <type_traits>
+
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -98,69 +100,100 @@ __global__ __launch_bounds__(kBlock) void k_sddmm_valu(
 }
 
 // k_sddmm_valu with vector lanes: a group of L lanes per position, each lane
-// reading VEC consecutive k of the C and D rows with one vector access
-// (K, ldc, ldd multiples of VEC, factors aligned), P positions per group in
-// flight; then an L-lane butterfly.
-template <typename V, typename FT, typename Acc, int CHUNK, int L, int VEC, int P>
+// reading VEC consecutive k of the C and D rows with one vector access, P
+// positions per group at a time; then an L-lane butterfly.  The chunk's column
+// coordinates and values are loaded with its row ends (one of each position
+// per thread and 256 positions, coalesced) and its dot products go to LDS and
+// leave with coalesced stores, so that in the loop over positions a gather
+// waits for LDS only.  RAG: K is no multiple of VEC (but at least VEC); the
+// vector that would reach past the row starts earlier and its elements before
+// its own first one count for nothing.
+//
+// Bound by the D-row gathers: 8e6 positions at K = 128 take 0.65 ms in FP32 and
+// 0.33 in BF16 (7.2 TB/s of D and C rows); with the coordinates read, and the
+// values read and results stored by one lane per group, inside the loop 0.85
+// and 0.42.  K = 100, BF16: 0.39 ms, 0.85 with one element per lane.
+template <typename V, typename FT, typename Acc, int CHUNK, int L, int VEC, int P, bool RAG>
 __global__ __launch_bounds__(kBlock) void k_sddmm_vec(
     int64_t K, const int32_t *__restrict__ pos, const int32_t *__restrict__ crd,
     const V *__restrict__ bv, const FT *__restrict__ C, int64_t ldc, const FT *__restrict__ D,
     int64_t ldd, V *__restrict__ out, const int32_t *__restrict__ trow,
     const int32_t *__restrict__ tpos, int64_t npieces, int64_t stride) {
+    constexpr int kPer = CHUNK / kBlock;
+    static_assert(kPer * kBlock == CHUNK, "whole positions per thread");
     __shared__ int32_t s_end[CHUNK];
     __shared__ int32_t s_row[CHUNK];
+    __shared__ int32_t s_col[CHUNK];
+    __shared__ Acc s_dot[CHUNK];
     __shared__ int64_t s_next[2];
     constexpr int kGroups = kBlock / L;
-    const int grp = threadIdx.x / L, lane = threadIdx.x % L;
+    const int tid = threadIdx.x, grp = tid / L, lane = tid % L;
     int64_t piece = static_cast<int64_t>(blockIdx.x) * stride;
     const int64_t piece_end = piece + stride < npieces ? piece + stride : npieces;
     int64_t ci = trow[piece], cp = tpos[piece];
     while (piece < piece_end) {
-        piece = chunk_end(pos, trow, tpos, piece, ci, cp, CHUNK, s_next);
-        const int64_t ei = s_next[0], ep = s_next[1];
+        // a piece that ends within this chunk needs no search
+        int64_t ei = trow[piece + 1], ep = tpos[piece + 1], next = piece + 1;
+        if (ei + ep - ci - cp > CHUNK) {
+            next = chunk_end(pos, trow, tpos, piece, ci, cp, CHUNK, s_next);
+            ei = s_next[0];
+            ep = s_next[1];
+        }
+        piece = next;
         const int nr = static_cast<int>(ei - ci), np = static_cast<int>(ep - cp);
+        V val[kPer];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int k = tid + j * kBlock;
+            if (k < np) {
+                s_col[k] = load_stream(crd + cp + k);
+                val[j] = load_stream(bv + cp + k);
+            }
+        }
         chunk_rows(pos, ci, cp, nr, np, s_end, s_row);
         for (int k = grp; k < np; k += P * kGroups) {
             const FT *crow[P];
             const FT *drow[P];
-            bool live[P];
 #pragma unroll
             for (int u = 0; u < P; ++u) {
-                const int ku = k + u * kGroups;
-                live[u] = ku < np;
-                const int kk = live[u] ? ku : k;  // dead slots reread a live position
+                const int ku = k + u * kGroups, kk = ku < np ? ku : k;  // dead slots repeat a live one
                 crow[u] = C + static_cast<int64_t>(s_row[kk]) * ldc;
-                // (the default cache policy: the next iteration's positions
-                // share these lines)
-                drow[u] = D + static_cast<int64_t>(crd[cp + kk]) * ldd;
+                drow[u] = D + static_cast<int64_t>(s_col[kk]) * ldd;
             }
             Acc a[P];
 #pragma unroll
             for (int u = 0; u < P; ++u) a[u] = 0;
             for (int64_t k0 = static_cast<int64_t>(lane) * VEC; k0 < K; k0 += L * VEC) {
-                Acc cr[P][VEC], dr[P][VEC];
+                const int64_t at = RAG && k0 + VEC > K ? K - VEC : k0;
+                const int skip = RAG ? static_cast<int>(k0 - at) : 0;
+                RowVec<VEC, FT> cr[P], dr[P];
 #pragma unroll
                 for (int u = 0; u < P; ++u) {
-                    load_row<VEC>(crow[u] + k0, cr[u]);
-                    load_row<VEC>(drow[u] + k0, dr[u]);
+                    cr[u].load(crow[u] + at);
+                    dr[u].load(drow[u] + at);
                 }
 #pragma unroll
                 for (int u = 0; u < P; ++u) {
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) a[u] += cr[u][v] * dr[u][v];
+                    for (int v = 0; v < VEC; ++v) {
+                        const Acc t = a[u] + static_cast<Acc>(cr[u].at(v)) * static_cast<Acc>(dr[u].at(v));
+                        a[u] = RAG && v < skip ? a[u] : t;
+                    }
                 }
             }
 #pragma unroll
             for (int u = 0; u < P; ++u) a[u] = group_sum<L>(a[u]);
             if (lane == 0) {
 #pragma unroll
-                for (int u = 0; u < P; ++u) {
-                    if (live[u]) {
-                        const int64_t p = cp + k + u * kGroups;
-                        store_stream(out + p, static_cast<V>(widen<Acc>(load_stream(bv + p)) * a[u]));
-                    }
-                }
+                for (int u = 0; u < P; ++u)
+                    if (k + u * kGroups < np) s_dot[k + u * kGroups] = a[u];
             }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int k = tid + j * kBlock;
+            if (k < np) store_stream(out + cp + k, static_cast<V>(widen<Acc>(val[j]) * s_dot[k]));
         }
         ci = ei;
         cp = ep;
@@ -238,15 +271,19 @@ hipError_t sddmm_vec(int lanes, dim3 grid, int64_t K, const int32_t *pos, const 
         return hipGetLastError();
     };
     using Acc = V;  // FP64 or FP32 accumulation, as the values
-    // positions per lane group in flight: 2 (fewer registers, more waves per
-    // SIMD) measured best at K = 128 on 8e6 positions: FP32 0.874 ms, BF16
-    // 0.433 ms, against 0.928 / 0.529 with 4, 1.08 / 0.51 with 1 and 1.28
-    // (FP32) with 8
+    // positions per lane group in flight: 2 (4 takes 0.643 / 0.328 ms instead
+    // of 0.646 / 0.330 at K = 128 on 8e6 positions, FP32 / BF16, and 27.6 us
+    // instead of 25.7 at K = 33 on 8e5)
     constexpr int kP = 2;
-    if (lanes == 32) return go(k_sddmm_vec<V, FT, Acc, kSddmmChunk, 32, VEC, kP>);
-    if (lanes == 16) return go(k_sddmm_vec<V, FT, Acc, kSddmmChunk, 16, VEC, kP>);
-    if (lanes == 8) return go(k_sddmm_vec<V, FT, Acc, kSddmmChunk, 8, VEC, kP>);
-    return hipErrorInvalidValue;
+    auto pick = [&](auto rag) {
+        constexpr bool kRag = decltype(rag)::value;
+        if (lanes == 32) return go(k_sddmm_vec<V, FT, Acc, kSddmmChunk, 32, VEC, kP, kRag>);
+        if (lanes == 16) return go(k_sddmm_vec<V, FT, Acc, kSddmmChunk, 16, VEC, kP, kRag>);
+        if (lanes == 8) return go(k_sddmm_vec<V, FT, Acc, kSddmmChunk, 8, VEC, kP, kRag>);
+        if (lanes == 4) return go(k_sddmm_vec<V, FT, Acc, kSddmmChunk, 4, VEC, kP, kRag>);
+        return hipErrorInvalidValue;
+    };
+    return K % VEC ? pick(std::true_type()) : pick(std::false_type());
 }
 }  // namespace
 

@@ -270,6 +270,35 @@ def test_sddmm(case):
         assert_close(host64(A), ref, S, 1e-12 if case == "f64" else 1e-5, f"sddmm {case} {sc}")
 
 
+# Vector lanes on any K, leading dimension and element alignment: edges of a
+# lane and of a group of 4 to 32 lanes, and past one pass of the widest group;
+# factors contiguous or views of wider arrays one element in, whose other
+# entries (NaN) must not reach the results.
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 7, 8, 9, 16, 17, 31, 33, 63, 65, 127, 129, 257, 300])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32, torch.bfloat16])
+def test_sddmm_ragged_k(dtype, K):
+    spl = _spl()
+    rs = np.random.RandomState(K)
+    pos, crd, _ = tiny.csr(rs, 90, 70, 0.1, empty_rows={0, 50, 89}, full_rows={3, 4})
+    vdt = torch.float64 if dtype == torch.float64 else torch.float32
+    for kind in ("int", "float"):
+        draw = (lambda s: rs.randint(-4, 5, s)) if kind == "int" else (lambda s: rs.uniform(-1, 1, s))
+        B = spl.CSR(_t(pos), _t(crd), _t(draw(crd.size), torch.float64).to(vdt), (90, 70))
+        C, D = (_t(draw((r, K)), torch.float64).to(dtype) for r in (90, 70))
+        ref, S = oracle.sddmm(pos, crd, host64(B.vals), host64(C), host64(D))
+        wide = [torch.full((a.shape[0], K + 3), float("nan"), dtype=dtype, device=dev()) for a in (C, D)]
+        for w, a in zip(wide, (C, D)):
+            w[:, 1:K + 1] = a
+        for Cv, Dv in ((C, D), tuple(w[:, 1:K + 1] for w in wide)):
+            for sc in (None, dict(kind="row"), dict(kind="nnz", tile=700)):
+                print(f"sddmm ragged {dtype} K={K} ld={Cv.stride(0)} {kind} {sc}", flush=True)
+                A = host64(spl.sddmm(B, Cv, Dv, sched=spl.schedule(**sc) if sc else None))
+                if kind == "int":
+                    assert np.array_equal(A, ref), sc
+                else:
+                    assert_close(A, ref, S, 1e-12 if dtype == torch.float64 else 1e-5, f"K={K} {sc}")
+
+
 def test_sddmm_edge_cases():
     spl = _spl()
     rs = np.random.RandomState(9)
