@@ -373,10 +373,12 @@ spl_status spl_spttv(spl_context *ctx, const spl_sparse *B, const spl_dense *c,
  * ends and fibers), NNZ (blocks of `tile` positions snapped to fiber starts:
  * the fused non-zero partition), ROW (blocks of `tile` slices); col_tile 16,
  * 32 or 64 rank columns per lane group.  sched->variant: 0 = each lane reads
- * and writes 4 consecutive rank columns with one vector access when R,
+ * and writes consecutive rank columns with one vector access: when col_tile
+ * and items_per_lane are left to the library (int32 positions), 4 F32 or 8
+ * BF16 columns from R = 4 or 8 on; otherwise 4 when R,
  * C->ld, D->ld and A->ld are multiples of 4, C and D are aligned to 4
  * elements, A to 16 bytes, col_tile is 32 or 64 and items_per_lane is not
- * 16 (otherwise one column per lane) -- with BF16 factors 8 rank columns
+ * 16 (else one column per lane) -- with BF16 factors 8 rank columns
  * (16 bytes) per lane instead when R and every ld are multiples of 8, C and
  * D 16-byte aligned and (col_tile, items_per_lane) is (32, 0), (32, 3),
  * (32, 4), (64, 0), (64, 4) or (64, 8); 1 = one column per lane; 2 (BF16 only, else SPL_ERR_ARG) = 4
@@ -389,8 +391,8 @@ spl_status spl_spttv(spl_context *ctx, const spl_sparse *B, const spl_dense *c,
  * LDS than 8, so more waves per SIMD.  0 (default) takes 5 for 4-column
  * lanes at col_tile 32 (4 with int64 positions or variant 3), 3 for
  * 8-column BF16 lanes at col_tile 32, 4 for the other vector lanes and 8
- * for one column per lane; tile 0 (default) takes 512 merged items with
- * vector lanes.  The workspace query returns the largest size over the
+ * for one column per lane; tile 0 (default) takes 64 to 512 merged
+ * items with vector lanes, the more the more there are.  The workspace query returns the largest size over the
  * lane widths the call may take.  A
  * (Dense, Dense, Compressed) B is accepted: its middle level's pos/crd
  * (I + 1 and I * J int32) are written into the workspace, counted by the

@@ -163,6 +163,7 @@ struct Plan {
     int variant = 0;
     int vec = 1;  // SpMM: dense columns per lane
     bool small = false;  // SpMV, SpTTV: the one-launch leaf
+    bool any_rank = false;  // MTTKRP: vector lanes whatever R and the alignment
 };
 
 int lanes_for_mean(double mean) {
@@ -484,7 +485,8 @@ spl_status expand_middle(spl_context *ctx, const spl_sparse *B, char *&ws, spl_s
     return SPL_OK;
 }
 
-spl_status resolve_mttkrp(spl_context *ctx, int64_t R, const spl_schedule *s, Plan &p) {
+spl_status resolve_mttkrp(spl_context *ctx, const spl_sparse *B, int64_t R, const spl_schedule *s,
+                          Plan &p) {
     spl_schedule d{};
     if (!s) s = &d;
     p.kind = s->kind == SPL_SCHED_DEFAULT ? SPL_MERGE : s->kind;
@@ -492,9 +494,14 @@ spl_status resolve_mttkrp(spl_context *ctx, int64_t R, const spl_schedule *s, Pl
         return fail(ctx, SPL_ERR_ARG, "unknown schedule kind %d", s->kind);
     int ct = s->col_tile;
     if (!ct) {
-        ct = 16;
+        // (BF16 vector lanes of 8 columns: at least a group of four)
+        ct = s->variant == 0 && !s->items_per_lane && B->vtype == SPL_BF16 &&
+                     B->pos_type == SPL_I32 && R >= 8
+                 ? 32
+                 : 16;
         while (ct < 64 && ct < R) ct <<= 1;
     }
+    p.any_rank = s->variant == 0 && !s->items_per_lane && !s->col_tile && B->pos_type == SPL_I32;
     if (ct != 16 && ct != 32 && ct != 64)
         return fail(ctx, SPL_ERR_ARG, "MTTKRP col_tile must be 16, 32 or 64");
     p.col_tile = ct;
@@ -524,10 +531,18 @@ int64_t mttkrp_chunk(const Plan &p) {
 // (5 for 8 lanes of 4 columns, 3 for 4 lanes of 8 BF16 columns -- each the
 // most merged items whose registers still leave 4 waves per SIMD; 4 for the
 // other vector lanes and for variant 3; 8 for one column per lane) and the
-// tile (512 merged items with vector lanes, four 256-thread chunks
-// otherwise).  With int64 positions the 4-column leaf takes 4 items: 5 would
+// tile (64 to 512 merged items with vector lanes, four 256-thread chunks
+// otherwise).  A workgroup walks its tile's chunks one after another, so
+// short tiles spread `total` merged items over more of them, and long ones
+// save carries once there are enough: up to 20,000 workgroups (8 waves on
+// every SIMD four times over) before the tile grows.  FP32, R = 32, in us at
+// tiles of 64 / 256 / 512: 16,134 items 22.7 / 42 / 60, 1.2e6 76 / 90 / 115,
+// 5.1e6 254 / 216 / 231, 19e6 1,003 / 842 / 827.  (FP32 with int64 positions,
+// for tensors past 2^31 of them, keeps 512.)  With int64 positions the 4-column leaf takes 4 items: 5 would
 // need one register more than 4 waves per SIMD allow.
-void finish_mttkrp(Plan &p, bool pos64) {
+void finish_mttkrp(Plan &p, const spl_sparse *B) {
+    const bool pos64 = B->pos_type == SPL_I64;
+    const int64_t total = B->dims[0] + B->nfibers;
     const int lanes = p.col_tile / p.vec;
     if (p.items == 0) {
         if (p.vec == 1)
@@ -539,10 +554,14 @@ void finish_mttkrp(Plan &p, bool pos64) {
         else
             p.items = lanes == 8 && !pos64 ? 5 : 4;
     }
-    if (p.tile == 0)
+    if (p.tile == 0) {
         p.tile = p.kind == SPL_ROW ? 64 : p.kind == SPL_NNZ ? 2048
-                 : p.vec > 1     ? 512
+                 : p.vec > 1     ? 64
                                  : 4 * mttkrp_chunk(p);
+        if (p.kind == SPL_MERGE && p.vec > 1)
+            while (p.tile < 512 && (p.tile * 20000 < total || (pos64 && B->vtype == SPL_F32)))
+                p.tile *= 2;
+    }
 }
 
 // Vector lanes for the MTTKRP leaf: v rank columns per lane when R, the
@@ -550,10 +569,18 @@ void finish_mttkrp(Plan &p, bool pos64) {
 // items_per_lane is not 16; otherwise one column per lane.  v = 4 (16-byte
 // FP32 rows, 8-byte BF16 rows; BF16 variant 2), or for BF16 under variant 0
 // v = 8 (16-byte rows) with (col_tile, items) (32, 3), (32, 4), (64, 4),
-// (64, 8) or items chosen by default.
+// (64, 8) or items chosen by default.  When the caller leaves the column tile
+// and the items to the library, R need only be v: the leaf shifts a row's
+// last vector (8e6 nonzeros, 5e6 fibers: R = 33 takes 401 us in FP32 and 383 in
+// BF16 where one column per lane takes 1,007 and 1,583; R = 16 takes 164 and
+// 196, 386 and 419).
 int mttkrp_vec(const Plan &p, const spl_dense *C, const spl_dense *D, const spl_dense *A) {
-    if (p.variant == 1 || p.items == 16 || (p.col_tile != 32 && p.col_tile != 64)) return 1;
     const int64_t R = C->dims[1];
+    if (p.any_rank) {
+        const int v = C->dtype == SPL_BF16 ? 8 : 4;
+        return R >= v ? v : 1;
+    }
+    if (p.variant == 1 || p.items == 16 || (p.col_tile != 32 && p.col_tile != 64)) return 1;
     auto fits = [&](int v) {
         const size_t fb = v * dtype_bytes(C->dtype);
         return R % v == 0 && C->ld % v == 0 && D->ld % v == 0 && A->ld % v == 0 &&
@@ -995,14 +1022,14 @@ spl_status spl_workspace_query(spl_context *ctx, spl_op op, const spl_sparse *B,
     }
     case SPL_OP_MTTKRP: {
         SPL_CHECK(check_sparse(ctx, B, 3, true));
-        SPL_CHECK(resolve_mttkrp(ctx, ncols, sched, p));
+        SPL_CHECK(resolve_mttkrp(ctx, B, ncols, sched, p));
         // the lane width depends on the factors' pointers: the largest
         // workspace over every width the call may take
         size_t ws = 0;
         for (int v : {1, 4, 8}) {
             Plan q = p;
             q.vec = v;
-            finish_mttkrp(q, B->pos_type == SPL_I64);
+            finish_mttkrp(q, B);
             ws = std::max(ws, mttkrp_ws(B, ncols, q));
         }
         *bytes = dense_middle_ws(B) + ws;
@@ -1509,7 +1536,7 @@ spl_status spl_mttkrp(spl_context *ctx, const spl_sparse *B, const spl_dense *C,
         return fail(ctx, SPL_ERR_DTYPE,
                     "MTTKRP dtypes (vals, C, D, A) must be (F32,F32,F32,F32) or (BF16,BF16,BF16,F32)");
     Plan p;
-    SPL_CHECK(resolve_mttkrp(ctx, R, sched, p));
+    SPL_CHECK(resolve_mttkrp(ctx, B, R, sched, p));
     if (p.variant == 2 && B->vtype != SPL_BF16)
         return fail(ctx, SPL_ERR_ARG, "MTTKRP variant 2 (8-byte lanes) is for BF16 factors");
     SPL_CHECK(set_device(ctx));
@@ -1518,7 +1545,7 @@ spl_status spl_mttkrp(spl_context *ctx, const spl_sparse *B, const spl_dense *C,
     if (I == 0 || R == 0) return SPL_OK;
     // the workspace query took the largest size over the lane widths
     p.vec = mttkrp_vec(p, C, D, A);
-    finish_mttkrp(p, pos64);
+    finish_mttkrp(p, B);
     if (p.variant == 3 && (B->vtype != SPL_F32 || p.items != 4))
         return fail(ctx, SPL_ERR_ARG,
                     "MTTKRP variant 3 (staged positions) is for F32 with items_per_lane 4");
@@ -1548,7 +1575,8 @@ spl_status spl_mttkrp(spl_context *ctx, const spl_sparse *B, const spl_dense *C,
     const Pieces q = mttkrp_pieces(B, p);
     Carved cv = carve(wp, q.count);
     const size_t fb = dtype_bytes(C->dtype);
-    const bool buf = spl::mttkrp_buf(B->nnz, dtype_bytes(B->vtype), B->dims[1], C->ld, B->dims[2],
+    const bool buf = dword_rows(C) && dword_rows(D) &&
+                     spl::mttkrp_buf(B->nnz, dtype_bytes(B->vtype), B->dims[1], C->ld, B->dims[2],
                                      D->ld, fb);
     if (pos64) {
         // slice ends are fiber indices (below 2^31): int32 tile bounds

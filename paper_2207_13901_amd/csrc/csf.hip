@@ -21,7 +21,8 @@
 // the cross-group pass and the tile carry exactly as the SpMM rows do).
 //
 // k_mttkrp_vec: the same leaf with 4 (FP32) or 8 (BF16) rank columns per
-// lane, one vector access per row, in 128-thread workgroups: the C rows of
+// lane, one vector access per row whatever the rank (lane_col), in 128-thread
+// workgroups: the C rows of
 // the group's fibers go to an LDS slab, the D rows of its positions are
 // gathered a batch at a time into registers (details below).
 #include "carry.hpp"
@@ -290,9 +291,10 @@ __global__ __launch_bounds__(NT) void k_mttkrp_vec(
 
     const int tid = threadIdx.x;
     const int g = tid / W, lane = tid % W;
-    // this lane's rank columns: col0 .. col0 + VEC - 1 (R is a multiple of VEC)
-    const int64_t col0 = (static_cast<int64_t>(blockIdx.y) * W + lane) * VEC;
-    const bool colok = col0 < R;
+    // this lane's rank columns: col0 .. col0 + VEC - 1
+    const int64_t vlane = static_cast<int64_t>(blockIdx.y) * W + lane;
+    const bool colok = vlane * VEC < R;
+    const int64_t col0 = lane_col<VEC>(vlane, R);
     int64_t piece = static_cast<int64_t>(blockIdx.x) * stride;
     const int64_t piece_end = piece + stride < npieces ? piece + stride : npieces;
     int64_t ci = tslice[piece], cf = tfib[piece];
@@ -579,7 +581,9 @@ __global__ __launch_bounds__(NT) void k_mttkrp_vec(
         // groups, then starts from the partials of the parts before it.
         {
             const int col = tid % NC, part = tid / NC;
-            const int64_t gcol = static_cast<int64_t>(blockIdx.y) * NC + col;
+            const int64_t clane = static_cast<int64_t>(blockIdx.y) * W + col / VEC;
+            const bool gok = clane * VEC < R;
+            const int64_t gcol = lane_col<VEC>(clane, R) + col % VEC;
             int pa = 1;
             Acc pb = 0;
             for (int k = 0; k < kGroupsPerPart; ++k) {
@@ -596,7 +600,7 @@ __global__ __launch_bounds__(NT) void k_mttkrp_vec(
             for (int k = 0; k < kGroupsPerPart; ++k) {
                 const int gg = part * kGroupsPerPart + k;
                 if (s_done[gg] > 0) {
-                    if (gcol < R) A[(ci + s_a0[gg]) * lda + gcol] = o + s_head[gg][col];
+                    if (gok) A[(ci + s_a0[gg]) * lda + gcol] = o + s_head[gg][col];
                     o = s_tail[gg][col];
                 } else {
                     o += s_tail[gg][col];
@@ -609,8 +613,9 @@ __global__ __launch_bounds__(NT) void k_mttkrp_vec(
         __syncthreads();
     }
     if (tid < NC) {
-        const int64_t gcol = static_cast<int64_t>(blockIdx.y) * NC + tid;
-        if (gcol < R) carry[static_cast<int64_t>(blockIdx.x) * R + gcol] = s_open[tid];
+        const int64_t clane = static_cast<int64_t>(blockIdx.y) * W + tid / VEC;
+        const int64_t gcol = lane_col<VEC>(clane, R) + tid % VEC;
+        if (clane * VEC < R) carry[static_cast<int64_t>(blockIdx.x) * R + gcol] = s_open[tid];
     }
 }
 
@@ -693,6 +698,11 @@ hipError_t mttkrp_types_b(bool stage, int col_tile, int items, int vec, int64_t 
         }
     }
     if (vec == kMttkrpVec) {
+        if constexpr (sizeof(FT) == 4 && sizeof(PosT) == 4) {
+            if (lanes == 4)  // up to 16 rank columns
+                return items == 4 ? go(k_mttkrp_vec<4, 4, kMttkrpVec, V, FT, float, PosT, false, kMttkrpThreads, BUF>)
+                                  : hipErrorInvalidValue;
+        }
         if (items == 5)  // col_tile 32 only
             return lanes == 8 ? go(k_mttkrp_vec<8, 5, kMttkrpVec, V, FT, float, PosT, sizeof(FT) == 2, kMttkrpThreads, BUF>)
                               : hipErrorInvalidValue;

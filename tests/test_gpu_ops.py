@@ -136,6 +136,37 @@ def test_mttkrp(dtype, R):
                                                            items_per_lane=3))
 
 
+# Vector lanes on any rank, leading dimension and element alignment (edges of a
+# lane, of a group and of a block of groups), factors and output contiguous or
+# views of wider arrays one element in: the factors' other entries (NaN) reach
+# nothing and the output's stay as they were.  Tiles of 64 to 512 merged items.
+@pytest.mark.parametrize("R", [1, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 33, 63, 65, 70, 130])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_mttkrp_ragged_rank(dtype, R):
+    spl = _spl()
+    rs = np.random.RandomState(R)
+    p1, c1, p2, c2, _ = tiny.csf(rs, 40, 30, 50, 0.08, empty_slices={0, 20, 39})
+    for kind in ("int", "float"):
+        draw = (lambda s: rs.randint(-3, 4, s)) if kind == "int" else (lambda s: rs.uniform(-1, 1, s))
+        B = spl.CSF(_t(p1), _t(c1), _t(p2), _t(c2), _t(draw(c2.size), torch.float64).to(dtype),
+                    (40, 30, 50))
+        C, D = (_t(draw((r, R)), torch.float64).to(dtype) for r in (30, 50))
+        ref, S = oracle.mttkrp(p1, c1, p2, c2, host64(B.vals), host64(C), host64(D))
+        wide = [torch.full((a.shape[0], R + 3), float("nan"), dtype=dtype, device=dev()) for a in (C, D)]
+        for w, a in zip(wide, (C, D)):
+            w[:, 1:R + 1] = a
+        for Cv, Dv in ((C, D), tuple(w[:, 1:R + 1] for w in wide)):
+            for tile in (0, 64, 512):
+                out = torch.full((40, R + 5), 7.0, dtype=torch.float32, device=dev())
+                print(f"mttkrp ragged {dtype} R={R} ld={Cv.stride(0)} {kind} tile={tile}", flush=True)
+                A = host64(spl.mttkrp(B, Cv, Dv, A=out[:, 2:R + 2], sched=spl.schedule(tile=tile)))
+                assert (out[:, :2] == 7).all() and (out[:, R + 2:] == 7).all()
+                if kind == "int":
+                    assert np.array_equal(A, ref), tile
+                else:
+                    assert_close(A, ref, S, 1e-5, f"{dtype} R={R} tile={tile}")
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_mttkrp_caller_workspace_from_query(dtype):
     # the query cannot see the lane width (it depends on the factors'
