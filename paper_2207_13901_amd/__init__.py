@@ -69,6 +69,13 @@ class CSR:
         s.pos_type = N.I64 if self.pos.dtype == torch.int64 else N.I32
         return s
 
+    def packed(self) -> bytes:
+        """struct() as bytes (N.SPARSE)."""
+        return N.SPARSE.pack(2, _dtype_code(self.vals), self.shape[0], self.shape[1], 0,
+                             N.DENSE, N.COMPRESSED, 0, 0, self.pos.data_ptr(), 0, 0,
+                             self.crd.data_ptr(), 0, self.vals.data_ptr(), self.crd.numel(), 0,
+                             N.I64 if self.pos.dtype == torch.int64 else N.I32)
+
     def with_vals(self, vals: torch.Tensor) -> "CSR":
         return CSR(self.pos, self.crd, vals, self.shape)
 
@@ -96,11 +103,22 @@ class CSF:
         s.vals = _ptr(self.vals)
         s.nnz = self.crd2.numel()
         s.nfibers = self.crd1.numel()
-        if self.pos2.dtype == torch.int64:
-            if self.pos1.dtype != torch.int64:
-                raise ValueError("int64 positions: pos1 and pos2 both int64")
-            s.pos_type = N.I64
+        s.pos_type = self._pos_type()
         return s
+
+    def _pos_type(self) -> int:
+        if self.pos2.dtype != torch.int64:
+            return N.I32
+        if self.pos1.dtype != torch.int64:
+            raise ValueError("int64 positions: pos1 and pos2 both int64")
+        return N.I64
+
+    def packed(self) -> bytes:
+        """struct() as bytes (N.SPARSE)."""
+        return N.SPARSE.pack(3, _dtype_code(self.vals), *self.shape[:3], N.DENSE, N.COMPRESSED,
+                             N.COMPRESSED, 0, self.pos1.data_ptr(), self.pos2.data_ptr(), 0,
+                             self.crd1.data_ptr(), self.crd2.data_ptr(), self.vals.data_ptr(),
+                             self.crd2.numel(), self.crd1.numel(), self._pos_type())
 
     def with_vals(self, vals: torch.Tensor) -> "CSF":
         return CSF(self.pos1, self.crd1, self.pos2, self.crd2, vals, self.shape)
@@ -134,6 +152,10 @@ class DDC:
         s.pos_type = N.I64 if self.pos2.dtype == torch.int64 else N.I32
         return s
 
+    def packed(self) -> bytes:
+        """struct() as bytes (N.SPARSE)."""
+        return bytes(self.struct())
+
     def with_vals(self, vals: torch.Tensor) -> "DDC":
         return DDC(self.pos2, self.crd2, vals, self.shape)
 
@@ -159,6 +181,22 @@ def _dense(t: torch.Tensor) -> N.SplDense:
     else:
         raise ValueError("dense operand must have 1 or 2 dimensions")
     return d
+
+
+def _dense_arg(t: torch.Tensor) -> bytes:
+    """_dense() as bytes (N.DENSE_ARG)."""
+    shape = t.shape
+    if len(shape) == 1:
+        if shape[0] and t.stride(0) != 1:
+            raise ValueError("dense vector must be contiguous")
+        return N.DENSE_ARG.pack(t.data_ptr(), _dtype_code(t), 1, shape[0], 1, 1)
+    if len(shape) == 2:
+        rows, cols = shape
+        ld, step = t.stride()
+        if rows and cols and step != 1:
+            raise ValueError("dense matrix must be row-major (unit column stride)")
+        return N.DENSE_ARG.pack(t.data_ptr(), _dtype_code(t), 2, rows, cols, ld if rows > 1 else cols)
+    raise ValueError("dense operand must have 1 or 2 dimensions")
 
 
 def schedule(kind: str = "default", lanes_per_row: int = 0, tile: int = 0,
@@ -206,26 +244,31 @@ class Context:
 
 
 def _ctx_stream(t: torch.Tensor, ctx: Optional[Context]):
-    ctx = ctx or Context.get(t.device.index)
-    stream = torch.cuda.current_stream(t.device).cuda_stream
-    return ctx, stream
+    device = t.device
+    ctx = ctx or Context.get(device.index)
+    if device.type != "cuda":  # refused
+        return ctx, torch.cuda.current_stream(device).cuda_stream
+    return ctx, torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def workspace_query(op: int, B, ncols: int = 1, sched=None,
                     ctx: Optional[Context] = None) -> int:
-    ctx = ctx or Context.get()
+    return _query(op, B.packed(), ncols, sched, ctx or Context.get())
+
+
+def _query(op, s: bytes, ncols, sched, ctx) -> int:
     nbytes = ctypes.c_size_t()
-    s = B.struct()
-    ctx.check(ctx.lib.spl_workspace_query(ctx.h, op, ctypes.byref(s), ncols,
-                                          ctypes.byref(sched) if sched else None,
-                                          ctypes.byref(nbytes)), "spl_workspace_query")
+    ctx.check(N.packed("spl_workspace_query")(ctx.h, op, s, ncols, _sched_ptr(sched),
+                                              ctypes.byref(nbytes)), "spl_workspace_query")
     return nbytes.value
 
 
-def _workspace(op, B, ncols, sched, ctx, device, given=None):
+def _workspace(op, s: bytes, ncols, sched, ctx, device, given=None):
+    """The workspace of one call on the packed operand `s`: the one given, or
+    a new tensor of the queried size (None for 0)."""
     if given is not None:
         return given, given.numel()
-    nbytes = workspace_query(op, B, ncols, sched, ctx)
+    nbytes = _query(op, s, ncols, sched, ctx)
     if nbytes == 0:
         return None, 0
     return torch.empty(nbytes, dtype=torch.uint8, device=device), nbytes
@@ -234,7 +277,7 @@ def _workspace(op, B, ncols, sched, ctx, device, given=None):
 def workspace(op: int, B, ncols: int = 1, sched=None, ctx: Optional[Context] = None):
     """A uint8 device tensor large enough for one call of `op` (or None)."""
     dev = B.vals.device
-    ws, _ = _workspace(op, B, ncols, sched, ctx or Context.get(dev.index), dev)
+    ws, _ = _workspace(op, B.packed(), ncols, sched, ctx or Context.get(dev.index), dev)
     return ws
 
 
@@ -244,12 +287,10 @@ def spmv(B: CSR, c: torch.Tensor, a: Optional[torch.Tensor] = None, sched=None,
     ctx, stream = _ctx_stream(B.vals, ctx)
     if a is None:
         a = torch.empty(B.shape[0], dtype=B.vals.dtype, device=B.vals.device)
-    s = B.struct()
-    ws, nb = _workspace(N.OP_SPMV, B, 1, sched, ctx, B.vals.device, ws)
-    ctx.check(ctx.lib.spl_spmv(ctx.h, ctypes.byref(s), ctypes.byref(_dense(c)),
-                               ctypes.byref(_dense(a)),
-                               ctypes.byref(sched) if sched else None,
-                               _ptr(ws), nb, stream), "spl_spmv")
+    s = B.packed()
+    ws, nb = _workspace(N.OP_SPMV, s, 1, sched, ctx, B.vals.device, ws)
+    ctx.check(N.packed("spl_spmv")(ctx.h, s, _dense_arg(c), _dense_arg(a), _sched_ptr(sched),
+                                   _ptr(ws), nb, stream), "spl_spmv")
     return a
 
 
@@ -259,11 +300,8 @@ def spmv_noalloc(B: CSR, c: torch.Tensor, a: torch.Tensor, sched=None,
     nothing (tile bounds and carries in its static device scratch), so `a`
     must be given."""
     ctx, stream = _ctx_stream(B.vals, ctx)
-    s = B.struct()
-    ctx.check(ctx.lib.spl_spmv_noalloc(ctx.h, ctypes.byref(s), ctypes.byref(_dense(c)),
-                                       ctypes.byref(_dense(a)),
-                                       ctypes.byref(sched) if sched else None, stream),
-              "spl_spmv_noalloc")
+    ctx.check(N.packed("spl_spmv_noalloc")(ctx.h, B.packed(), _dense_arg(c), _dense_arg(a),
+                                           _sched_ptr(sched), stream), "spl_spmv_noalloc")
     return a
 
 
@@ -289,10 +327,9 @@ def spmv_window(B: CSR, begin: torch.Tensor, end: torch.Tensor, c: torch.Tensor,
     ctx, stream = _ctx_stream(B.vals, ctx)
     if a is None:
         a = torch.empty(B.shape[0], dtype=B.vals.dtype, device=B.vals.device)
-    s = B.struct()
-    ctx.check(ctx.lib.spl_spmv_window(ctx.h, ctypes.byref(s), _ptr(begin), _ptr(end),
-                                      ctypes.byref(_dense(c)), ctypes.byref(_dense(a)),
-                                      _sched_ptr(sched), stream), "spl_spmv_window")
+    ctx.check(N.packed("spl_spmv_window")(ctx.h, B.packed(), _ptr(begin), _ptr(end),
+                                          _dense_arg(c), _dense_arg(a), _sched_ptr(sched),
+                                          stream), "spl_spmv_window")
     return a
 
 
@@ -303,12 +340,10 @@ def spmm(B: CSR, C: torch.Tensor, A: Optional[torch.Tensor] = None, sched=None,
     if A is None:
         odt = torch.float32 if C.dtype == torch.bfloat16 else C.dtype
         A = torch.empty(B.shape[0], C.shape[1], dtype=odt, device=C.device)
-    s = B.struct()
-    ws, nb = _workspace(N.OP_SPMM, B, C.shape[1], sched, ctx, B.vals.device, ws)
-    ctx.check(ctx.lib.spl_spmm(ctx.h, ctypes.byref(s), ctypes.byref(_dense(C)),
-                               ctypes.byref(_dense(A)),
-                               ctypes.byref(sched) if sched else None,
-                               _ptr(ws), nb, stream), "spl_spmm")
+    s = B.packed()
+    ws, nb = _workspace(N.OP_SPMM, s, C.shape[1], sched, ctx, B.vals.device, ws)
+    ctx.check(N.packed("spl_spmm")(ctx.h, s, _dense_arg(C), _dense_arg(A), _sched_ptr(sched),
+                                   _ptr(ws), nb, stream), "spl_spmm")
     return A
 
 
@@ -407,11 +442,10 @@ def spttv(B: CSF, c: torch.Tensor, A: Optional[torch.Tensor] = None, sched=None,
     ctx, stream = _ctx_stream(B.vals, ctx)
     if A is None:
         A = torch.empty(B.nfibers, dtype=B.vals.dtype, device=B.vals.device)
-    s = B.struct()
-    ws, nb = _workspace(N.OP_SPTTV, B, 1, sched, ctx, B.vals.device, ws)
-    ctx.check(ctx.lib.spl_spttv(ctx.h, ctypes.byref(s), ctypes.byref(_dense(c)),
-                                ctypes.byref(_dense(A)), _sched_ptr(sched), _ptr(ws), nb,
-                                stream), "spl_spttv")
+    s = B.packed()
+    ws, nb = _workspace(N.OP_SPTTV, s, 1, sched, ctx, B.vals.device, ws)
+    ctx.check(N.packed("spl_spttv")(ctx.h, s, _dense_arg(c), _dense_arg(A), _sched_ptr(sched),
+                                    _ptr(ws), nb, stream), "spl_spttv")
     return A
 
 
@@ -422,11 +456,10 @@ def mttkrp(B: CSF, C: torch.Tensor, D: torch.Tensor, A: Optional[torch.Tensor] =
     ctx, stream = _ctx_stream(B.vals, ctx)
     if A is None:
         A = torch.empty(B.shape[0], C.shape[1], dtype=torch.float32, device=C.device)
-    s = B.struct()
-    ws, nb = _workspace(N.OP_MTTKRP, B, C.shape[1], sched, ctx, B.vals.device, ws)
-    ctx.check(ctx.lib.spl_mttkrp(ctx.h, ctypes.byref(s), ctypes.byref(_dense(C)),
-                                 ctypes.byref(_dense(D)), ctypes.byref(_dense(A)),
-                                 _sched_ptr(sched), _ptr(ws), nb, stream), "spl_mttkrp")
+    s = B.packed()
+    ws, nb = _workspace(N.OP_MTTKRP, s, C.shape[1], sched, ctx, B.vals.device, ws)
+    ctx.check(N.packed("spl_mttkrp")(ctx.h, s, _dense_arg(C), _dense_arg(D), _dense_arg(A),
+                                     _sched_ptr(sched), _ptr(ws), nb, stream), "spl_mttkrp")
     return A
 
 
@@ -436,15 +469,14 @@ def inner(B, C, out: Optional[torch.Tensor] = None, ctx: Optional[Context] = Non
     ctx, stream = _ctx_stream(B.vals, ctx)
     if out is None:
         out = torch.empty(1, dtype=torch.float64, device=B.vals.device)
-    sb, sc = B.struct(), C.struct()
+    sb, sc = B.packed(), C.packed()
     if ws is None and isinstance(C, DDC):
         # a Dense middle level of C is written out in the workspace as well
-        nbytes = (workspace_query(N.OP_INNER, B, 1, None, ctx) +
-                  workspace_query(N.OP_INNER, C, 1, None, ctx))
+        nbytes = _query(N.OP_INNER, sb, 1, None, ctx) + _query(N.OP_INNER, sc, 1, None, ctx)
         ws = torch.empty(nbytes, dtype=torch.uint8, device=B.vals.device)
-    ws, nb = _workspace(N.OP_INNER, B, 1, None, ctx, B.vals.device, ws)
-    ctx.check(ctx.lib.spl_inner(ctx.h, ctypes.byref(sb), ctypes.byref(sc), out.data_ptr(),
-                                None, _ptr(ws), nb, stream), "spl_inner")
+    ws, nb = _workspace(N.OP_INNER, sb, 1, None, ctx, B.vals.device, ws)
+    ctx.check(N.packed("spl_inner")(ctx.h, sb, sc, out.data_ptr(), None, _ptr(ws), nb, stream),
+              "spl_inner")
     return out
 
 
@@ -455,11 +487,10 @@ def sddmm(B: CSR, C: torch.Tensor, D: torch.Tensor, A: Optional[torch.Tensor] = 
     ctx, stream = _ctx_stream(B.vals, ctx)
     if A is None:
         A = torch.empty(B.crd.numel(), dtype=B.vals.dtype, device=B.vals.device)
-    s = B.struct()
-    ws, nb = _workspace(N.OP_SDDMM, B, C.shape[1], sched, ctx, B.vals.device, ws)
-    ctx.check(ctx.lib.spl_sddmm(ctx.h, ctypes.byref(s), ctypes.byref(_dense(C)),
-                                ctypes.byref(_dense(D)), ctypes.byref(_dense(A)),
-                                _sched_ptr(sched), _ptr(ws), nb, stream), "spl_sddmm")
+    s = B.packed()
+    ws, nb = _workspace(N.OP_SDDMM, s, C.shape[1], sched, ctx, B.vals.device, ws)
+    ctx.check(N.packed("spl_sddmm")(ctx.h, s, _dense_arg(C), _dense_arg(D), _dense_arg(A),
+                                    _sched_ptr(sched), _ptr(ws), nb, stream), "spl_sddmm")
     return A
 
 
@@ -469,19 +500,17 @@ def spadd3(B: CSR, C: CSR, D: CSR, sched=None, ctx: Optional[Context] = None) ->
     ctx, stream = _ctx_stream(B.vals, ctx)
     dev = B.vals.device
     n = B.shape[0]
-    sb, sc, sd = B.struct(), C.struct(), D.struct()
+    sb, sc, sd = B.packed(), C.packed(), D.packed()
     apos = torch.empty(n + 1, dtype=torch.int32, device=dev)
-    ws, nb = _workspace(N.OP_SPADD3, B, 1, None, ctx, dev)
+    ws, nb = _workspace(N.OP_SPADD3, sb, 1, None, ctx, dev)
     nnz = ctypes.c_int64()
-    ctx.check(ctx.lib.spl_spadd3_symbolic(ctx.h, ctypes.byref(sb), ctypes.byref(sc),
-                                          ctypes.byref(sd), apos.data_ptr(), ctypes.byref(nnz),
-                                          _sched_ptr(sched), _ptr(ws), nb, stream),
-              "spl_spadd3_symbolic")
+    ctx.check(N.packed("spl_spadd3_symbolic")(ctx.h, sb, sc, sd, apos.data_ptr(),
+                                              ctypes.byref(nnz), _sched_ptr(sched), _ptr(ws), nb,
+                                              stream), "spl_spadd3_symbolic")
     acrd = torch.empty(nnz.value, dtype=torch.int32, device=dev)
     avals = torch.empty(nnz.value, dtype=B.vals.dtype, device=dev)
-    ctx.check(ctx.lib.spl_spadd3_numeric(ctx.h, ctypes.byref(sb), ctypes.byref(sc),
-                                         ctypes.byref(sd), apos.data_ptr(), _ptr(acrd),
-                                         _ptr(avals), _sched_ptr(sched), stream),
+    ctx.check(N.packed("spl_spadd3_numeric")(ctx.h, sb, sc, sd, apos.data_ptr(), _ptr(acrd),
+                                             _ptr(avals), _sched_ptr(sched), stream),
               "spl_spadd3_numeric")
     return CSR(apos, acrd, avals, B.shape)
 
@@ -494,16 +523,16 @@ def transpose(B: CSR, ctx: Optional[Context] = None) -> CSR:
     dev = B.vals.device
     n, m = B.shape
     nnz = B.crd.numel()
-    s = B.struct()
+    s = B.packed()
     nb = ctypes.c_size_t()
-    ctx.check(ctx.lib.spl_transpose_workspace_query(ctx.h, ctypes.byref(s), ctypes.byref(nb)),
+    ctx.check(N.packed("spl_transpose_workspace_query")(ctx.h, s, ctypes.byref(nb)),
               "spl_transpose_workspace_query")
     ws = torch.empty(nb.value, dtype=torch.uint8, device=dev)
     tpos = torch.empty(m + 1, dtype=torch.int32, device=dev)
     tcrd = torch.empty(nnz, dtype=torch.int32, device=dev)
     tvals = torch.empty(nnz, dtype=B.vals.dtype, device=dev)
-    ctx.check(ctx.lib.spl_transpose(ctx.h, ctypes.byref(s), tpos.data_ptr(), _ptr(tcrd),
-                                    _ptr(tvals), ws.data_ptr(), nb.value, stream), "spl_transpose")
+    ctx.check(N.packed("spl_transpose")(ctx.h, s, tpos.data_ptr(), _ptr(tcrd), _ptr(tvals),
+                                        ws.data_ptr(), nb.value, stream), "spl_transpose")
     return CSR(tpos, tcrd, tvals, (m, n))
 
 

@@ -799,11 +799,12 @@ spl_status select_schedule(spl_context *ctx, spl_op op, const spl_sparse *B, con
 
 // Bindings of one index-notation call, its plan for this call's operands,
 // and the compiled leaves for those formats (from the context's cache, or
-// generated and compiled now when `compile` is set).
+// generated and compiled now; `compiled` NULL: only planned).  source: prog's
+// source is wanted.
 spl_status tin_prepare(spl_context *ctx, const char *stmt, int nops, const spl_tin_operand *ops,
                        const spl_tin_operand *out, std::vector<spl::tin::Binding> &b,
                        spl::tin::Binding &ob, spl::tin::Program &prog,
-                       spl::tin::Program **compiled) {
+                       spl::tin::Program **compiled, bool source = false) {
     if (!stmt || !out || nops < 0 || (nops > 0 && !ops))
         return fail(ctx, SPL_ERR_ARG, "NULL statement, operand list or output");
     b.resize(static_cast<size_t>(nops));
@@ -818,14 +819,15 @@ spl_status tin_prepare(spl_context *ctx, const char *stmt, int nops, const spl_t
     ob.sparse = out->sparse;
     ob.dense = out->dense;
     std::string err;
-    spl_status st = spl::tin::plan(stmt, b, ob, prog, err);
+    spl_status st = spl::tin::plan(stmt, b, ob, source, prog, err);
     if (st != SPL_OK) return fail(ctx, st, "%s", err.c_str());
     if (!compiled) return SPL_OK;
     auto it = ctx->tin_cache.find(prog.key);
     if (it == ctx->tin_cache.end()) {
         SPL_CHECK(set_device(ctx));
-        std::unique_ptr<spl::tin::Program> c(new spl::tin::Program(prog));
-        st = spl::tin::compile(*c, err);
+        std::unique_ptr<spl::tin::Program> c(new spl::tin::Program());
+        st = spl::tin::plan(stmt, b, ob, true, *c, err);
+        if (st == SPL_OK) st = spl::tin::compile(*c, err);
         if (st != SPL_OK) return fail(ctx, st, "%s", err.c_str());
         it = ctx->tin_cache.emplace(prog.key, std::move(c)).first;
     }
@@ -1878,7 +1880,7 @@ spl_status spl_tin_source(spl_context *ctx, const char *tin, int nops, const spl
     std::vector<spl::tin::Binding> b;
     spl::tin::Binding ob;
     spl::tin::Program prog;
-    SPL_CHECK(tin_prepare(ctx, tin, nops, ops, out, b, ob, prog, nullptr));
+    SPL_CHECK(tin_prepare(ctx, tin, nops, ops, out, b, ob, prog, nullptr, true));
     if (len) *len = prog.source.size();
     if (buf && cap) {
         const size_t n = std::min(cap - 1, prog.source.size());

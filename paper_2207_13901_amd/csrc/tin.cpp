@@ -658,7 +658,7 @@ Program::~Program() {
 }
 
 spl_status plan(const char *stmt, const std::vector<Binding> &ops, const Binding &out,
-                Program &prog, std::string &err) {
+                bool source, Program &prog, std::string &err) {
     if (!stmt) {
         err = "statement is NULL";
         return SPL_ERR_ARG;
@@ -908,27 +908,29 @@ spl_status plan(const char *stmt, const std::vector<Binding> &ops, const Binding
         return SPL_ERR_UNSUPPORTED;
     }
 
-    std::ostringstream src;
-    src << "// generated from: " << stmt << "\n";
-    src << "typedef long long i64;\n";
-    src << "struct TinArgs { unsigned long long s[" << prog.slots.size() << "]; };\n";
-    if (g.stages())  // a value at a byte offset of a buffer; 0 past its range
-        src << "__device__ __forceinline__ float load_float(__amdgpu_buffer_rsrc_t r, int off) {\n"
-               "    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));\n}\n"
-               "typedef unsigned u32x2 __attribute__((ext_vector_type(2)));\n"
-               "__device__ __forceinline__ double load_double(__amdgpu_buffer_rsrc_t r, int off) {\n"
-               "    const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);\n"
-               "    return __hiloint2double((int)w[1], (int)w[0]);\n}\n";
-    if (kind == kOutCsr) {
-        g.mode = Gen::kCount;
-        src << g.kernel("tin_count");
-        g.mode = Gen::kFill;
-        src << g.kernel("tin_fill");
-    } else {
-        g.mode = Gen::kEval;
-        src << g.kernel("tin_eval");
+    if (source) {
+        std::ostringstream src;
+        src << "// generated from: " << stmt << "\n";
+        src << "typedef long long i64;\n";
+        src << "struct TinArgs { unsigned long long s[" << prog.slots.size() << "]; };\n";
+        if (g.stages())  // a value at a byte offset of a buffer; 0 past its range
+            src << "__device__ __forceinline__ float load_float(__amdgpu_buffer_rsrc_t r, int off) {\n"
+                   "    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));\n}\n"
+                   "typedef unsigned u32x2 __attribute__((ext_vector_type(2)));\n"
+                   "__device__ __forceinline__ double load_double(__amdgpu_buffer_rsrc_t r, int off) {\n"
+                   "    const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);\n"
+                   "    return __hiloint2double((int)w[1], (int)w[0]);\n}\n";
+        if (kind == kOutCsr) {
+            g.mode = Gen::kCount;
+            src << g.kernel("tin_count");
+            g.mode = Gen::kFill;
+            src << g.kernel("tin_fill");
+        } else {
+            g.mode = Gen::kEval;
+            src << g.kernel("tin_eval");
+        }
+        prog.source = src.str();
     }
-    prog.source = src.str();
     prog.out_kind = kind;
     prog.vtype = vt;
     prog.rows = ext[i0];

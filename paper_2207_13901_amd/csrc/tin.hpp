@@ -65,9 +65,10 @@ struct Program {
 // Parse `stmt`, check it against the bindings and plan the loop nest.
 // `out` is the left side's binding (its sparse/dense pointers may hold
 // placeholders: only formats, dtypes and dimensions are read here).
-// Returns SPL_OK or a status with the reason in `err`.
+// source: generate prog.source too (a call whose leaves are compiled already
+// needs the plan alone).  Returns SPL_OK or a status with the reason in `err`.
 spl_status plan(const char *stmt, const std::vector<Binding> &ops, const Binding &out,
-                Program &prog, std::string &err);
+                bool source, Program &prog, std::string &err);
 
 // Compile prog.source with hiprtc for gfx950 and load it on the current
 // device.

@@ -59,3 +59,26 @@ def test_status_strings_and_null_args(lib):
     assert lib.spl_last_error(None) == b""
     out = ctypes.c_int32()
     assert lib.spl_op_parse(None, ctypes.byref(out)) == 1
+
+
+def test_packed_arguments_match_the_structs():
+    import torch
+    import paper_2207_13901_amd as spl
+
+    def z(*s, dt=torch.int32):
+        return torch.zeros(*s, dtype=dt)
+
+    i64, f32, f64 = torch.int64, torch.float32, torch.float64
+    for op in (spl.CSR(z(5), z(7), z(7, dt=f32), (4, 9)),
+               spl.CSR(z(5, dt=i64), z(7), z(7, dt=torch.bfloat16), (4, 9)),
+               spl.CSF(z(5), z(3), z(4), z(7), z(7, dt=f64), (4, 5, 6)),
+               spl.CSF(z(5, dt=i64), z(3), z(4, dt=i64), z(7), z(7, dt=f64), (4, 5, 6)),
+               spl.DDC(z(21), z(7), z(7, dt=f64), (4, 5, 6))):
+        assert op.packed() == bytes(op.struct()), op
+    for d in (z(5, dt=f64), z(0, dt=f64), z(4, 6, dt=f32), z(4, 9, dt=f32)[:, 2:5],
+              z(1, 9, dt=f32)[:, 2:5], z(0, 3, dt=f64), z(3, 0, dt=f64)):
+        assert spl._dense_arg(d) == bytes(spl._dense(d)), d.shape
+    for bad in (z(8, dt=f64)[::2], z(4, 6, dt=f32).t(), z(2, 2, 2, dt=f32)):
+        for marshal in (spl._dense, spl._dense_arg):
+            with pytest.raises(ValueError):
+                marshal(bad)
