@@ -1131,11 +1131,12 @@ hipError_t launch_spmv_fixup(int dtype, int64_t n, const Tiles &t, int64_t strid
 }
 
 // Items that the small-matrix leaf takes, and the longest row (a bound is
-// enough) that one of its workgroups should be left with: 256 workgroups, one
+// enough) that one of its workgroups should be left with: 1,024 workgroups, four
 // per CU, and eight rounds of a long row's positions, about what the
-// partition and fix-up launches take on the GPU.
+// partition and fix-up launches take on the GPU (3.6e5 items: 9.0 us a call
+// against 15).
 bool spmv_is_small(int64_t n, int64_t m, int64_t nnz) {
-    return n + nnz <= 256 * kSmallChunk && std::min(m, nnz) <= 8 * kSmallDeep * kBlock;
+    return n + nnz <= 1024 * kSmallChunk && std::min(m, nnz) <= 8 * kSmallDeep * kBlock;
 }
 
 hipError_t launch_spmv_small(int dtype, bool pos64, int64_t n, int64_t nnz, const void *pos,

@@ -273,7 +273,8 @@ SMALL_ROWS = {
     "edges": [1023, 0, 1022, 1, 1024, 0, 1025, 2047, 3, 0, 0],
     "long_after_short": [1] * 511 + [9000] + [2] * 5, "long_first": [4096 + 1023, 0, 7],
     "whole_rounds": [1023 + 3 * 4096], "empty_chunks": [0] * 5000 + [3] + [0] * 3000,
-    "trailing_long": [5] * 200 + [32768], "largest": [15] * 16384, "above": [15] * 16384 + [0],
+    "trailing_long": [5] * 200 + [32768], "quarter_million": [15] * 16384,
+    "largest": [15] * 65536, "above": [15] * 65536 + [0],
     "longest": [32768], "above_longest": [32769],
 }
 
