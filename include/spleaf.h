@@ -453,9 +453,9 @@ spl_status spl_spadd3_symbolic(spl_context *ctx, const spl_sparse *B, const spl_
  * coordinate.  sched->variant picks the form: 1 a lane per row merging its
  * inputs read directly from memory, 2 the same with the workgroup's
  * coordinate runs staged in LDS, 3 with coordinates and values staged,
- * 4 by ranks (coordinates staged, a lane per input entry computing its
- * output slot by binary search in the other operands' rows); 0 the library
- * default (4).  Workgroups whose runs exceed the
+ * 4 with the coordinate runs staged, a lane per row noting which operands
+ * hold each output entry and a lane per output entry finding its inputs by
+ * counting those notes; 0 the library default (4).  Workgroups whose runs exceed the
  * stage fall back to direct reads; every variant gives the same bits, and
  * anything else is SPL_ERR_ARG. */
 spl_status spl_spadd3_numeric(spl_context *ctx, const spl_sparse *B, const spl_sparse *C,

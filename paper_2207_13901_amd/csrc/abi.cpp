@@ -25,12 +25,12 @@ struct spl_context {
     void *ws = nullptr;   // context-owned workspace (used when the caller gives none)
     size_t ws_bytes = 0;
     int64_t *flags = nullptr;  // 2 x int64 device scratch for spl_validate
-    // pinned host slot for the counts read back to the host (an output's
-    // nonzero count, spl_validate's flags): a copy into pinned memory is a
-    // plain DMA, where pageable memory goes through the runtime's staging
-    // buffer.  Calls on one context are not meant to overlap across host
+    // pinned host slot for the counts read back to the host: an output's
+    // nonzero count, which the scan's kernel writes there itself (no copy;
+    // `counted` tells the host), and spl_validate's flags, copied.  Calls on one context are not meant to overlap across host
     // threads (the error string is shared too).
     int64_t *readback = nullptr;  // 2 x int64
+    hipEvent_t counted = nullptr;
     // leaf-kernel timing (spl_timing_enable / spl_timing_read)
     struct Mark {
         hipEvent_t start, stop;
@@ -642,7 +642,8 @@ size_t inner_ws(const spl_sparse *B) {
 }
 
 size_t spadd3_ws(int64_t n) {
-    return align_up(static_cast<size_t>(spl::spadd3_scan_tiles(n)) * 8) + align_up(8);
+    const size_t blocks = static_cast<size_t>(spl::spadd3_blocks(n));
+    return align_up(blocks * 8) + align_up(blocks * 4);
 }
 
 bool same_dims(const spl_sparse *a, const spl_sparse *b) {
@@ -878,9 +879,11 @@ spl_status spl_context_create(int device, spl_context **out) {
     if (hipSetDevice(device) != hipSuccess ||
         hipMalloc(reinterpret_cast<void **>(&ctx->flags), 2 * sizeof(int64_t)) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void **>(&ctx->readback), 2 * sizeof(int64_t),
-                      hipHostMallocDefault) != hipSuccess) {
+                      hipHostMallocDefault) != hipSuccess ||
+        hipEventCreateWithFlags(&ctx->counted, hipEventDisableTiming) != hipSuccess) {
         (void)hipGetLastError();
         if (ctx->flags) (void)hipFree(ctx->flags);
+        if (ctx->readback) (void)hipHostFree(ctx->readback);
         delete ctx;
         return SPL_ERR_HIP;
     }
@@ -899,6 +902,7 @@ spl_status spl_context_destroy(spl_context *ctx) {
     if (ctx->ws) (void)hipFree(ctx->ws);
     if (ctx->flags) (void)hipFree(ctx->flags);
     if (ctx->readback) (void)hipHostFree(ctx->readback);
+    if (ctx->counted) (void)hipEventDestroy(ctx->counted);
     for (const auto &m : ctx->marks) {
         (void)hipEventDestroy(m.start);
         (void)hipEventDestroy(m.stop);
@@ -1740,13 +1744,14 @@ spl_status spl_sddmm(spl_context *ctx, const spl_sparse *B, const spl_dense *C,
 
 namespace {
 // The numeric phase's default form (0 direct, 1 coordinates staged, 2
-// coordinates and values staged, 3 by ranks).
+// The numeric phase's default form (0 direct, 1 coordinates staged, 2
+// coordinates and values staged, 3 coordinates staged and entries counted).
 constexpr int kSpadd3DefaultStage = 3;
 
 // sched->variant (0..4) picks the numeric phase's form: 0 library default,
 // 1..3 the merges (inputs read directly, coordinate runs staged in LDS,
-// coordinates and values staged), 4 by ranks (coordinates staged, a lane per
-// input entry).  The symbolic phase checks it and counts by merge always.
+// coordinates and values staged), 4 by counting (coordinates staged, a lane
+// per output entry).  The symbolic phase checks it and counts by merge always.
 spl_status spadd3_variant(spl_context *ctx, const spl_schedule *sched, int *variant) {
     *variant = sched ? sched->variant : 0;
     if (*variant < 0 || *variant > 4) return fail(ctx, SPL_ERR_ARG, "SpAdd3 variant must be 0..4");
@@ -1783,18 +1788,16 @@ spl_status spl_spadd3_symbolic(spl_context *ctx, const spl_sparse *B, const spl_
     const int64_t n = B->dims[0];
     void *ws = nullptr;
     SPL_CHECK(get_workspace(ctx, workspace, workspace_bytes, spadd3_ws(n), &ws));
-    int64_t *tile_sum = static_cast<int64_t *>(ws);
-    int64_t *total =
-        reinterpret_cast<int64_t *>(static_cast<char *>(ws) +
-                                    align_up(static_cast<size_t>(spl::spadd3_scan_tiles(n)) * 8));
+    int64_t *base = static_cast<int64_t *>(ws);
+    int32_t *block_sum = reinterpret_cast<int32_t *>(
+        static_cast<char *>(ws) + align_up(static_cast<size_t>(spl::spadd3_blocks(n)) * 8));
     LeafTimer tm(ctx, SPL_OP_SPADD3, s);
-    SPL_HIP(spl::launch_spadd3_symbolic(n, B->pos[1], B->crd[1], C->pos[1], C->crd[1], D->pos[1],
-                                        D->crd[1], A_pos, tile_sum, total, s),
+    SPL_HIP(spl::launch_spadd3_symbolic(n, B->nnz + C->nnz + D->nnz, B->pos[1], B->crd[1], C->pos[1],
+                                        C->crd[1], D->pos[1], D->crd[1], A_pos, base, block_sum,
+                                        ctx->readback, ctx->counted, s),
             "SpAdd3 symbolic launch");
     tm.stop();
-    SPL_HIP(hipMemcpyAsync(ctx->readback, total, sizeof(int64_t), hipMemcpyDeviceToHost, s),
-            "hipMemcpyAsync");
-    SPL_HIP(hipStreamSynchronize(s), "hipStreamSynchronize");
+    SPL_HIP(hipEventSynchronize(ctx->counted), "hipEventSynchronize");
     const int64_t host_total = ctx->readback[0];
     if (host_total > kIndexMax)
         return fail(ctx, SPL_ERR_SHAPE, "output nnz %lld exceeds int32 positions",
@@ -1822,7 +1825,7 @@ spl_status spl_spadd3_numeric(spl_context *ctx, const spl_sparse *B, const spl_s
     SPL_CHECK(set_device(ctx));
     hipStream_t s = static_cast<hipStream_t>(stream);
     LeafTimer tm(ctx, SPL_OP_SPADD3, s);
-    SPL_HIP(spl::launch_spadd3_numeric(B->vtype, n, B->pos[1], B->crd[1], B->vals, C->pos[1],
+    SPL_HIP(spl::launch_spadd3_numeric(B->vtype, n, B->nnz + C->nnz + D->nnz, B->pos[1], B->crd[1], B->vals, C->pos[1],
                                        C->crd[1], C->vals, D->pos[1], D->crd[1], D->vals, A_pos,
                                        A_crd, A_vals, stage, s),
             "SpAdd3 numeric launch");
@@ -1909,17 +1912,14 @@ spl_status spl_tin_symbolic(spl_context *ctx, const char *tin, int nops, const s
     SPL_CHECK(get_workspace(ctx, workspace, workspace_bytes, spl::tin::workspace_bytes(prog, true),
                             &ws));
     int64_t *tile_sum = static_cast<int64_t *>(ws);
-    int64_t *total = reinterpret_cast<int64_t *>(
-        static_cast<char *>(ws) + align_up(static_cast<size_t>(spl::spadd3_scan_tiles(prog.rows)) * 8));
     std::vector<unsigned long long> slots;
     unsigned block = 256, lds = 0;
     spl::tin::stage_shape(prog, b, -1, block, lds);
     spl::tin::fill_slots(prog, b, ob, A_pos, nullptr, nullptr, lds, slots);
     SPL_HIP(tin_launch(cp->f_count, prog.rows, slots, s, block, lds), "generated count launch");
-    SPL_HIP(spl::launch_pos_scan(prog.rows, A_pos, tile_sum, total, s), "scan launch");
-    SPL_HIP(hipMemcpyAsync(ctx->readback, total, sizeof(int64_t), hipMemcpyDeviceToHost, s),
-            "hipMemcpyAsync");
-    SPL_HIP(hipStreamSynchronize(s), "hipStreamSynchronize");
+    SPL_HIP(spl::launch_pos_scan(prog.rows, A_pos, tile_sum, ctx->readback, s, ctx->counted),
+            "scan launch");
+    SPL_HIP(hipEventSynchronize(ctx->counted), "hipEventSynchronize");
     const int64_t host_total = ctx->readback[0];
     if (host_total > kIndexMax)
         return fail(ctx, SPL_ERR_SHAPE, "output nnz %lld exceeds int32 positions",

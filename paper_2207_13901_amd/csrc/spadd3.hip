@@ -8,15 +8,15 @@
 // results).
 //
 // Values are summed in operand order B, C, D over the operands present (a
-// cancellation to zero keeps its coordinate).  The symbolic phase copies
-// the workgroup's input coordinates to LDS with coalesced loads, and one
-// lane per row merges the three sorted coordinate lists there to count the
-// union.  The scan is three passes: per-workgroup totals, one workgroup
-// scanning the totals, per-workgroup rescan.  The numeric phase's default
-// form works by ranks: with the coordinates staged, every input entry finds
-// its own output slot by binary search in the other operands' rows, so the
-// work is spread over all lanes and every input line is read with coalesced
-// loads.  The merge forms (one lane per row, output staged in LDS windows
+// cancellation to zero keeps its coordinate).  Both phases copy the
+// workgroup's input coordinates to LDS with coalesced loads, and one lane per
+// row merges the three sorted coordinate lists there.  The symbolic phase
+// counts the union, leaving sums within workgroups and their totals, which one
+// workgroup scans and a last kernel adds.  The numeric phase's default form
+// notes which operands hold each coordinate of the union; with that, every
+// lane finds its output entries' inputs by counting and reads and writes
+// beside its neighbours (k_spadd3_bits).  The merge forms (one lane per row,
+// output staged in LDS windows
 // so that its stores are coalesced) remain as schedule variants: one lane
 // per row reading or storing straight to HBM keeps far more partly used
 // lines open than the caches hold, and a window is filled only by the lanes
@@ -160,51 +160,6 @@ __device__ __forceinline__ int32_t union_count(const Csr3 &m, const Crd3 &x, int
     return k;
 }
 
-// The same from the staged runs s_x (first positions f), without branches:
-// each step takes the smallest head, advances every list holding it and
-// reads all three heads again at indices clamped into the stage, so a step
-// is one round of LDS reads instead of up to three behind lane-masked
-// branches.
-__device__ __forceinline__ int32_t union_count_staged(const Csr3 &m, int32_t (*s_x)[kStageCap],
-                                                      const int32_t *f, int64_t i) {
-    constexpr int32_t kInf = Merge3::kInf;
-    int32_t p[3] = {m.bp[i] - f[0], m.cp[i] - f[1], m.dp[i] - f[2]};
-    const int32_t e[3] = {m.bp[i + 1] - f[0], m.cp[i + 1] - f[1], m.dp[i + 1] - f[2]};
-    auto head = [&](int X) {
-        const int32_t q = p[X] < kStageCap ? p[X] : kStageCap - 1;
-        const int32_t v = s_x[X][q];
-        return p[X] < e[X] ? v : kInf;
-    };
-    int32_t h[3] = {head(0), head(1), head(2)};
-    int32_t k = 0;
-    while (min(h[0], min(h[1], h[2])) != kInf) {
-        const int32_t c = min(h[0], min(h[1], h[2]));
-#pragma unroll
-        for (int X = 0; X < 3; ++X) p[X] += h[X] == c ? 1 : 0;
-#pragma unroll
-        for (int X = 0; X < 3; ++X) h[X] = head(X);
-        ++k;
-    }
-    return k;
-}
-
-__global__ __launch_bounds__(kBlock) void k_spadd3_count(int64_t n, Csr3 m, int32_t *apos) {
-    __shared__ int32_t s_x[3][kStageCap];
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kBlock;
-    const int64_t r1 = r0 + kBlock < n ? r0 + kBlock : n;
-    const int64_t i = r0 + threadIdx.x;
-    int32_t f[3];
-    const bool staged = stage_crd(m, r0, r1, s_x, f);
-    if (i == 0) apos[0] = 0;
-    if (i >= n) return;
-    // the staged path is code of its own, so that it reads LDS directly
-    // rather than through generic (flat) loads
-    if (staged)
-        apos[i + 1] = union_count_staged(m, s_x, f, i);
-    else
-        apos[i + 1] = union_count(m, Crd3{m.bc, m.cc, m.dc, 0, 0, 0}, i);
-}
-
 // Numeric phase.  The 256 rows of a workgroup own one contiguous run of the
 // output, [apos[r0], apos[r0 + 256]), written in windows of kFillCap
 // entries: in each window every lane continues its row's merge from where
@@ -219,7 +174,7 @@ constexpr int kFillCap = 2048;
 // The workgroup's rows [r0, r1) merged a lane per row into output windows
 // of kWin entries in LDS (w_crd, w_val), each window written with coalesced
 // stores.
-template <typename V, int kWin>
+template <typename V, int kWin, int T = kBlock>
 __device__ __forceinline__ void fill_windows(int64_t n, const Csr3 &m, const Crd3 &x,
                                              const Vals3<V> &vv, const int32_t *apos,
                                              int32_t *acrd, V *aval, int64_t r0, int64_t r1,
@@ -240,7 +195,7 @@ __device__ __forceinline__ void fill_windows(int64_t n, const Csr3 &m, const Crd
             w_val[k - w] = sum;
         }
         __syncthreads();
-        for (int64_t q = threadIdx.x; q < we - w; q += kBlock) {
+        for (int64_t q = threadIdx.x; q < we - w; q += T) {
             store_stream(acrd + base + w + q, w_crd[q]);
             store_stream(aval + base + w + q, w_val[q]);
         }
@@ -289,303 +244,355 @@ __global__ __launch_bounds__(kBlock) void k_spadd3_fill(int64_t n, Csr3 m, const
                           apos, acrd, aval, r0, r1, s_crd, s_val);
 }
 
-// Numeric phase by ranks.  The workgroup's coordinate runs of the three
-// operands are staged in LDS, and every input entry then finds its output
-// slot by itself, a lane per entry: an entry of C duplicates one of B when
-// B's row holds its coordinate, an entry of D when B's or C's row does; the
-// first operand holding a coordinate owns it and writes it at
-//   A.pos[i] + #(B_i < x) + #(owned C_i < x) + #(owned D_i < x),
-// the counts from lower bounds by binary search in the staged rows less the
-// duplicates below them, which come from one ballot of the duplicate flags
-// per 64 entries and a prefix over those words.  The owner adds the values
-// of the duplicates in the order B, C, D as the merge does.  Every input
-// line is read with coalesced loads (values by their owner lanes, the
-// duplicates' values gathered from lines their neighbours read), and no lane
-// walks a whole row.  Runs longer than kRankCap fall back to the windowed
-// merge for that workgroup.  A workgroup takes 128 rows with its 256 lanes
-// (5 entries a lane and operand, 22 KB of LDS): 0.142 ms on three 1e6-row
-// operands of 8 entries a row, against 0.153 with 192 rows (7 a lane,
-// 31 KB), 0.166 with 256 (9 a lane, 40 KB, 4 workgroups a CU) and 0.149
-// with 64 (3 a lane): more workgroups per CU until a lane has too little
-// to overlap.
-constexpr int kRankRows = 128;                 // rows per workgroup
-constexpr int kRankCap = 1280;                 // entries per operand and workgroup
-constexpr int kRankPer = kRankCap / kBlock;     // entries per lane and operand
-constexpr int kRankChunks = kRankCap / 64 + 1;  // ballot words, one spare for a full run
-static_assert(kRankCap % kBlock == 0, "whole entries per lane");
-static_assert(kRankRows <= 256 && kRankRows <= kBlock, "a row index fits a byte, a lane per row");
-static_assert(kRankChunks <= 64, "one wave scans the ballot words");
+// ---- count and default fill: rows staged in dynamic LDS -------------------
+//
+// A workgroup of T lanes takes T rows and stages the three operands'
+// coordinate runs, each with a spare entry behind it, so that a lane walks
+// its row's three lists there without branches.  T and the LDS asked for
+// follow the operands' mean row lengths (stage_rows); a workgroup whose runs
+// do not fit walks them in HBM.
+
+struct Runs {
+    int32_t first[3], n[3];
+};
+
+__device__ __forceinline__ Runs runs_of(const Csr3 &m, int64_t r0, int64_t r1) {
+    Runs R;
+    R.first[0] = m.bp[r0];
+    R.first[1] = m.cp[r0];
+    R.first[2] = m.dp[r0];
+    R.n[0] = m.bp[r1] - R.first[0];
+    R.n[1] = m.cp[r1] - R.first[1];
+    R.n[2] = m.dp[r1] - R.first[2];
+    return R;
+}
+__device__ __forceinline__ int64_t runs_bytes(const Runs &R) {
+    return 4 * (static_cast<int64_t>(R.n[0]) + R.n[1] + R.n[2] + 3);
+}
+
+// Copies the runs to x[0], x[1], x[2] (kStageDeep entries per lane and operand
+// loaded before the first is stored) and synchronizes the workgroup.
+constexpr int kStageDeep = 10;
+
+template <int T>
+__device__ __forceinline__ void stage_runs(const Csr3 &m, const Runs &R, int32_t *const (&x)[3]) {
+    const int32_t *src[3] = {m.bc + R.first[0], m.cc + R.first[1], m.dc + R.first[2]};
+    const int most = max(R.n[0], max(R.n[1], R.n[2]));
+    for (int k0 = threadIdx.x; k0 - static_cast<int>(threadIdx.x) < most; k0 += kStageDeep * T) {
+        uint32_t v[3][kStageDeep];
+#pragma unroll
+        for (int X = 0; X < 3; ++X) {
+            const auto rc = span_rsrc(src[X], 4u * static_cast<uint32_t>(R.n[X]));
+#pragma unroll
+            for (int j = 0; j < kStageDeep; ++j)
+                v[X][j] = buf_u32(rc, 4u * static_cast<uint32_t>(k0 + j * T));
+        }
+#pragma unroll
+        for (int X = 0; X < 3; ++X)
+#pragma unroll
+            for (int j = 0; j < kStageDeep; ++j)
+                if (k0 + j * T < R.n[X]) x[X][k0 + j * T] = static_cast<int32_t>(v[X][j]);
+    }
+    __syncthreads();
+}
+
+// Walks row i's staged lists: calls found(bits) for every coordinate of the
+// union in order, bit X set when operand X holds it.
+template <typename Found>
+__device__ __forceinline__ void walk_staged(const Csr3 &m, const Runs &R, int32_t *const (&x)[3],
+                                            int64_t i, Found found) {
+    constexpr int32_t kInf = Merge3::kInf;
+    int32_t p[3] = {m.bp[i] - R.first[0], m.cp[i] - R.first[1], m.dp[i] - R.first[2]};
+    const int32_t e[3] = {m.bp[i + 1] - R.first[0], m.cp[i + 1] - R.first[1],
+                          m.dp[i + 1] - R.first[2]};
+    auto head = [&](int X) {
+        const int32_t v = x[X][p[X]];  // p <= the run's length: at most its spare entry
+        return p[X] < e[X] ? v : kInf;
+    };
+    int32_t h[3] = {head(0), head(1), head(2)};
+    for (int32_t c = min(h[0], min(h[1], h[2])); c != kInf; c = min(h[0], min(h[1], h[2]))) {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int X = 0; X < 3; ++X) {
+            const uint32_t has = h[X] == c ? 1u : 0u;
+            p[X] += static_cast<int32_t>(has);
+            bits |= has << X;
+        }
+#pragma unroll
+        for (int X = 0; X < 3; ++X) h[X] = head(X);
+        found(bits);
+    }
+}
+
+// Inclusive sum over the T lanes of the workgroup; *all gets the total.
+template <int T>
+__device__ __forceinline__ int32_t group_inclusive(int32_t v, int32_t *s_wave, int32_t *all) {
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int32_t u = __shfl_up(v, off);
+        v += lane >= off ? u : 0;
+    }
+    if (lane == kWave - 1) s_wave[wave] = v;
+    __syncthreads();
+    int32_t total = 0;
+#pragma unroll
+    for (int w = 0; w < T / kWave; ++w) {
+        v += w < wave ? s_wave[w] : 0;
+        total += s_wave[w];
+    }
+    *all = total;
+    return v;
+}
+
+// Symbolic phase (35 us on the operands described at k_spadd3_bits, whose
+// coordinates are 0.11 GB: bound by the walks' vector-ALU work as much as by
+// HBM): apos[i + 1] = entries of the workgroup's output rows up to
+// row i, block_sum = all of them (k_block_bases and k_add_bases then make
+// positions of them).
+template <int T>
+__global__ __launch_bounds__(T) void k_spadd3_count(int64_t n, Csr3 m, int room, int32_t *apos,
+                                                    int32_t *block_sum) {
+    extern __shared__ __align__(16) int32_t s_pool[];
+    __shared__ int32_t s_wave[T / kWave];
+    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * T;
+    const int64_t r1 = r0 + T < n ? r0 + T : n;
+    const int64_t i = r0 + threadIdx.x;
+    const Runs R = runs_of(m, r0, r1);
+    int32_t k = 0;
+    if (runs_bytes(R) <= room) {
+        int32_t *const x[3] = {s_pool, s_pool + R.n[0] + 1, s_pool + R.n[0] + R.n[1] + 2};
+        stage_runs<T>(m, R, x);
+        if (i < n) walk_staged(m, R, x, i, [&](uint32_t) { ++k; });
+    } else if (i < n) {
+        k = union_count(m, Crd3{m.bc, m.cc, m.dc, 0, 0, 0}, i);
+    }
+    int32_t all;
+    const int32_t upto = group_inclusive<T>(k, s_wave, &all);
+    if (i < n) apos[i + 1] = upto;
+    if (threadIdx.x == 0) block_sum[blockIdx.x] = all;
+}
+
+// One workgroup: base[b] = sum of block_sum[0 .. b - 1]; the total to *total
+// (pinned host memory).  1,024 lanes, kBasePer consecutive blocks each a round.
+constexpr int kBaseLanes = 1024, kBasePer = 8;
+
+__global__ __launch_bounds__(kBaseLanes) void k_block_bases(int64_t blocks,
+                                                            const int32_t *__restrict__ block_sum,
+                                                            int64_t *__restrict__ base, int64_t *total) {
+    __shared__ int64_t s_wave[kBaseLanes / kWave];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    int64_t carry = 0;
+    for (int64_t b0 = 0; b0 < blocks; b0 += kBaseLanes * kBasePer) {
+        const int64_t b = b0 + static_cast<int64_t>(threadIdx.x) * kBasePer;
+        int64_t v[kBasePer], sum = 0;
+#pragma unroll
+        for (int j = 0; j < kBasePer; ++j) v[j] = b + j < blocks ? block_sum[b + j] : 0;
+#pragma unroll
+        for (int j = 0; j < kBasePer; ++j) sum += v[j];
+        int64_t inc = sum;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int64_t u = __shfl_up(inc, off);
+            inc += lane >= off ? u : 0;
+        }
+        if (lane == kWave - 1) s_wave[wave] = inc;
+        __syncthreads();
+        int64_t all = 0, run = carry + inc - sum;
+        for (int w = 0; w < kBaseLanes / kWave; ++w) {
+            run += w < wave ? s_wave[w] : 0;
+            all += s_wave[w];
+        }
+#pragma unroll
+        for (int j = 0; j < kBasePer; ++j) {
+            if (b + j < blocks) base[b + j] = run;
+            run += v[j];
+        }
+        carry += all;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *total = carry;
+}
+
+// apos[i + 1] += base of row i's block of 2^log2rows rows; apos[0] = 0.
+// A workgroup takes 1,024 rows.  base == nullptr: it adds up the block sums
+// before its own by itself, which costs less than another launch while they
+// are few, and the last workgroup writes the total.
+constexpr int kAddRows = 4;
+constexpr int64_t kOwnBases = 16384;  // blocks up to which it does
+
+__global__ __launch_bounds__(kBlock) void k_add_bases(int64_t n, int log2rows, int64_t blocks,
+                                                      const int64_t *__restrict__ base,
+                                                      const int32_t *__restrict__ block_sum,
+                                                      int32_t *__restrict__ apos, int64_t *total) {
+    __shared__ int64_t s_sum[kBlock / kWave];
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * kBlock * kAddRows;
+    int64_t before = 0;  // entries before the workgroup's first block
+    if (!base) {
+        const int64_t fb = first >> log2rows;
+#pragma unroll 8
+        for (int64_t b = threadIdx.x; b < fb; b += kBlock) before += block_sum[b];
+        before = group_sum<kWave>(before);
+        if (threadIdx.x % kWave == 0) s_sum[threadIdx.x / kWave] = before;
+        __syncthreads();
+        before = 0;
+#pragma unroll
+        for (int w = 0; w < kBlock / kWave; ++w) before += s_sum[w];
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+            int64_t all = before;
+            for (int64_t b = fb; b < blocks; ++b) all += block_sum[b];
+            *total = all;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kAddRows; ++j) {
+        const int64_t i = first + threadIdx.x + j * kBlock;
+        if (i >= n) continue;
+        int64_t add = before;
+        if (base)
+            add = base[i >> log2rows];
+        else
+            for (int64_t b = first >> log2rows; b < i >> log2rows; ++b) add += block_sum[b];
+        apos[i + 1] += static_cast<int32_t>(add);
+    }
+    if (first + threadIdx.x == 0) apos[0] = 0;
+}
 
 // Value at byte offset `off` of a buffer (0 past its range, with no access).
 __device__ __forceinline__ float buf_load(const float *, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 2));
 }
 __device__ __forceinline__ double buf_load(const double *, __amdgpu_buffer_rsrc_t r,
                                            uint32_t off) {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+    const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 2);
     return __hiloint2double(static_cast<int>(w[1]), static_cast<int>(w[0]));
 }
 
-__device__ __forceinline__ int lower_bound_lds(const int32_t *a, int lo, int hi, int32_t x) {
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (a[mid] < x)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    return lo;
-}
+// Numeric phase (default form): the lane of a row walks its staged lists and
+// leaves one byte per output entry, which operands hold it.  The workgroup's
+// output entries, like its input entries, are in row and coordinate order, so
+// the position of operand X's entry behind output entry k is the number of
+// entries before k whose bit X is set: a wave takes 64 consecutive output
+// entries, finds those numbers with ballots and a running count, and reads
+// coordinates (LDS) and values and writes the output with consecutive lanes
+// on consecutive addresses.  Every wave takes one run of these words; a first
+// pass counts its bits, so that the others know where theirs start.
+//
+// Three FP32 operands of 1e6 rows and 8 entries a row (24e6 in, 18.4e6 out; 0.35
+// GB, 73 us at the rate of a copy) take 103 us, 138 when every input entry
+// looked for its output slot by binary search in the other operands' rows
+// (its counts of 64-bit masks and searches kept the vector ALUs busy).  Ten
+// words in flight: 131 us with two, 119 with four, 111 with eight, 127 with 16.
+constexpr int kFillWords = 10;   // words of 64 entries in flight per wave
+constexpr int kFillWin = 512;    // output window of the walk in HBM
 
-// Flagged entries among the first k of a run: the prefix of k's 64-entry
-// word plus the flags below k inside it.
-__device__ __forceinline__ int flags_below(const uint64_t *mask, const int32_t *pre, int k) {
-    const int c = k >> 6;
-    return pre[c] + __popcll(mask[c] & ((1ull << (k & 63)) - 1));
-}
-
-// LDS of the rank forms: the coordinate runs, the row of each staged entry
-// (relative to the workgroup's first row), the rows' starts in the runs,
-// the duplicate flags of C and D with their per-word prefixes, and a
-// per-row constant of the output slots.
-struct RankLds {
-    int32_t x[3][kRankCap];
-    uint8_t row[3][kRankCap];
-    int32_t start[3][kRankRows + 1];
-    uint64_t mask[2][kRankChunks];
-    int32_t pre[2][kRankChunks];
-    int32_t base[kRankRows];
-
-    __device__ __forceinline__ int lb(int X, int r, int32_t v) const {
-        return lower_bound_lds(x[X], start[X][r], start[X][r + 1], v);
-    }
-    __device__ __forceinline__ bool holds(int X, int r, int p, int32_t v) const {
-        return p < start[X][r + 1] && x[X][p] == v;
-    }
-    // owned entries of C (X = 1) or D (X = 2) before staged index k of the run
-    __device__ __forceinline__ int owned(int X, int k) const {
-        return k - flags_below(mask[X - 1], pre[X - 1], k);
-    }
-    __device__ __forceinline__ bool dup(int X, int e) const {
-        return (mask[X - 1][e >> 6] >> (e & 63)) & 1;
-    }
-};
-
-// What the flag pass found for a lane's entries of C and D, kept for the
-// output pass: the row (8 bits) and the lower bounds in B's row and, for D,
-// in C's row (12 bits each, kRankCap <= 4096).
-struct RankSeen {
-    uint32_t c[kRankPer], d[kRankPer];
-};
-static_assert(kRankCap <= 4096, "staged indices fit 12 bits");
-
-// Stages rows [r0, r0 + nr) whose runs (n3 entries from first3) fit, flags
-// the duplicates and sets the per-row constants
-//   base[r] = apos[r] - apos[r0] - start_B[r] - owned_C(start_C[r]) - owned_D(start_D[r]),
-// so that an entry's output slot, relative to the workgroup's first output,
-// is base[r] plus its counts before it.
-// Ends with the workgroup synchronized.
-__device__ void rank_prepare(const Csr3 &m, int64_t r0, int nr, const int32_t *first3,
-                             const int32_t *n3, const int32_t *apos, RankLds &L,
-                             RankSeen &S) {
-    const int t = threadIdx.x;
-    const int32_t *pos[3] = {m.bp, m.cp, m.dp};
-    const int32_t *crd[3] = {m.bc, m.cc, m.dc};
-    const int32_t *src[3] = {crd[0] + first3[0], crd[1] + first3[1], crd[2] + first3[2]};
-    int32_t *dst[3] = {L.x[0], L.x[1], L.x[2]};
-    stage3<kRankPer>(src, n3, dst);
-#pragma unroll
-    for (int X = 0; X < 3; ++X)
-        for (int r = t; r <= nr; r += kBlock) L.start[X][r] = pos[X][r0 + r] - first3[X];
-    __syncthreads();
-    if (t < nr) {
-#pragma unroll
-        for (int X = 0; X < 3; ++X)
-            for (int k = L.start[X][t]; k < L.start[X][t + 1]; ++k) L.row[X][k] = t;
-    }
-    __syncthreads();
-    const int lane = t & 63, wave = t >> 6;
-#pragma unroll
-    for (int j = 0; j < kRankPer; ++j) {  // C entries that B's row holds
-        const int e = j * kBlock + t;
-        bool d = false;
-        S.c[j] = 0;
-        if (e < n3[1]) {
-            const int r = L.row[1][e];
-            const int32_t v = L.x[1][e];
-            const int p = L.lb(0, r, v);
-            d = L.holds(0, r, p, v);
-            S.c[j] = r | (p << 8);
-        }
-        const uint64_t word = __ballot(d);
-        if (lane == 0) L.mask[0][4 * j + wave] = word;
-    }
-#pragma unroll
-    for (int j = 0; j < kRankPer; ++j) {  // D entries that B's or C's row holds
-        const int e = j * kBlock + t;
-        bool d = false;
-        S.d[j] = 0;
-        if (e < n3[2]) {
-            const int r = L.row[2][e];
-            const int32_t v = L.x[2][e];
-            const int p = L.lb(0, r, v), q = L.lb(1, r, v);
-            d = L.holds(0, r, p, v) || L.holds(1, r, q, v);
-            S.d[j] = r | (p << 8) | (q << 20);
-        }
-        const uint64_t word = __ballot(d);
-        if (lane == 0) L.mask[1][4 * j + wave] = word;
-    }
-    static_assert(kBlock == 256, "four waves: word 4j + wave holds entries j*256 + 64*wave ..");
-    __syncthreads();
-    if (wave < 2) {  // exclusive prefix of the flag counts per word: wave 0 for C, 1 for D
-        const int words = (n3[1 + wave] + 63) >> 6;
-        int cnt = 0;
-        if (lane < kRankChunks) {
-            if (lane < words)
-                cnt = __popcll(L.mask[wave][lane]);
-            else
-                L.mask[wave][lane] = 0;
-        }
-        int incl = cnt;
-        for (int d = 1; d < 64; d <<= 1) {
-            const int v = __shfl_up(incl, d);
-            if (lane >= d) incl += v;
-        }
-        if (lane < kRankChunks) L.pre[wave][lane] = incl - cnt;
-    }
-    __syncthreads();
-    if (t < nr)
-        L.base[t] = apos[r0 + t] - apos[r0] - L.start[0][t] - L.owned(1, L.start[1][t]) -
-                    L.owned(2, L.start[2][t]);
-    __syncthreads();
-}
-
-// Output slot and value loads of entry j of operand X, when it owns its
-// coordinate (o = -1 otherwise): s1 / s2 are the byte offsets of the values
-// of C / D at that coordinate when they hold it (kBufOut when not).
-template <int X, typename V>
-__device__ __forceinline__ void rank_slot(const RankLds &L, const RankSeen &S, int j, int n,
-                                          int32_t &o, int32_t &x, uint32_t &s1, uint32_t &s2) {
-    const int e = j * kBlock + threadIdx.x;
-    s1 = kBufOut;
-    s2 = kBufOut;
-    o = -1;
-    x = 0;
-    if (e < n && (X == 0 || !L.dup(X, e))) {
-        int r, slot;
-        if constexpr (X == 0) {  // B owns all its entries
-            r = L.row[0][e];
-            x = L.x[0][e];
-            const int p = L.lb(1, r, x), q = L.lb(2, r, x);
-            if (L.holds(1, r, p, x)) s1 = static_cast<uint32_t>(sizeof(V) * p);
-            if (L.holds(2, r, q, x)) s2 = static_cast<uint32_t>(sizeof(V) * q);
-            slot = e + L.owned(1, p) + L.owned(2, q);
-        } else if constexpr (X == 1) {  // B does not hold it
-            r = S.c[j] & 255;
-            x = L.x[1][e];
-            const int p = S.c[j] >> 8, q = L.lb(2, r, x);
-            if (L.holds(2, r, q, x)) s2 = static_cast<uint32_t>(sizeof(V) * q);
-            slot = p + L.owned(1, e) + L.owned(2, q);
-        } else {  // neither B nor C holds it
-            r = S.d[j] & 255;
-            x = L.x[2][e];
-            const int p = (S.d[j] >> 8) & 4095, q = S.d[j] >> 20;
-            slot = p + L.owned(1, q) + L.owned(2, e);
-        }
-        o = L.base[r] + slot;
-    }
-}
-
-// Entries J0 .. J0 + kRankGroup - 1 of each operand that own their
-// coordinate, written at their output slots (relative to the workgroup's
-// first output at acrd, aval).  First the searches in LDS, then the loads
-// of the values of the later operands holding the coordinates, all at
-// once, then the sums (own: the entries' own values, loaded with the
-// staging) and stores.  The three operands' entries of a group fall in
-// about the same rows, so the group fills its output lines while the L2
-// still holds them (one operand after another left them partly written
-// and evicted: 2.3 times the output's bytes written).  Groups of three
-// entries per operand (at 256 rows a workgroup: 0.167 ms on three 1e6-row
-// operands, against 0.175 for groups of one, fewer loads in flight, and
-// 0.189 for one operand after another).
-constexpr int kRankGroup = 3;
-
-template <int J0, typename V>
-__device__ __forceinline__ void rank_emit(const RankLds &L, const RankSeen &S,
-                                          const V *const *vals, const __amdgpu_buffer_rsrc_t *rv,
-                                          const V (*own)[kRankPer], const int32_t *n3,
-                                          int32_t *acrd, V *aval) {
-    // the last group may be short
-    constexpr int NJ = J0 + kRankGroup <= kRankPer ? kRankGroup : kRankPer - J0;
-    int32_t o[3][kRankGroup], xs[3][kRankGroup];
-    V g1[kRankGroup], g2[2][kRankGroup];
-    uint32_t has1 = 0, has2 = 0;  // bit 3X + jj: entry adds C's value (X = 0) / D's (X < 2)
-#pragma unroll
-    for (int jj = 0; jj < NJ; ++jj) {
-        uint32_t s1, s2;
-        rank_slot<0, V>(L, S, J0 + jj, n3[0], o[0][jj], xs[0][jj], s1, s2);
-        g1[jj] = buf_load(vals[1], rv[1], s1);
-        g2[0][jj] = buf_load(vals[2], rv[2], s2);
-        has1 |= static_cast<uint32_t>(s1 != kBufOut) << jj;
-        has2 |= static_cast<uint32_t>(s2 != kBufOut) << jj;
-        rank_slot<1, V>(L, S, J0 + jj, n3[1], o[1][jj], xs[1][jj], s1, s2);
-        g2[1][jj] = buf_load(vals[2], rv[2], s2);
-        has2 |= static_cast<uint32_t>(s2 != kBufOut) << (kRankGroup + jj);
-        rank_slot<2, V>(L, S, J0 + jj, n3[2], o[2][jj], xs[2][jj], s1, s2);
-    }
-#pragma unroll
-    for (int X = 0; X < 3; ++X)
-#pragma unroll
-        for (int jj = 0; jj < NJ; ++jj) {
-            if (o[X][jj] < 0) continue;
-            // the merge's order: B's value, else 0, then + C's, then + D's
-            V v = X == 0 ? own[0][J0 + jj] : V(0) + own[X][J0 + jj];
-            if (X == 0 && ((has1 >> jj) & 1)) v = v + g1[jj];
-            if (X < 2 && ((has2 >> (kRankGroup * X + jj)) & 1)) v = v + g2[X < 2 ? X : 0][jj];
-            acrd[o[X][jj]] = xs[X][jj];
-            aval[o[X][jj]] = v;
-        }
-}
-
-template <typename V>
-__global__ __launch_bounds__(kBlock) void k_spadd3_rank(int64_t n, Csr3 m, const V *bv,
-                                                        const V *cv, const V *dv,
-                                                        const int32_t *apos, int32_t *acrd,
-                                                        V *aval) {
-    __shared__ __align__(16) RankLds L;
-    constexpr int kRankWin = 1024;  // output window of the fallback merge
-    static_assert(kRankWin * (4 + sizeof(V)) <= sizeof(L.x), "fallback windows fit the stage");
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kRankRows;
-    const int64_t r1 = r0 + kRankRows < n ? r0 + kRankRows : n;
-    const int nr = static_cast<int>(r1 - r0);
-    const int32_t first3[3] = {m.bp[r0], m.cp[r0], m.dp[r0]};
-    const int32_t n3[3] = {m.bp[r1] - first3[0], m.cp[r1] - first3[1], m.dp[r1] - first3[2]};
-    if (n3[0] > kRankCap || n3[1] > kRankCap || n3[2] > kRankCap) {
-        fill_windows<V, kRankWin>(n, m, Crd3{m.bc, m.cc, m.dc, 0, 0, 0},
-                                  Vals3<V>{bv, cv, dv, 0, 0, 0}, apos, acrd, aval, r0, r1,
-                                  &L.x[0][0], reinterpret_cast<V *>(&L.x[0][0] + kRankWin));
+template <typename V, int T>
+__global__ __launch_bounds__(T) void k_spadd3_bits(int64_t n, Csr3 m, int room, const V *bv,
+                                                   const V *cv, const V *dv, const int32_t *apos,
+                                                   int32_t *acrd, V *aval) {
+    constexpr int kWaves = T / kWave;
+    extern __shared__ __align__(16) int32_t s_pool[];
+    __shared__ int32_t s_bits[kWaves][3];
+    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * T;
+    const int64_t r1 = r0 + T < n ? r0 + T : n;
+    const int64_t i = r0 + threadIdx.x;
+    const Runs R = runs_of(m, r0, r1);
+    const int32_t out0 = apos[r0];
+    const int count = apos[r1] - out0;
+    if (runs_bytes(R) + count > room) {
+        V *w_val = reinterpret_cast<V *>(s_pool);
+        fill_windows<V, kFillWin, T>(n, m, Crd3{m.bc, m.cc, m.dc, 0, 0, 0},
+                                     Vals3<V>{bv, cv, dv, 0, 0, 0}, apos, acrd, aval, r0, r1,
+                                     reinterpret_cast<int32_t *>(w_val + kFillWin), w_val);
         return;
+    }
+    int32_t *const x[3] = {s_pool, s_pool + R.n[0] + 1, s_pool + R.n[0] + R.n[1] + 2};
+    uint8_t *s_has = reinterpret_cast<uint8_t *>(x[2] + R.n[2] + 1);
+    int q = i < r1 ? apos[i] - out0 : 0;
+    stage_runs<T>(m, R, x);
+    if (i < r1)
+        walk_staged(m, R, x, i, [&](uint32_t bits) { s_has[q++] = static_cast<uint8_t>(bits); });
+    __syncthreads();
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int words = (count + 63) >> 6, per = (words + kWaves - 1) / kWaves;
+    const int w0 = wave * per, w1 = min(w0 + per, words);
+    int32_t at[3] = {0, 0, 0};  // entries of each operand before the wave's next word
+    for (int w = w0; w < w1; ++w) {
+        const int k = w * 64 + lane;
+        const uint32_t has = k < count ? s_has[k] : 0;
+#pragma unroll
+        for (int X = 0; X < 3; ++X) at[X] += __popcll(__ballot((has >> X) & 1));
+    }
+    if (lane == 0)
+        for (int X = 0; X < 3; ++X) s_bits[wave][X] = at[X];
+    __syncthreads();
+#pragma unroll
+    for (int X = 0; X < 3; ++X) {
+        at[X] = 0;
+        for (int w = 0; w < wave; ++w) at[X] += s_bits[w][X];
     }
     const V *vals[3] = {bv, cv, dv};
     __amdgpu_buffer_rsrc_t rv[3];
-    V own[3][kRankPer];  // the lane's entries' values, in flight with the staging
 #pragma unroll
-    for (int X = 0; X < 3; ++X) {
-        rv[X] = span_rsrc(vals[X] + first3[X], sizeof(V) * n3[X]);
+    for (int X = 0; X < 3; ++X)
+        rv[X] = span_rsrc(vals[X] + R.first[X], static_cast<uint32_t>(sizeof(V)) * R.n[X]);
+    const int b1 = R.n[0] + 1, b2 = R.n[0] + R.n[1] + 2;  // where x[1] and x[2] start
+    for (int w = w0; w < w1; w += kFillWords) {
+        uint32_t has[kFillWords];
+        int32_t c[kFillWords];
+        V v[kFillWords][3];
 #pragma unroll
-        for (int j = 0; j < kRankPer; ++j) {
-            const int e = j * kBlock + threadIdx.x;
-            own[X][j] = buf_load(vals[X], rv[X],
-                                 e < n3[X] ? static_cast<uint32_t>(sizeof(V) * e) : kBufOut);
+        for (int u = 0; u < kFillWords; ++u) {
+            const int k = (w + u) * 64 + lane;
+            has[u] = w + u < w1 && k < count ? s_has[k] : 0;
+            int p[3];
+#pragma unroll
+            for (int X = 0; X < 3; ++X) {
+                const bool on = (has[u] >> X) & 1;
+                const uint64_t all = __ballot(on);
+                // at[X] + set lanes below this one
+                p[X] = __builtin_amdgcn_mbcnt_hi(
+                    static_cast<uint32_t>(all >> 32),
+                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(all), at[X]));
+                at[X] += __popcll(all);
+                v[u][X] = buf_load(vals[X], rv[X], on ? static_cast<uint32_t>(sizeof(V)) * p[X] : kBufOut);
+            }
+            // (an entry past the end reads a staged coordinate that goes nowhere)
+            c[u] = s_pool[has[u] & 1 ? p[0] : has[u] & 2 ? b1 + p[1] : b2 + p[2]];
+        }
+#pragma unroll
+        for (int u = 0; u < kFillWords; ++u) {
+            if (!has[u]) continue;
+            const int k = (w + u) * 64 + lane;
+            // the merge's order: B's value, else 0, then + C's, then + D's
+            V s = has[u] & 1 ? v[u][0] : V(0);
+            if (has[u] & 2) s = s + v[u][1];
+            if (has[u] & 4) s = s + v[u][2];
+            store_stream(acrd + out0 + k, c[u]);
+            store_stream(aval + out0 + k, s);
         }
     }
-    RankSeen S;
-    rank_prepare(m, r0, nr, first3, n3, apos, L, S);
-    const int32_t out0 = apos[r0];
-    rank_emit<0>(L, S, vals, rv, own, n3, acrd + out0, aval + out0);
-    rank_emit<3>(L, S, vals, rv, own, n3, acrd + out0, aval + out0);
-    static_assert(kRankPer == 5 && kRankGroup == 3, "groups of 3 and 2");
+}
+
+// Rows per workgroup (128 or 64; 0: not even 64 mean rows fit) and LDS bytes
+// for rows of `per_row` bytes on average.  (On the operands above 64 rows take
+// 5 us more in count and fill together; at half of kMost a CU still holds
+// five workgroups of 128 rows.)
+struct StageShape {
+    int rows;
+    unsigned bytes;
+};
+StageShape stage_rows(double per_row, unsigned least) {
+    constexpr double kSpread = 1.07;  // runs of 64 and more rows vary less than their mean
+    constexpr unsigned kSlack = 512, kMost = 65536;
+    for (int rows : {128, 64}) {
+        const double need = per_row * rows * kSpread + kSlack;
+        if (need > (rows == 128 ? kMost / 2 : kMost)) continue;
+        const unsigned b = (static_cast<unsigned>(need) + 255u) & ~255u;
+        return {rows, b > least ? b : least};
+    }
+    return {0, least};
 }
 
 // Element i of the scanned sequence: x[i], or with window bounds the window
@@ -713,7 +720,7 @@ hipError_t launch_window_offsets(int64_t n, const int32_t *begin, const int32_t 
 }
 
 hipError_t launch_pos_scan(int64_t n, int32_t *apos, int64_t *tile_sum, int64_t *total,
-                           hipStream_t s) {
+                           hipStream_t s, hipEvent_t counted) {
     // apos[1..n] hold counts: scanned in place, apos[0] = 0
     const int64_t nt = spadd3_scan_tiles(n);
     k_scan_tile_sums<<<dim3(static_cast<unsigned>(nt)), kBlock, 0, s>>>(n, apos + 1, nullptr,
@@ -724,31 +731,46 @@ hipError_t launch_pos_scan(int64_t n, int32_t *apos, int64_t *tile_sum, int64_t 
     if ((e = hipGetLastError()) != hipSuccess) return e;
     k_scan_tile_apply<<<dim3(static_cast<unsigned>(nt)), kBlock, 0, s>>>(n, apos + 1, nullptr,
                                                                          nullptr, tile_sum, apos);
-    return hipGetLastError();
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    return counted ? hipEventRecord(counted, s) : hipSuccess;
 }
 
-hipError_t launch_spadd3_symbolic(int64_t n, const int32_t *bp, const int32_t *bc,
+int64_t spadd3_blocks(int64_t n) { return ceil_div(n > 0 ? n : 1, 64); }
+
+hipError_t launch_spadd3_symbolic(int64_t n, int64_t nnz_in, const int32_t *bp, const int32_t *bc,
                                   const int32_t *cp, const int32_t *cc, const int32_t *dp,
-                                  const int32_t *dc, int32_t *apos, int64_t *tile_sum,
-                                  int64_t *total, hipStream_t s) {
+                                  const int32_t *dc, int32_t *apos, int64_t *base,
+                                  int32_t *block_sum, int64_t *total, hipEvent_t counted,
+                                  hipStream_t s) {
     Csr3 m{bp, bc, cp, cc, dp, dc};
-    const dim3 rows_grid(static_cast<unsigned>(ceil_div(n > 0 ? n : 1, kBlock)));
-    k_spadd3_count<<<rows_grid, kBlock, 0, s>>>(n, m, apos);
+    const StageShape g = stage_rows(n ? 4.0 * static_cast<double>(nnz_in) / static_cast<double>(n) : 0, 1024);
+    const int rows = g.rows ? g.rows : 64;
+    const int64_t blocks = ceil_div(n, rows);
+    if (n > 0) {
+        const dim3 grid(static_cast<unsigned>(blocks));
+        const int room = static_cast<int>(g.bytes);
+        if (rows == 128)
+            k_spadd3_count<128><<<grid, 128, g.bytes, s>>>(n, m, room, apos, block_sum);
+        else
+            k_spadd3_count<64><<<grid, 64, g.bytes, s>>>(n, m, room, apos, block_sum);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t nt = spadd3_scan_tiles(n);
-    k_scan_tile_sums<<<dim3(static_cast<unsigned>(nt)), kBlock, 0, s>>>(n, apos + 1, nullptr,
-                                                                        nullptr, tile_sum);
+    const dim3 add_grid(static_cast<unsigned>(ceil_div(n > 0 ? n : 1, kAddRows * kBlock)));
+    const int log2rows = rows == 128 ? 7 : 6;
+    if (blocks <= kOwnBases) {
+        k_add_bases<<<add_grid, kBlock, 0, s>>>(n, log2rows, blocks, nullptr, block_sum, apos, total);
+    } else {
+        k_block_bases<<<1, kBaseLanes, 0, s>>>(blocks, block_sum, base, total);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        k_add_bases<<<add_grid, kBlock, 0, s>>>(n, log2rows, blocks, base, block_sum, apos, total);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_scan_tile_prefix<<<1, kBlock, 0, s>>>(nt, tile_sum, total);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_scan_tile_apply<<<dim3(static_cast<unsigned>(nt)), kBlock, 0, s>>>(n, apos + 1, nullptr,
-                                                                         nullptr, tile_sum, nullptr);
-    return hipGetLastError();
+    return hipEventRecord(counted, s);
 }
 
 template <typename V>
-hipError_t spadd3_fill(int stage, int64_t n, const Csr3 &m, const void *bv, const void *cv,
+hipError_t spadd3_fill(int stage, int64_t n, int64_t nnz_in, const Csr3 &m, const void *bv, const void *cv,
                        const void *dv, const int32_t *apos, int32_t *acrd, void *aval,
                        hipStream_t s) {
     dim3 grid(static_cast<unsigned>(ceil_div(n, kBlock)));
@@ -758,25 +780,33 @@ hipError_t spadd3_fill(int stage, int64_t n, const Csr3 &m, const void *bv, cons
         return hipGetLastError();
     };
     if (stage == 3) {
-        k_spadd3_rank<V><<<dim3(static_cast<unsigned>(ceil_div(n, kRankRows))), kBlock, 0, s>>>(
-            n, m, static_cast<const V *>(bv), static_cast<const V *>(cv),
-            static_cast<const V *>(dv), apos, acrd, static_cast<V *>(aval));
-        return hipGetLastError();
+        // coordinates in, and at most as many bytes out
+        const StageShape g = stage_rows(5.0 * static_cast<double>(nnz_in) / static_cast<double>(n),
+                                        kFillWin * (4 + sizeof(V)));
+        const int room = static_cast<int>(g.bytes);
+        auto bits = [&](auto kern, int rows) {
+            kern<<<dim3(static_cast<unsigned>(ceil_div(n, rows))), rows, g.bytes, s>>>(
+                n, m, room, static_cast<const V *>(bv), static_cast<const V *>(cv),
+                static_cast<const V *>(dv), apos, acrd, static_cast<V *>(aval));
+            return hipGetLastError();
+        };
+        if (g.rows == 128) return bits(k_spadd3_bits<V, 128>, 128);
+        if (g.rows == 64) return bits(k_spadd3_bits<V, 64>, 64);
     }
     if (stage == 1) return go(k_spadd3_fill<V, 1>);
     if (stage == 2) return go(k_spadd3_fill<V, 2>);
     return go(k_spadd3_fill<V, 0>);
 }
 
-hipError_t launch_spadd3_numeric(int vtype, int64_t n, const int32_t *bp, const int32_t *bc,
+hipError_t launch_spadd3_numeric(int vtype, int64_t n, int64_t nnz_in, const int32_t *bp, const int32_t *bc,
                                  const void *bv, const int32_t *cp, const int32_t *cc,
                                  const void *cv, const int32_t *dp, const int32_t *dc,
                                  const void *dv, const int32_t *apos, int32_t *acrd, void *aval,
                                  int stage, hipStream_t s) {
     Csr3 m{bp, bc, cp, cc, dp, dc};
     if (n == 0) return hipSuccess;
-    if (vtype == SPL_F64) return spadd3_fill<double>(stage, n, m, bv, cv, dv, apos, acrd, aval, s);
-    return spadd3_fill<float>(stage, n, m, bv, cv, dv, apos, acrd, aval, s);
+    if (vtype == SPL_F64) return spadd3_fill<double>(stage, n, nnz_in, m, bv, cv, dv, apos, acrd, aval, s);
+    return spadd3_fill<float>(stage, n, nnz_in, m, bv, cv, dv, apos, acrd, aval, s);
 }
 
 }  // namespace spl

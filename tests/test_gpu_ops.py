@@ -834,3 +834,34 @@ def test_mttkrp_int64_positions_match_int32(dtype):
                 dict(kind="merge", variant=1)):
         with pytest.raises(spl.SpleafError, match="SPL_ERR_UNSUPPORTED"):
             spl.mttkrp(B64, C, D, sched=spl.schedule(**bad))
+
+
+# The staged count and fill: 128- and 64-row workgroups and their ragged last
+# ones, rows too long for the stage beside rows that fit it, mean rows that no
+# stage takes, empty operands, and more blocks than one add kernel sums by itself
+@pytest.mark.parametrize("n,m,deg,long", [
+    (1, 5, 2, ()), (127, 900, 3, ()), (128, 900, 8, ()), (129, 900, 8, ()), (1025, 900, 8, ()),
+    (300, 900, 30, ()), (65, 2000, 60, ()), (200, 3000, 400, ()), (700, 20000, 2, (0, 130, 699)),
+    (64, 300, 0, (63,)), (500, 40, 0, ()), (2_200_000, 50, 1, ())])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_spadd3_staged_shapes(n, m, deg, long, dtype):
+    spl = _spl()
+    rs = np.random.RandomState(n + deg)
+    print(f"spadd3 n={n} m={m} deg={deg} long={long} {dtype}", flush=True)
+    host, ops = [], []
+    for k in range(3):
+        d = np.minimum(rs.poisson(deg, n), m) if k or deg else np.zeros(n, np.int64)
+        d[list(long)] = m // (k + 1)
+        key = np.repeat(np.arange(n, dtype=np.int64), d) * m + rs.randint(0, m, d.sum())
+        key = np.unique(key)
+        pos = np.zeros(n + 1, np.int32)
+        np.cumsum(np.bincount(key // m, minlength=n), out=pos[1:])
+        crd, vals = (key % m).astype(np.int32), rs.uniform(-1, 1, key.size)
+        ops.append(spl.CSR(_t(pos), _t(crd), _t(vals, torch.float64).to(dtype), (n, m)))
+        host.append((pos, crd, host64(ops[-1].vals)))
+    rpos, rcrd, rvals, rS, _ = oracle.spadd3(*host)
+    A = spl.spadd3(*ops)
+    assert np.array_equal(A.pos.cpu().numpy(), rpos) and np.array_equal(A.crd.cpu().numpy(), rcrd)
+    assert_close(host64(A.vals), rvals, rS, RTOL[dtype], "spadd3 staged")
+    again = spl.spadd3(*ops, sched=spl.schedule("row", variant=1))
+    assert torch.equal(A.vals, again.vals) and torch.equal(A.crd, again.crd)
