@@ -406,8 +406,8 @@ spl_status spl_mttkrp(spl_context *ctx, const spl_sparse *B, const spl_dense *C,
  * too).  When B and C share one pattern (identical pos and crd pointers and
  * equal nnz) the aligned values are multiplied; otherwise the two patterns
  * are co-iterated (Sec. IV-C): each coordinate of B's last-but-one level is
- * looked up in C's segment of the same parent, and for CSF the two sorted
- * last-level lists are merged, so only coordinates both store contribute.
+ * looked up in C's segment of the same parent, and for CSF the entries of a
+ * fiber in the matching fiber, so only coordinates both store contribute.
  * Same dimensions required.  Values both F64 or both F32, summed in F64
  * with a fixed reduction order; the result is one double written to `out`
  * (device).  Either operand may be (Dense, Dense, Compressed): unless the

@@ -636,9 +636,8 @@ constexpr int64_t kInnerParts = 2048;
 // Workspace of an inner product with B as the first operand: the shared-
 // pattern partials or the general co-iteration's per-workgroup partials.
 size_t inner_ws(const spl_sparse *B) {
-    const int64_t units = B->order == 2 ? B->nnz : B->nfibers;
     return align_up(std::max(static_cast<size_t>(kInnerParts) * sizeof(double),
-                             spl::inner_general_ws(units)));
+                             spl::inner_general_ws(B->order, B->nnz)));
 }
 
 size_t spadd3_ws(int64_t n) {

@@ -1,27 +1,29 @@
 // Inner product of two sparse tensors with different patterns (the TIN
 // statement with no free index, Sec. II-A): a = sum over the coordinates
 // both store of B * C.  The co-iteration intersects the operands level by
-// level (the paper's coordinate-tree iteration, Sec. IV-C): a unit of work
-// is one stored coordinate of B's last-but-one level — a position of a CSR
-// matrix, a fiber of a CSF tensor — whose coordinate is looked up in C's
-// segment of the same parent by binary search; for a fiber the two sorted
-// last-level coordinate lists are then merged.
+// level (the paper's coordinate-tree iteration, Sec. IV-C): a coordinate of
+// B's last-but-one level — a position of a CSR matrix, a fiber of a CSF
+// tensor — is looked up in C's segment of the same parent by binary search;
+// the entries of a fiber are then looked up in the matching C fiber.
 //
-// A workgroup takes kUnitIters * 256 consecutive units, a lane every 256th.
-// The parent of each unit comes from the parent pos entries of the
-// workgroup's unit range, staged in LDS, and so do C's parent pos entries
-// and the C coordinates that can match: units are sorted by (parent,
-// coordinate), so the matches of the range lie between the first position
-// of C's first parent holding a coordinate at or past the range's first,
-// and the last position of C's last parent holding one at or below the
-// range's last.  The searches then run in LDS.  Those range bounds come from
-// a pre-pass (k_inner_bounds, a lane per workgroup boundary, all searching
-// at once) rather than from a serial search at the start of each workgroup.  When more than kParents
-// parents or kCStage C coordinates fall in the range, each lane searches
-// pos and crd in HBM instead.  Products are summed in double: each lane,
-// then a fixed tree over the workgroup into one partial per workgroup,
-// then a fixed-order final pass (k_inner_final), so the result does not
-// depend on timing.
+// CSR (k_inner_matrix): a workgroup takes kUnitIters * 256 consecutive
+// positions, a lane every 256th.  The parent of each comes from the parent
+// pos entries of the workgroup's range, staged in LDS, and so do C's parent
+// pos entries and the C coordinates that can match: positions are sorted by
+// (parent, coordinate), so the matches of the range lie between the first
+// position of C's first parent holding a coordinate at or past the range's
+// first, and the last position of C's last parent holding one at or below
+// the range's last.  The searches then run in LDS.  Those range bounds come
+// from a pre-pass (k_inner_bounds, a lane per workgroup boundary, all
+// searching at once) rather than from a serial search at the start of each
+// workgroup.  When more than kParents parents or kCStage C coordinates fall
+// in the range, each lane searches pos and crd in HBM instead.
+//
+// CSF (k_inner_fibers): see there.
+//
+// Products are summed in double: each lane, then a fixed tree over the
+// workgroup into one partial per workgroup, then a fixed-order final pass
+// (k_inner_final), so the result does not depend on timing.
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -31,7 +33,6 @@ namespace {
 constexpr int kParents = 1024;   // parents staged per workgroup
 constexpr int kCStage = 2560;    // C coordinates staged per workgroup
 constexpr int kUnitIters = 8;    // units per lane
-constexpr int kLockstep = 2;     // fibers a lane merges in lockstep
 
 // Largest r in [lo, hi) with pos[r] <= u (the parent holding unit u); I is
 // the index type (32-bit where the indices are LDS offsets, fewer VALU
@@ -109,40 +110,11 @@ __global__ __launch_bounds__(kBlock) void k_inner_bounds(int64_t n, int64_t unit
     bnd[4 * b + 3] = cb;
 }
 
-// 4-byte integer at byte offset `off` of a buffer (0 past its range); the
-// default cache policy, since neighbouring lanes' fibers share lines.
-__device__ __forceinline__ int32_t load_i32(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-    return static_cast<int32_t>(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-}
-// 4- or 8-byte value at byte offset `off` of a buffer (0 past its range).
-__device__ __forceinline__ float load_val(const float *, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-}
-__device__ __forceinline__ double load_val(const double *, __amdgpu_buffer_rsrc_t r,
-                                           uint32_t off) {
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
-    return __hiloint2double(static_cast<int>(w[1]), static_cast<int>(w[0]));
-}
-
-// BUF (CSF operands whose last-level arrays each fit a buffer descriptor's
-// range; nnzb, nnzc, cunits size them): the lane's fibers are merged
-// kLockstep at a time in lockstep, every step loading the next coordinates
-// and values of both at once (a lane with nothing to load reads 0 past the
-// descriptor's range, without a branch), so the lane's chain of dependent
-// loads is about half as long (0.956 -> 0.891 ms on the 1e8-nonzero tensor;
-// 4 at a time: 0.930, 8: slower still, as lanes load for fibers that have
-// ended; these loads keep the default cache policy, since neighbouring
-// lanes' fibers share lines: with the non-temporal hint, 1.08).  Without
-// BUF the fibers are merged one after another.
-template <typename V, int ORDER, bool BUF = false>
-__global__ __launch_bounds__(kBlock) void k_inner_general(
-    int64_t n, int64_t units, const int32_t *__restrict__ bpos, const int32_t *__restrict__ bcrd,
-    const int32_t *__restrict__ bpos2, const int32_t *__restrict__ bcrd2,
+template <typename V>
+__global__ __launch_bounds__(kBlock) void k_inner_matrix(
+    int64_t units, const int32_t *__restrict__ bpos, const int32_t *__restrict__ bcrd,
     const V *__restrict__ bv, const int32_t *__restrict__ cpos, const int32_t *__restrict__ ccrd,
-    const int32_t *__restrict__ cpos2, const int32_t *__restrict__ ccrd2,
-    const V *__restrict__ cv, const int64_t *__restrict__ bnd, double *__restrict__ part,
-    int64_t nnzb, int64_t nnzc, int64_t cunits) {
+    const V *__restrict__ cv, const int64_t *__restrict__ bnd, double *__restrict__ part) {
     __shared__ int32_t s_pos[kParents + 1];   // B's parent pos entries of the range
     __shared__ int32_t s_cpos[kParents + 1];  // C's
     __shared__ int32_t s_ccrd[kCStage];       // C's coordinates that can match
@@ -207,79 +179,6 @@ __global__ __launch_bounds__(kBlock) void k_inner_general(
     const int32_t cnt32 = static_cast<int32_t>(cnt);
     const int32_t c0s = static_cast<int32_t>(c0), c1s = static_cast<int32_t>(c1);
     int32_t rk = 0;  // staged parent index of the lane's previous unit (units ascend)
-    if constexpr (BUF && ORDER == 3) {
-        // the C fiber matching each of the lane's fibers (-1: none)
-        int32_t gq[kUnitIters];
-#pragma unroll
-        for (int it = 0; it < kUnitIters; ++it) {
-            const int64_t u64 = u0 + it * kBlock + threadIdx.x;
-            gq[it] = -1;
-            if (u64 >= u1) continue;
-            const int32_t u = static_cast<int32_t>(u64);
-            const int32_t j = jv[it];
-            if (staged) {
-                rk = parent_of<int32_t>([&](int32_t k) { return s_pos[k]; }, rk, cnt32, u);
-                const int32_t lo = s_cpos[rk] > c0s ? s_cpos[rk] : c0s;
-                const int32_t hi = s_cpos[rk + 1] < c1s ? s_cpos[rk + 1] : c1s;
-                const int32_t g =
-                    find_sorted<int32_t>([&](int32_t k) { return s_ccrd[k]; }, lo - c0s, hi - c0s, j);
-                gq[it] = g >= 0 ? g + c0s : -1;
-            } else {
-                const int64_t r = parent_of<int64_t>(gpos, r0, r0 + cnt, u);
-                gq[it] = static_cast<int32_t>(find_sorted<int64_t>(
-                    [&](int64_t k) { return ccrd[k]; }, cpos[r], cpos[r + 1], j));
-            }
-        }
-        const __amdgpu_buffer_rsrc_t rbp = span_rsrc(bpos2, 4u * static_cast<uint32_t>(units + 1));
-        const __amdgpu_buffer_rsrc_t rcp = span_rsrc(cpos2, 4u * static_cast<uint32_t>(cunits + 1));
-        const __amdgpu_buffer_rsrc_t rbc = span_rsrc(bcrd2, 4u * static_cast<uint32_t>(nnzb));
-        const __amdgpu_buffer_rsrc_t rcc = span_rsrc(ccrd2, 4u * static_cast<uint32_t>(nnzc));
-        const __amdgpu_buffer_rsrc_t rbv =
-            span_rsrc(bv, static_cast<uint32_t>(sizeof(V)) * static_cast<uint32_t>(nnzb));
-        const __amdgpu_buffer_rsrc_t rcv =
-            span_rsrc(cv, static_cast<uint32_t>(sizeof(V)) * static_cast<uint32_t>(nnzc));
-#pragma unroll
-        for (int g0 = 0; g0 < kUnitIters; g0 += kLockstep) {
-            // both fibers' position ranges of the group, all at once
-            int32_t p[kLockstep], pe[kLockstep], q[kLockstep], qe[kLockstep];
-#pragma unroll
-            for (int i = 0; i < kLockstep; ++i) {
-                const int it = g0 + i;
-                const int64_t u = u0 + it * kBlock + threadIdx.x;
-                const bool hit = gq[it] >= 0;
-                const uint32_t ob = hit ? 4u * static_cast<uint32_t>(u) : kBufOut;
-                const uint32_t oc = hit ? 4u * static_cast<uint32_t>(gq[it]) : kBufOut;
-                p[i] = load_i32(rbp, ob);
-                pe[i] = load_i32(rbp, ob + 4);
-                q[i] = load_i32(rcp, oc);
-                qe[i] = load_i32(rcp, oc + 4);
-            }
-            for (;;) {  // one merge step of every fiber of the group
-                int32_t kb[kLockstep], kc[kLockstep];
-                V vb[kLockstep], vc[kLockstep];
-                bool any = false;
-#pragma unroll
-                for (int i = 0; i < kLockstep; ++i) {
-                    const bool act = p[i] < pe[i] && q[i] < qe[i];
-                    any = any || act;
-                    const uint32_t ob = act ? 4u * static_cast<uint32_t>(p[i]) : kBufOut;
-                    const uint32_t oc = act ? 4u * static_cast<uint32_t>(q[i]) : kBufOut;
-                    kb[i] = load_i32(rbc, ob);
-                    kc[i] = load_i32(rcc, oc);
-                    vb[i] = load_val(bv, rbv, act ? static_cast<uint32_t>(sizeof(V)) * p[i] : kBufOut);
-                    vc[i] = load_val(cv, rcv, act ? static_cast<uint32_t>(sizeof(V)) * q[i] : kBufOut);
-                }
-                if (!any) break;
-#pragma unroll
-                for (int i = 0; i < kLockstep; ++i) {
-                    if (!(p[i] < pe[i] && q[i] < qe[i])) continue;
-                    if (kb[i] == kc[i]) acc += to_f64(vb[i]) * to_f64(vc[i]);
-                    p[i] += kb[i] <= kc[i] ? 1 : 0;
-                    q[i] += kc[i] <= kb[i] ? 1 : 0;
-                }
-            }
-        }
-    } else
 #pragma unroll
     for (int it = 0; it < kUnitIters; ++it) {
         const int64_t u64 = u0 + it * kBlock + threadIdx.x;
@@ -300,20 +199,7 @@ __global__ __launch_bounds__(kBlock) void k_inner_general(
                 find_sorted<int64_t>([&](int64_t k) { return ccrd[k]; }, cpos[r], cpos[r + 1], j));
         }
         if (g < 0) continue;
-        if (ORDER == 2) {
-            acc += to_f64(bv[u]) * to_f64(cv[g]);
-        } else {
-            int32_t p = bpos2[u], q = cpos2[g];
-            const int32_t pe = bpos2[u + 1], qe = cpos2[g + 1];
-            while (p < pe && q < qe) {
-                // values loaded with the coordinates (one round of loads a step)
-                const int32_t kb = bcrd2[p], kc = ccrd2[q];
-                const V vb = bv[p], vc = cv[q];
-                if (kb == kc) acc += to_f64(vb) * to_f64(vc);
-                p += kb <= kc ? 1 : 0;
-                q += kc <= kb ? 1 : 0;
-            }
-        }
+        acc += to_f64(bv[u]) * to_f64(cv[g]);
     }
     // fixed order: a butterfly in each wave, then the four wave sums in order
     acc = group_sum<kWave>(acc);
@@ -322,19 +208,367 @@ __global__ __launch_bounds__(kBlock) void k_inner_general(
     if (threadIdx.x == 0) part[blockIdx.x] = ((s_sum[0] + s_sum[1]) + s_sum[2]) + s_sum[3];
 }
 
-}  // namespace
+// ------------------------------------------------------------- CSF operands
+constexpr int kFiberBlock = 256;               // lanes per workgroup
+constexpr int kEntries = 4;                    // entries of B per lane
+constexpr int kFiberTile = kFiberBlock * kEntries;  // entries of B per workgroup
+constexpr int kTileParents = kFiberTile / 4;   // parents staged per workgroup
+constexpr int kTileC = kFiberTile * 5 / 4;     // C fibers, and C entries, staged
+constexpr int kProbe = 8;                     // lanes that search one bound together
 
-int64_t inner_general_parts(int64_t units) {
-    return ceil_div(units > 0 ? units : 1, kBlock * kUnitIters);
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t vi32x4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// First index of [lo, hi) at which `before` does not hold (hi: it holds at
+// all; it holds up to some index and at none past it), found by the kProbe
+// lanes of an aligned group together: each step leaves an eighth.
+template <typename Before>
+__device__ __forceinline__ uint32_t split_point(uint32_t lo, uint32_t hi, const Before &before) {
+    const uint32_t lane = threadIdx.x & (kProbe - 1);
+    const int first = threadIdx.x & (kWave - kProbe);  // the group's first lane of its wave
+    while (lo < hi) {
+        const uint32_t step = (hi - lo + kProbe - 1) / kProbe;
+        const uint32_t at = lo + step * lane + (step - 1);
+        const bool b = at < hi && before(at);
+        const uint32_t k = __popcll((__ballot(b) >> first) & ((1u << kProbe) - 1));
+        lo += step * k;
+        if (lo > hi) lo = hi;
+        if (lo + (step - 1) < hi) hi = lo + (step - 1);
+    }
+    return lo;
 }
 
-namespace {
+// Bounds of every tile of kFiberTile entries of B: what precedes its first
+// entry (the start, side 0) and what its last one reaches (the end, side 1),
+// as (parent, fiber, C fiber, C entry): the parent and the fiber that hold
+// the entry; the first C fiber of that parent at or past (start) or past
+// (end) the fiber's coordinate; and where that fiber or its predecessor
+// matches, the first of its entries at or past (past) the entry's
+// coordinate, else that C fiber's first entry.  bnd[2 * b] is the start of
+// tile b, bnd[2 * b + 1] the end of tile b - 1.
+// The chain of dependent loads bounds this pass (four searches, one after
+// another): kProbe lanes search together, which makes it a third as long as
+// a binary search's (19 us for 20,000 tiles of a 2e7-entry tensor; 16 lanes
+// 25).
+__global__ __launch_bounds__(kBlock) void k_fiber_bounds(
+    uint32_t n, uint32_t units, uint32_t nnzb, uint32_t parts, const int32_t *__restrict__ bpos,
+    const int32_t *__restrict__ bcrd, const int32_t *__restrict__ bpos2,
+    const int32_t *__restrict__ bcrd2, const int32_t *__restrict__ cpos,
+    const int32_t *__restrict__ ccrd, const int32_t *__restrict__ cpos2,
+    const int32_t *__restrict__ ccrd2, i32x4 *__restrict__ bnd) {
+    const uint32_t t = (blockIdx.x * kBlock + threadIdx.x) / kProbe;
+    const uint32_t b = t >> 1;
+    const bool end = t & 1;
+    if (b > parts || (end ? b == 0 : b == parts)) return;
+    const uint32_t past = b * kFiberTile < nnzb ? b * kFiberTile : nnzb;
+    const int32_t e = static_cast<int32_t>(end ? past - 1 : past);
+    const uint32_t u =
+        split_point(1, units, [&](uint32_t x) { return bpos2[x] <= e; }) - 1;
+    const int32_t iu = static_cast<int32_t>(u);
+    const uint32_t r = split_point(1, n, [&](uint32_t x) { return bpos[x] <= iu; }) - 1;
+    const int32_t j = bcrd[u], k = bcrd2[e];
+    const uint32_t lo = cpos[r], hi = cpos[r + 1];
+    const uint32_t c =
+        split_point(lo, hi, [&](uint32_t x) { return end ? ccrd[x] <= j : ccrd[x] < j; });
+    uint32_t q;
+    const uint32_t f = end ? c - 1 : c;  // the C fiber that may match
+    if ((end ? c > lo : c < hi) && ccrd[f] == j)
+        q = split_point(cpos2[f], cpos2[f + 1],
+                        [&](uint32_t x) { return end ? ccrd2[x] <= k : ccrd2[x] < k; });
+    else
+        q = cpos2[c];
+    if ((threadIdx.x & (kProbe - 1)) == 0) {
+        const i32x4 v = {static_cast<int32_t>(r), iu, static_cast<int32_t>(c),
+                         static_cast<int32_t>(q)};
+        bnd[t] = v;
+    }
+}
+
+// x[i]: the last index of [x[i], last[i]] whose read is at most key[i] (x[i]
+// itself if none is), N searches side by side so that their reads overlap.
+template <int N, typename Read>
+__device__ __forceinline__ void last_at_most(const Read &read, const int32_t (&key)[N],
+                                             int32_t (&x)[N], const int32_t (&last)[N]) {
+    int32_t far = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) far = last[i] - x[i] > far ? last[i] - x[i] : far;
+    for (int32_t step = far > 0 ? 1 << (31 - __clz(far)) : 0; step > 0; step >>= 1) {
+        int32_t y[N], v[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            y[i] = last[i] - x[i] > step ? x[i] + step : last[i];
+            v[i] = read(y[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) x[i] = v[i] <= key[i] ? y[i] : x[i];
+    }
+}
+
+// One workgroup per tile of kFiberTile consecutive entries of B (a fiber may
+// lie in several tiles), kEntries consecutive ones per lane.  B's parents of
+// the tile, and C's fibers and entries that can match (the tile's bounds are
+// clipped at both levels), are staged in LDS.  Then
+//  1. a lane per fiber of B finds the C fiber of its coordinate and notes it
+//     where the fiber's first entry of the tile stands;
+//  2. a running maximum over the tile's notes (they ascend) gives every
+//     entry its C fiber;
+//  3. every lane finds its entries' coordinates in their C fibers, and reads
+//     the values of those that match.
+// Everything but the matching values of C (whose lines neighbouring lanes
+// share) is read once at consecutive addresses, whatever the lengths of the
+// fibers; with a lane walking each pair of fibers in HBM the chain of
+// dependent loads bounded the kernel: 273 -> 156 us on 2e7 entries a tensor
+// in FP64, most fibers of one to five (0.7 GB, 4.5 TB/s of the 4.8 that a
+// large copy reaches), the whole call 1.66 -> 1.37 ms on 1e8 entries and
+// 33 -> 0.11 ms with 4,000 fibers of 2,200.  A lane's searches run side by
+// side (last_at_most): one after another, with a three-way compare, 166.
+// Tiles of 2,048 with 512 lanes or with 8 entries a lane: 179 and 190, though
+// the bounds and the final sum then take half.
+// What does not fit its stage (more parents than kTileParents; more C fibers
+// or entries than kTileC, neither of which is staged then) is searched in
+// HBM; a tile of more than 2 * kFiberTile fibers (most of them empty) finds
+// each entry's fiber by a search instead of 1 and 2.
+template <typename V>
+__global__ __launch_bounds__(kFiberBlock) void k_inner_fibers(
+    uint32_t nnzb, const int32_t *__restrict__ bpos, const int32_t *__restrict__ bcrd,
+    const int32_t *__restrict__ bpos2, const int32_t *__restrict__ bcrd2,
+    const V *__restrict__ bv, const int32_t *__restrict__ cpos, const int32_t *__restrict__ ccrd,
+    const int32_t *__restrict__ cpos2, const int32_t *__restrict__ ccrd2,
+    const V *__restrict__ cv, const i32x4 *__restrict__ bnd, double *__restrict__ part) {
+    __shared__ int32_t s_pos[kTileParents + 1];   // B's parent pos entries of the tile
+    __shared__ int32_t s_cpos[kTileParents + 1];  // C's
+    __shared__ int32_t s_cf[kTileC];              // C's fibers that can match
+    __shared__ uint16_t s_cq[kTileC + 1];         // their first entries, from the tile's first
+    __shared__ int32_t s_ck[kTileC];              // C's entries that can match
+    __shared__ __attribute__((aligned(16))) uint32_t s_note[kFiberTile];
+    __shared__ uint32_t s_top[kFiberBlock / kWave];
+    __shared__ double s_sum[kFiberBlock / kWave];
+    static_assert(kEntries % 4 == 0, "whole vectors of B");
+    const uint32_t p0 = blockIdx.x * kFiberTile;
+    const int np = static_cast<int>(nnzb - p0 < kFiberTile ? nnzb - p0 : kFiberTile);
+    const i32x4 a = bnd[2 * blockIdx.x], z = bnd[2 * blockIdx.x + 3];
+    const int32_t r0 = a.x, nr = z.x - a.x + 1, u0 = a.y, nu = z.y - a.y + 1;
+    const int32_t c0 = a.z, nc = z.z - a.z, q0 = a.w, nq = z.w - a.w;
+    if (nc <= 0 || nq <= 0) {  // no entry of C in the tile's range
+        if (threadIdx.x == 0) part[blockIdx.x] = 0.0;
+        return;
+    }
+    const bool sp = nr <= kTileParents, sc = nc <= kTileC && nq <= kTileC;
+    const bool by_fiber = nu <= 2 * kFiberTile;
+
+    // the lane's entries of B, four at a time except in a ragged last tile
+    const int e0 = threadIdx.x * kEntries;
+    int32_t k[kEntries];
+    V vb[kEntries];
+    if (np == kFiberTile) {
+#pragma unroll
+        for (int i = 0; i < kEntries; i += 4) {
+            const vi32x4 x = *reinterpret_cast<const vi32x4 *>(bcrd2 + p0 + e0 + i);
+            k[i] = x.x, k[i + 1] = x.y, k[i + 2] = x.z, k[i + 3] = x.w;
+        }
+#pragma unroll
+        for (int i = 0; i < kEntries; ++i)
+            vb[i] = load_stream(bv + p0 + i * kFiberBlock + threadIdx.x);
+    } else {
+#pragma unroll
+        for (int i = 0; i < kEntries; ++i) {
+            const int x = i * kFiberBlock + threadIdx.x;
+            k[i] = e0 + i < np ? bcrd2[p0 + e0 + i] : 0;
+            vb[i] = x < np ? bv[p0 + x] : V(0);
+        }
+    }
+    if (sp)
+        for (int i = threadIdx.x; i <= nr; i += kFiberBlock) {
+            s_pos[i] = bpos[r0 + i];
+            s_cpos[i] = cpos[r0 + i];
+        }
+    auto in_range = [&](int32_t q) {  // an entry of C from q0, clipped to the range
+        return q < q0 ? 0 : q - q0 < nq ? q - q0 : nq;
+    };
+    if (sc) {
+        // every lane issues all its loads before any store (past the range:
+        // 0, with no access)
+        constexpr int kPer = (kTileC + kFiberBlock) / kFiberBlock;
+        const __amdgpu_buffer_rsrc_t rf = span_rsrc(ccrd + c0, 4u * nc);
+        const __amdgpu_buffer_rsrc_t rq = span_rsrc(cpos2 + c0, 4u * (nc + 1));
+        const __amdgpu_buffer_rsrc_t rk = span_rsrc(ccrd2 + q0, 4u * nq);
+        uint32_t f[kPer], q[kPer], w[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int x = i * kFiberBlock + threadIdx.x;
+            f[i] = buf_u32(rf, x < nc ? 4u * x : kBufOut);
+            q[i] = buf_u32(rq, x <= nc ? 4u * x : kBufOut);
+            w[i] = buf_u32(rk, x < nq ? 4u * x : kBufOut);
+        }
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int x = i * kFiberBlock + threadIdx.x;
+            if (x < nc) s_cf[x] = static_cast<int32_t>(f[i]);
+            if (x <= nc) s_cq[x] = static_cast<uint16_t>(in_range(static_cast<int32_t>(q[i])));
+            if (x < nq) s_ck[x] = static_cast<int32_t>(w[i]);
+        }
+    }
+    // Fibers b + i * 256 + lane of the tile: their coordinates, and the
+    // tile's first entry of each (-1: it has none in the tile).
+    int32_t u[kEntries], j[kEntries], first[kEntries];
+    auto load_fibers = [&](int32_t b) {
+#pragma unroll
+        for (int i = 0; i < kEntries; ++i) {
+            const int32_t x = b + i * kFiberBlock + static_cast<int32_t>(threadIdx.x);
+            u[i] = u0 + (x < nu ? x : nu - 1);
+            j[i] = bcrd[u[i]];
+            const int64_t f = static_cast<int64_t>(bpos2[u[i]]) - p0;
+            const int64_t e = static_cast<int64_t>(bpos2[u[i] + 1]) - p0;
+            const int32_t at = f > 0 ? static_cast<int32_t>(f) : 0;
+            first[i] = x < nu && at < e && at < np ? at : -1;
+        }
+    };
+    if (by_fiber) load_fibers(0);
+#pragma unroll
+    for (int i = 0; i < kEntries; ++i) s_note[e0 + i] = 0;
+    __syncthreads();
+
+    // The notes of fibers u of coordinates j: 2 * g + 1, g the first C fiber
+    // of the parent, from c0, at or past j; one more if it matches.
+    auto match = [&](const int32_t (&u)[kEntries], const int32_t (&j)[kEntries],
+                     uint32_t (&out)[kEntries]) {
+        int32_t r[kEntries], x[kEntries], last[kEntries];
+#pragma unroll
+        for (int i = 0; i < kEntries; ++i) {
+            r[i] = 0;
+            last[i] = nr - 1;
+        }
+        if (sp)
+            last_at_most([&](int32_t y) { return s_pos[y]; }, u, r, last);
+        else
+            last_at_most([&](int32_t y) { return bpos[r0 + y]; }, u, r, last);
+        int32_t lo[kEntries];
+        bool any[kEntries];  // C fibers of the parent in the range
+#pragma unroll
+        for (int i = 0; i < kEntries; ++i) {
+            lo[i] = sp ? s_cpos[r[i]] : cpos[r0 + r[i]];
+            const int32_t hi = sp ? s_cpos[r[i] + 1] : cpos[r0 + r[i] + 1];
+            lo[i] = lo[i] < c0 ? 0 : lo[i] - c0 < nc ? lo[i] - c0 : nc;
+            last[i] = (hi < c0 ? 0 : hi - c0 < nc ? hi - c0 : nc) - 1;
+            any[i] = last[i] >= lo[i];
+            x[i] = any[i] ? lo[i] : 0;
+            last[i] = any[i] ? last[i] : 0;
+        }
+        if (sc)
+            last_at_most([&](int32_t y) { return s_cf[y]; }, j, x, last);
+        else
+            last_at_most([&](int32_t y) { return ccrd[c0 + y]; }, j, x, last);
+#pragma unroll
+        for (int i = 0; i < kEntries; ++i) {
+            const int32_t v = sc ? s_cf[x[i]] : ccrd[c0 + x[i]];
+            const int32_t g = any[i] ? x[i] + (v < j[i] ? 1 : 0) : lo[i];
+            out[i] = 2u * static_cast<uint32_t>(g) + 1u + (any[i] && v == j[i] ? 1u : 0u);
+        }
+    };
+    uint32_t note[kEntries];
+    if (by_fiber) {
+        for (int32_t b = 0; b < nu; b += kFiberTile) {
+            if (b > 0) load_fibers(b);
+            uint32_t w[kEntries];
+            match(u, j, w);
+#pragma unroll
+            for (int i = 0; i < kEntries; ++i)
+                if (first[i] >= 0) s_note[first[i]] = w[i];
+        }
+        __syncthreads();
+        // running maximum: in the lane, over the wave, over the waves
+        uint32_t top = 0;
+#pragma unroll
+        for (int i = 0; i < kEntries; ++i) {
+            note[i] = s_note[e0 + i];
+            top = note[i] > top ? note[i] : top;
+        }
+        const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const uint32_t o = __shfl_up(top, off);
+            top = lane >= off && o > top ? o : top;
+        }
+        if (lane == kWave - 1) s_top[threadIdx.x / kWave] = top;
+        uint32_t run = __shfl_up(top, 1);
+        if (lane == 0) run = 0;
+        __syncthreads();
+        for (int w = 0; w < static_cast<int>(threadIdx.x / kWave); ++w)
+            run = s_top[w] > run ? s_top[w] : run;
+#pragma unroll
+        for (int i = 0; i < kEntries; ++i) {
+            run = note[i] > run ? note[i] : run;
+            note[i] = run;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kEntries; ++i) {
+            // the last fiber that starts at or before the entry (past the
+            // tile: any)
+            const int32_t p = static_cast<int32_t>(p0 + (e0 + i < np ? e0 + i : np - 1));
+            u[i] = u0 + parent_of<int32_t>([&](int32_t x) { return bpos2[u0 + x]; }, 0, nu, p);
+            j[i] = bcrd[u[i]];
+        }
+        match(u, j, note);
+    }
+
+    // the entries' places in C from q0 (-1: none), handed through LDS to the
+    // lanes that read the values, each wave consecutive ones
+    int32_t x[kEntries], last[kEntries];
+    bool any[kEntries];
+#pragma unroll
+    for (int i = 0; i < kEntries; ++i) {
+        const uint32_t w = note[i] - 1u;
+        any[i] = e0 + i < np && (w & 1u);
+        const int32_t g = any[i] ? static_cast<int32_t>(w >> 1) : 0;
+        x[i] = sc ? s_cq[g] : in_range(cpos2[c0 + g]);
+        last[i] = (sc ? s_cq[g + 1] : in_range(cpos2[c0 + g + 1])) - 1;
+        any[i] = any[i] && x[i] <= last[i];
+        x[i] = any[i] ? x[i] : 0;
+        last[i] = any[i] ? last[i] : 0;
+    }
+    if (sc)
+        last_at_most([&](int32_t y) { return s_ck[y]; }, k, x, last);
+    else
+        last_at_most([&](int32_t y) { return ccrd2[q0 + y]; }, k, x, last);
+#pragma unroll
+    for (int i = 0; i < kEntries; ++i) {
+        const int32_t v = sc ? s_ck[x[i]] : ccrd2[q0 + x[i]];
+        s_note[e0 + i] = any[i] && v == k[i] ? static_cast<uint32_t>(x[i]) : ~0u;
+    }
+    __syncthreads();
+    int32_t at[kEntries];
+    V vc[kEntries];
+#pragma unroll
+    for (int i = 0; i < kEntries; ++i)
+        at[i] = static_cast<int32_t>(s_note[i * kFiberBlock + threadIdx.x]);
+#pragma unroll
+    for (int i = 0; i < kEntries; ++i) vc[i] = cv[q0 + (at[i] >= 0 ? at[i] : 0)];
+    double acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < kEntries; ++i)
+        if (at[i] >= 0) acc += to_f64(vb[i]) * to_f64(vc[i]);
+    // fixed order: a butterfly in each wave, then the wave sums in order
+    acc = group_sum<kWave>(acc);
+    if ((threadIdx.x & (kWave - 1)) == 0) s_sum[threadIdx.x / kWave] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kFiberBlock / kWave; ++w) acc += s_sum[w];
+        part[blockIdx.x] = acc;
+    }
+}
+
+int64_t inner_parts(int order, int64_t nnz) {
+    return ceil_div(nnz, order == 2 ? kBlock * kUnitIters : kFiberTile);
+}
 size_t part_bytes(int64_t parts) { return (static_cast<size_t>(parts) * 8 + 255) / 256 * 256; }
+
 }  // namespace
 
-size_t inner_general_ws(int64_t units) {
-    const int64_t parts = inner_general_parts(units);
-    return part_bytes(parts) + static_cast<size_t>(parts + 1) * 4 * sizeof(int64_t);
+size_t inner_general_ws(int order, int64_t nnz) {
+    // the partials, then 32 bytes of bounds per workgroup boundary
+    const int64_t parts = inner_parts(order, nnz > 0 ? nnz : 1);
+    return part_bytes(parts) + static_cast<size_t>(parts + 1) * 32;
 }
 
 hipError_t launch_inner_general(int vtype, int order, int64_t n, int64_t units,
@@ -343,39 +577,50 @@ hipError_t launch_inner_general(int vtype, int order, int64_t n, int64_t units,
                                 const int32_t *ccrd, const int32_t *cpos2, const int32_t *ccrd2,
                                 const void *cv, int64_t nnzb, int64_t nnzc, int64_t cunits,
                                 void *ws, double *out, hipStream_t s) {
-    const int64_t parts = inner_general_parts(units);
+    // Every entry of the first operand is read, and only the second's lines
+    // that can match, so the sparser tensor goes first (products commute
+    // exactly) unless the other one's fibers would no longer fit a tile's
+    // stage for it: 8e6 entries against half, a quarter, a 64th of them 68,
+    // 66, 59 us this way, 64, 52, 30 the other way, but against three
+    // quarters of them 70 and 83.
+    if (order == 3 && nnzb / 2 >= nnzc && nnzc > 0)
+        return launch_inner_general(vtype, order, n, cunits, cpos, ccrd, cpos2, ccrd2, cv, bpos,
+                                    bcrd, bpos2, bcrd2, bv, nnzc, nnzb, units, ws, out, s);
+    const bool none = nnzb <= 0 || nnzc <= 0;
+    const int64_t parts = none ? 0 : inner_parts(order, nnzb);
     double *part = static_cast<double *>(ws);
-    int64_t *bnd = reinterpret_cast<int64_t *>(static_cast<char *>(ws) + part_bytes(parts));
-    if (units > 0) {
-        k_inner_bounds<<<dim3(static_cast<unsigned>(ceil_div(parts + 1, kBlock))), kBlock, 0, s>>>(
-            n, units, kBlock * kUnitIters, parts, bpos, bcrd, cpos, ccrd, bnd);
-        dim3 grid(static_cast<unsigned>(parts));
-        auto go = [&](auto kern, auto *b, auto *c) {
-            kern<<<grid, kBlock, 0, s>>>(n, units, bpos, bcrd, bpos2, bcrd2, b, cpos, ccrd, cpos2,
-                                         ccrd2, c, bnd, part, nnzb, nnzc, cunits);
+    char *bounds = static_cast<char *>(ws) + part_bytes(parts);
+    if (!none) {
+        const dim3 grid(static_cast<unsigned>(parts));
+        auto go = [&](auto *b, auto *c) {
+            using V = std::remove_const_t<std::remove_pointer_t<decltype(b)>>;
+            if (order == 2) {
+                int64_t *bnd = reinterpret_cast<int64_t *>(bounds);
+                k_inner_bounds<<<dim3(static_cast<unsigned>(ceil_div(parts + 1, kBlock))), kBlock,
+                                 0, s>>>(n, nnzb, kBlock * kUnitIters, parts, bpos, bcrd, cpos,
+                                         ccrd, bnd);
+                k_inner_matrix<V><<<grid, kBlock, 0, s>>>(nnzb, bpos, bcrd, b, cpos, ccrd, c, bnd,
+                                                          part);
+            } else {
+                i32x4 *bnd = reinterpret_cast<i32x4 *>(bounds);
+                const int64_t lanes = (parts + 1) * 2 * kProbe;
+                k_fiber_bounds<<<dim3(static_cast<unsigned>(ceil_div(lanes, kBlock))), kBlock, 0,
+                                 s>>>(static_cast<uint32_t>(n), static_cast<uint32_t>(units),
+                                      static_cast<uint32_t>(nnzb), static_cast<uint32_t>(parts),
+                                      bpos, bcrd, bpos2, bcrd2, cpos, ccrd, cpos2, ccrd2, bnd);
+                k_inner_fibers<V><<<grid, kFiberBlock, 0, s>>>(static_cast<uint32_t>(nnzb), bpos, bcrd,
+                                                          bpos2, bcrd2, b, cpos, ccrd, cpos2,
+                                                          ccrd2, c, bnd, part);
+            }
         };
-        // the lockstep merge when every last-level array fits a descriptor
-        const size_t vb = vtype == SPL_F64 ? 8 : 4;
-        auto fits = [](int64_t count, size_t bytes) {
-            return count >= 0 && static_cast<uint64_t>(count) * bytes <= kBufRange;
-        };
-        const bool buf = order == 3 && fits(nnzb, vb) && fits(nnzc, vb) && fits(units + 1, 4) &&
-                         fits(cunits + 1, 4);
-        if (vtype == SPL_F64) {
-            const double *b = static_cast<const double *>(bv), *c = static_cast<const double *>(cv);
-            if (order == 2) go(k_inner_general<double, 2>, b, c);
-            else if (buf) go(k_inner_general<double, 3, true>, b, c);
-            else go(k_inner_general<double, 3>, b, c);
-        } else {
-            const float *b = static_cast<const float *>(bv), *c = static_cast<const float *>(cv);
-            if (order == 2) go(k_inner_general<float, 2>, b, c);
-            else if (buf) go(k_inner_general<float, 3, true>, b, c);
-            else go(k_inner_general<float, 3>, b, c);
-        }
+        if (vtype == SPL_F64)
+            go(static_cast<const double *>(bv), static_cast<const double *>(cv));
+        else
+            go(static_cast<const float *>(bv), static_cast<const float *>(cv));
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return launch_inner_final(units > 0 ? parts : 0, part, out, s);
+    return launch_inner_final(parts, part, out, s);
 }
 
 }  // namespace spl

@@ -149,12 +149,10 @@ hipError_t launch_inner(int vtype, int64_t nnz, const void *a, const void *b, do
 hipError_t launch_inner_final(int64_t nparts, const double *part, double *out, hipStream_t s);
 
 // ---- inner.hip -----------------------------------------------------------
-// Inner product of operands with different patterns (order 2: units are B's
-// positions, n rows; order 3: units are B's fibers, n slices); the workspace
-// `ws` holds inner_general_ws(units) bytes (per-workgroup partials and range
-// bounds).
-int64_t inner_general_parts(int64_t units);
-size_t inner_general_ws(int64_t units);
+// Inner product of operands with different patterns (n rows, or n slices,
+// `units` fibers of B and `cunits` of C); the workspace `ws` holds inner_general_ws(order, nnz
+// of B) bytes (per-workgroup partials and range bounds).
+size_t inner_general_ws(int order, int64_t nnz);
 hipError_t launch_inner_general(int vtype, int order, int64_t n, int64_t units,
                                 const int32_t *bpos, const int32_t *bcrd, const int32_t *bpos2,
                                 const int32_t *bcrd2, const void *bv, const int32_t *cpos,

@@ -624,6 +624,73 @@ def test_inner_general_staging_limits(dtype):
                      "inner general CSR staging, swapped")
 
 
+def _fibers_csf(slices, rs):
+    """(pos1, crd1, pos2, crd2, vals) of a list of slices, each a list of
+    (j, sorted k's) fibers, uniform[-1, 1] values."""
+    pos1 = np.cumsum([0] + [len(s) for s in slices]).astype(np.int32)
+    fibers = [f for s in slices for f in s]
+    crd1 = np.array([j for j, _ in fibers], np.int32)
+    pos2 = np.cumsum([0] + [len(k) for _, k in fibers]).astype(np.int32)
+    crd2 = np.concatenate([np.asarray(k, np.int32) for _, k in fibers] + [np.zeros(0, np.int32)])
+    return pos1, crd1, pos2, crd2, rs.uniform(-1, 1, len(crd2))
+
+
+def _inner_fiber_cases(rs):
+    def pick(m, count):
+        return np.sort(rs.choice(m, size=count, replace=False))
+
+    def random(n, fibers, entries, m=3000):
+        return [[(int(j), pick(m, rs.randint(1, entries + 1))) for j in pick(m, rs.randint(0, fibers))]
+                for _ in range(n)]
+
+    def thinned(slices):  # two entries in three, some fibers dropped
+        return [[(j, k[rs.rand(len(k)) < 0.67]) for j, k in s if rs.rand() < 0.8] for s in slices]
+
+    def exact(total):  # one slice of single-entry fibers, `total` entries
+        return [[(j, np.array([7])) for j in range(total)]]
+
+    m = 40_000
+    one = random(60, 100, 3)
+    long = [[(5, pick(m, 9000)), (9, np.array([m - 1]))], [], [(0, pick(m, 2000))]]
+    return {
+        "short_fibers": (one, thinned(one)),
+        "long_fibers": (long, [[(5, np.arange(m)), (9, np.arange(m))], [(2, pick(m, 5))],
+                               [(0, pick(m, 20000))]]),
+        "an_entry_per_slice": (random(3000, 3, 1), random(3000, 3, 2)),
+        "few_against_many": ([[(3, pick(3000, 4)), (2990, pick(3000, 9))]] * 3,
+                             random(1, 3, 1) + [[(j, pick(3000, 2)) for j in range(3000)]] * 2),
+        "empty_fibers": ([[(j, pick(50, 1) if j % 700 == 0 else pick(50, 0)) for j in range(6000)]],
+                         [[(j, pick(50, 10)) for j in range(0, 6000, 7)]]),
+        "tile": (exact(1024), exact(1023)),
+        "tile_and_one": (exact(1025), exact(2048)),
+        "one": (exact(1), exact(1)),
+        "nothing_in_range": (exact(2500), [[(2600, np.array([7]))]]),
+        "no_entries": (exact(5), [[]]),
+    }
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_inner_fiber_tiles(dtype):
+    """CSF operands of different patterns, where a tile of B's entries meets
+    one end of what it stages: fibers over several tiles, more slices, C
+    fibers, C entries or empty fibers than a tile holds, remainders."""
+    spl = _spl()
+    for name, (bs, cs) in _inner_fiber_cases(np.random.RandomState(71)).items():
+        n = max(len(bs), len(cs))
+        rs = np.random.RandomState(72)
+        hosts, ops = [], []
+        for s in (bs, cs):
+            h = _fibers_csf(list(s) + [[]] * (n - len(s)), rs)
+            T = spl.CSF(*(_t(x) for x in h[:4]), _t(h[4], torch.float64).to(dtype),
+                        (n, 40_000, 40_000))
+            ops.append(T)
+            hosts.append(h[:4] + (host64(T.vals),))
+        for x, y in ((0, 1), (1, 0)):
+            ref, S = oracle.inner(hosts[x], hosts[y])
+            assert_close(host64(spl.inner(ops[x], ops[y])), np.array([ref]), np.array([S]),
+                         RTOL[dtype], f"inner {name}")
+
+
 # ------------------------------------------- (Dense, Dense, Compressed) -----
 
 def _ddc(spl, c, dtype, vals_key="vals"):
