@@ -220,16 +220,36 @@ spl_status resolve_spmm(spl_context *ctx, const spl_sparse *B, int64_t N, const 
         // 278 us against 309, 16 columns 294 against 491; FP32, 1e5 rows: 8
         // columns 31.6 against 38.5)
         const int v = spl::spmm_vec_width(B->vtype);
-        if (p.kind == SPL_MERGE && s->variant == 0 && p.items <= 16 && B->pos_type == SPL_I32 && N >= v)
-            ct = 4 * v;
+        const bool vectors = p.kind == SPL_MERGE && s->variant == 0 && p.items <= 16 && N >= v;
+        if (vectors && B->pos_type == SPL_I32) ct = 4 * v;
         while (ct < 64 && ct < N) ct <<= 1;
+        // Vector lanes with nothing else asked for.  Groups of four lanes
+        // make chunks of 1,024 items, each group walking 16 of them one
+        // after another: with 8 a matrix that takes few rounds of
+        // workgroups takes less (8 columns, 4.4e6 items, 16 -> 8: FP64 36 ->
+        // 33 us, FP32 32 -> 29, BF16 34 -> 28; 2.2e7 items: 167 -> 169, 153
+        // -> 154, 158 -> 143, so only BF16 keeps it).  And up to 1,024
+        // workgroups (four a CU) of one chunk each, FP64's second chunk a
+        // workgroup only lengthens the call (1e4 rows of 10 entries, 4
+        // columns: 22 -> 16 us, 32 columns: 20 -> 16; 1.6e5 rows, 32
+        // columns, 6,900 workgroups: 75 and 76).  With columns in several
+        // blocks it can lose instead, since twice the carries cost the
+        // fix-up more (128 columns, one row of half the entries: 31 -> 33).
+        if (vectors && ct >= 4 * v && !s->items_per_lane && !s->tile) {
+            const int64_t merged = B->dims[0] + B->nnz;
+            if (ct == 4 * v && (B->vtype == SPL_BF16 || merged <= int64_t{1} << 23)) p.items = 8;
+            const int64_t chunk = 256 / (ct / v) * p.items;
+            if (N <= ct && (merged + chunk - 1) / chunk <= 1024)
+                p.tile = std::min<int64_t>(chunk, 4 * (256 / ct) * p.items);
+        }
     }
     if (ct != 8 && ct != 16 && ct != 32 && ct != 64)
         return fail(ctx, SPL_ERR_ARG, "col_tile must be 8, 16, 32 or 64");
     p.col_tile = ct;
     if (p.items != 8 && p.items != 16 && p.items != 32)
         return fail(ctx, SPL_ERR_ARG, "SpMM items_per_lane must be 8, 16 or 32");
-    p.tile = s->tile ? s->tile : (p.kind == SPL_ROW ? 256 / ct : 4 * (256 / ct) * p.items);
+    if (s->tile || !p.tile)
+        p.tile = s->tile ? s->tile : (p.kind == SPL_ROW ? 256 / ct : 4 * (256 / ct) * p.items);
     if (p.tile < 1) return fail(ctx, SPL_ERR_ARG, "tile must be positive");
     if (s->variant < 0 || s->variant > 2)
         return fail(ctx, SPL_ERR_ARG,

@@ -476,3 +476,27 @@ def test_spmm_ragged_columns(dtype, N):
                     assert np.array_equal(host64(A), ref), sc
                 else:
                     assert_close(host64(A), ref, S, RTOL[dtype], f"{dtype} N={N} {sc}")
+
+
+# The default schedule's rules on the number of merged items: one chunk a
+# workgroup up to 1,024 workgroups (FP64: 20,000 rows below, 21,000 above), and
+# 8 items for groups of four lanes up to 2^23 (320,000 and 330,000 rows).
+# Small integers: the sums are exact.
+@pytest.mark.parametrize("rows", [1, 300, 20_000, 21_000, 320_000, 330_000])
+@pytest.mark.parametrize("dtype,N", [(torch.float64, 4), (torch.float64, 33), (torch.float64, 65),
+                                     (torch.float32, 16), (torch.bfloat16, 24)])
+def test_spmm_default_by_size(dtype, N, rows):
+    spl = _spl()
+    g = torch.Generator(device=dev())
+    g.manual_seed(rows)
+    deg, m = 25, 5000
+    crd = torch.randint(0, m // deg, (rows, deg), generator=g, device=dev())
+    crd += torch.arange(deg, device=dev()) * (m // deg)
+    pos = torch.arange(rows + 1, device=dev(), dtype=torch.int32) * deg
+    vals = torch.randint(-3, 4, (rows * deg,), generator=g, device=dev()).to(dtype)
+    C = torch.randint(-3, 4, (m, N), generator=g, device=dev()).to(dtype)
+    B = spl.CSR(pos, crd.reshape(-1).to(torch.int32), vals, (rows, m))
+    ref = torch.zeros(rows, N, dtype=torch.float64, device=dev())
+    for k in range(deg):
+        ref += vals.reshape(rows, deg)[:, k, None].double() * C[crd[:, k]].double()
+    assert torch.equal(spl.spmm(B, C).double(), ref)
