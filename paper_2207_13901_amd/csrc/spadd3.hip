@@ -654,16 +654,25 @@ __global__ __launch_bounds__(kBlock) void k_scan_tile_prefix(int64_t ntiles, int
 // with window bounds the values are the window lengths instead of x).  The
 // tile goes through LDS so that the loads and stores are coalesced; each
 // thread scans 16 consecutive elements there (padded: element e at
-// e + e / 16, so the threads' runs fall in different banks).
+// e + e / 16, so the threads' runs fall in different banks).  `own`: the tile
+// sums are as counted, and every workgroup adds up those before its own; the
+// last one writes the total.
 __global__ __launch_bounds__(kBlock) void k_scan_tile_apply(int64_t n, int32_t *x,
                                                             const int32_t *begin,
                                                             const int32_t *end,
-                                                            const int64_t *tile_sum,
-                                                            int32_t *head) {
+                                                            const int64_t *tile_sum, bool own,
+                                                            int64_t *total, int32_t *head) {
     if (head && blockIdx.x == 0 && threadIdx.x == 0) *head = 0;  // the leading 0 of a pos array
     constexpr int kPad = kScanTile + kScanTile / kScanItems;
     __shared__ int64_t s_v[kPad];
     __shared__ int64_t s[kBlock];
+    __shared__ int64_t s_first[kBlock / kWave];
+    if (own) {
+        int64_t before = 0;
+        for (int64_t t = threadIdx.x; t < blockIdx.x; t += kBlock) before += tile_sum[t];
+        before = group_sum<kWave>(before);
+        if (threadIdx.x % kWave == 0) s_first[threadIdx.x / kWave] = before;
+    }
     const int64_t base = static_cast<int64_t>(blockIdx.x) * kScanTile;
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) {
@@ -688,7 +697,10 @@ __global__ __launch_bounds__(kBlock) void k_scan_tile_apply(int64_t n, int32_t *
         s[threadIdx.x] += add;
         __syncthreads();
     }
-    const int64_t before = tile_sum[blockIdx.x] + s[threadIdx.x] - run;
+    int64_t first = own ? 0 : tile_sum[blockIdx.x];
+    for (int w = 0; own && w < kBlock / kWave; ++w) first += s_first[w];
+    if (own && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = first + s[kBlock - 1];
+    const int64_t before = first + s[threadIdx.x] - run;
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) s_v[p0 + j] += before;
     __syncthreads();
@@ -704,34 +716,39 @@ __global__ __launch_bounds__(kBlock) void k_scan_tile_apply(int64_t n, int32_t *
 
 int64_t spadd3_scan_tiles(int64_t n) { return ceil_div(n > 0 ? n : 1, kScanTile); }
 
-hipError_t launch_window_offsets(int64_t n, const int32_t *begin, const int32_t *end,
-                                 int32_t *vpos, int64_t *tile_sum, int64_t *total, hipStream_t s) {
-    // vpos[0] = 0 and vpos[1..n] the inclusive scan of the window lengths
+// The inclusive scan of n values into out[1..n], out[0] = 0.  Up to kOwnTiles
+// tiles the workgroups of the last step add up the sums before theirs by
+// themselves (16 loads a lane at most): a launch of one workgroup and its
+// gap less (1e6 values: 18 -> 14 us).
+constexpr int64_t kOwnTiles = 16 * kBlock;
+
+static hipError_t launch_scan(int64_t n, const int32_t *x, const int32_t *begin,
+                              const int32_t *end, int32_t *out, int64_t *tile_sum,
+                              int64_t *total, hipStream_t s) {
     const int64_t nt = spadd3_scan_tiles(n);
-    k_scan_tile_sums<<<dim3(static_cast<unsigned>(nt)), kBlock, 0, s>>>(n, nullptr, begin, end,
-                                                                        tile_sum);
+    const dim3 grid(static_cast<unsigned>(nt));
+    const bool own = nt <= kOwnTiles;
+    k_scan_tile_sums<<<grid, kBlock, 0, s>>>(n, x, begin, end, tile_sum);
     hipError_t e;
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_scan_tile_prefix<<<1, kBlock, 0, s>>>(nt, tile_sum, total);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_scan_tile_apply<<<dim3(static_cast<unsigned>(nt)), kBlock, 0, s>>>(n, vpos + 1, begin, end,
-                                                                         tile_sum, vpos);
+    if (!own) {
+        k_scan_tile_prefix<<<1, kBlock, 0, s>>>(nt, tile_sum, total);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    k_scan_tile_apply<<<grid, kBlock, 0, s>>>(n, out + 1, begin, end, tile_sum, own, total, out);
     return hipGetLastError();
+}
+
+hipError_t launch_window_offsets(int64_t n, const int32_t *begin, const int32_t *end,
+                                 int32_t *vpos, int64_t *tile_sum, int64_t *total, hipStream_t s) {
+    return launch_scan(n, nullptr, begin, end, vpos, tile_sum, total, s);
 }
 
 hipError_t launch_pos_scan(int64_t n, int32_t *apos, int64_t *tile_sum, int64_t *total,
                            hipStream_t s, hipEvent_t counted) {
-    // apos[1..n] hold counts: scanned in place, apos[0] = 0
-    const int64_t nt = spadd3_scan_tiles(n);
-    k_scan_tile_sums<<<dim3(static_cast<unsigned>(nt)), kBlock, 0, s>>>(n, apos + 1, nullptr,
-                                                                        nullptr, tile_sum);
-    hipError_t e;
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_scan_tile_prefix<<<1, kBlock, 0, s>>>(nt, tile_sum, total);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_scan_tile_apply<<<dim3(static_cast<unsigned>(nt)), kBlock, 0, s>>>(n, apos + 1, nullptr,
-                                                                         nullptr, tile_sum, apos);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // apos[1..n] hold counts: scanned in place
+    const hipError_t e = launch_scan(n, apos + 1, nullptr, nullptr, apos, tile_sum, total, s);
+    if (e != hipSuccess) return e;
     return counted ? hipEventRecord(counted, s) : hipSuccess;
 }
 

@@ -149,3 +149,24 @@ def test_tin_csr_outputs_staged_and_direct_rows(n, m, deg, long, stmt, dtype):
     assert np.array_equal(A.pos.cpu().numpy(), pos)
     assert np.array_equal(A.crd.cpu().numpy(), mask.nonzero()[:, 1].numpy())
     assert_close(host64(A.vals), want[mask].numpy(), S[mask].numpy(), RTOL[dtype], stmt)
+
+
+# The scan of the row counts: one tile, a remainder, and either side of the
+# tiles whose sums the last step adds up by itself.
+@pytest.mark.parametrize("n", [1, 4096, 4097, 4096 * 4096, 4096 * 4096 + 1])
+def test_csr_output_positions(n):
+    spl, dev = _spl(), torch.device("cuda")
+    g = torch.Generator(device=dev)
+    g.manual_seed(n % 1000)
+    m = 50
+    keys = [torch.unique(torch.randint(0, n * m, (3000,), generator=g, device=dev)) for _ in range(2)]
+    rows = torch.arange(n + 1, device=dev) * m
+
+    def csr(k):
+        return spl.CSR(torch.searchsorted(k, rows).to(torch.int32), (k % m).to(torch.int32),
+                       torch.ones(k.numel(), dtype=torch.float64, device=dev), (n, m))
+
+    A = spl.tin("A(i,j) = B(i,j) - C(i,j)", shape=(n, m), B=csr(keys[0]), C=csr(keys[1]))
+    union = torch.unique(torch.cat(keys))
+    assert torch.equal(A.pos, torch.searchsorted(union, rows).to(torch.int32))
+    assert torch.equal(A.crd, (union % m).to(torch.int32))
