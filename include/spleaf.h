@@ -268,7 +268,9 @@ spl_status spl_probe(spl_context *ctx, int kind, const void *buf, int64_t bytes,
  * 2 = each lane sums whole rows of the chunk from its staged products (rows
  * of more than 32 positions in the chunk by a wave each), the open row by
  * the workgroup -- for short rows such as CSF fibers (int32 positions only).
- * Kinds
+ * With no field set, a matrix of at most 1,048,576 rows and positions
+ * whose rows can hold at most 32,768 runs as one launch that needs no
+ * workspace (the query's size still holds for one that is passed).  Kinds
  * SPL_SCHED_LEARNED / SPL_SCHED_AUTOTUNE are resolved first to one of the
  * candidates (which synchronizes on
  * `stream`; a caller workspace must then fit every candidate, as

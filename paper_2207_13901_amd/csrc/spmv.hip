@@ -30,7 +30,7 @@
 //  * k_spmv_pipe (schedule variant 1): the merge-split form of
 //    k_spmv_tiles with its staging software-pipelined two chunks deep.
 //
-//  * k_spmv_flag (merge split, default): the same pipeline with the row
+//  * k_spmv_flag (merge split, tiles of several chunks): the same pipeline with the row
 //    ends staged as flags in the merged sequence, so that no lane searches
 //    or reads row ends (see below).
 //
@@ -520,8 +520,8 @@ __device__ __forceinline__ void flag_walk(Flags fl, int d0, int steps, int nr, d
     }
 }
 
-// Merge-split leaf with row-end flags (the default; k_spmv_pipe is schedule
-// variant 1).  The same pieces, pipeline and carries as k_spmv_pipe, but
+// Merge-split leaf with row-end flags, for tiles of several chunks
+// (k_spmv_pipe is schedule variant 1).  The same pieces, pipeline and carries as k_spmv_pipe, but
 // instead of the row ends
 // the staging writes a flag byte at each row end's place in the chunk's
 // merged sequence (row end r of the chunk sits at r + pos[r+1] - chunk
