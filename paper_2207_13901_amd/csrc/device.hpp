@@ -277,6 +277,42 @@ __device__ __forceinline__ int64_t merge_search(int64_t d, int64_t nr, int64_t n
     return lo;
 }
 
+// Rows that end before merged item d of the rows' ends and positions (row i
+// ends at item i + pos[i + 1]), found by one wave, 64 probes a step.
+template <typename P>
+__device__ __forceinline__ int64_t wave_merge_row(const P *__restrict__ pos, int64_t rows, int64_t d) {
+    const int lane = threadIdx.x & (kWave - 1);
+    int64_t lo = -1, hi = rows;  // row lo ends before d (or lo == -1); row hi does not (or hi == rows)
+    while (hi - lo > 1) {
+        const int64_t step = (hi - lo + kWave - 1) / kWave;
+        const int64_t at = lo + (lane + 1) * step;
+        const bool before = at < hi && at + static_cast<int64_t>(pos[at + 1]) < d;
+        const int k = __popcll(__ballot(before));
+        hi = lo + (k + 1) * step < hi ? lo + (k + 1) * step : hi;
+        lo += k * step;
+    }
+    return hi;
+}
+
+// The bounds of the chunk of merged items [d0, d1): rows and positions before
+// it and up to its end, by the workgroup's first two waves.  For leaves that
+// find their own chunks: with few workgroups the launch of a partition kernel
+// costs more than a search in each of them.
+struct ChunkBounds {
+    int64_t ci, cp, ei, ep;
+};
+template <typename P>
+__device__ __forceinline__ ChunkBounds own_bounds(const P *__restrict__ pos, int64_t rows, int64_t d0,
+                                                  int64_t d1, int64_t *s_row) {
+    const int wave = threadIdx.x / kWave;
+    if (wave < 2) {
+        const int64_t i = wave_merge_row(pos, rows, wave == 0 ? d0 : d1);
+        if (threadIdx.x % kWave == 0) s_row[wave] = i;
+    }
+    __syncthreads();
+    return {s_row[0], d0 - s_row[0], s_row[1], d1 - s_row[1]};
+}
+
 __host__ __device__ __forceinline__ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // End of the next chunk of a leaf workgroup walking the merged sequence of

@@ -21,6 +21,9 @@ struct Tiles {
     int32_t *pos;
     int64_t ntiles;
     int64_t *pos64 = nullptr;  // in place of pos when the positions are int64
+    // rows + positions when the leaf finds its chunks by itself (no bounds are
+    // computed before it; SpMM's leaf writes row[1..]), else 0
+    int64_t own = 0;
 };
 
 // ---- partition.hip -------------------------------------------------------
@@ -167,7 +170,7 @@ int sddmm_vec_width(int ftype);
 // vec_lanes (variant 0): 0 = one element per lane access; 4, 8, 16 or 32 =
 // lanes per position reading sddmm_vec_width(ftype) elements each (K at
 // least that).
-hipError_t launch_sddmm(int vtype, int ftype, int variant, int vec_lanes, int64_t K,
+hipError_t launch_sddmm(int vtype, int ftype, int variant, int vec_lanes, int64_t rows, int64_t K,
                         const int32_t *pos, const int32_t *crd, const void *bv, const void *C,
                         int64_t ldc, const void *D, int64_t ldd, void *out, const Tiles &t,
                         int64_t stride, hipStream_t s);

@@ -113,9 +113,12 @@ __global__ __launch_bounds__(kBlock) void k_sddmm_valu(
 // 0.33 in BF16 (7.2 TB/s of D and C rows); with the coordinates read, and the
 // values read and results stored by one lane per group, inside the loop 0.85
 // and 0.42.  K = 100, BF16: 0.39 ms, 0.85 with one element per lane.
+//
+// own (rows + positions, else 0): workgroups of one chunk that find its bounds
+// by themselves.
 template <typename V, typename FT, typename Acc, int CHUNK, int L, int VEC, int P, bool RAG>
 __global__ __launch_bounds__(kBlock) void k_sddmm_vec(
-    int64_t K, const int32_t *__restrict__ pos, const int32_t *__restrict__ crd,
+    int64_t rows, int64_t own, int64_t K, const int32_t *__restrict__ pos, const int32_t *__restrict__ crd,
     const V *__restrict__ bv, const FT *__restrict__ C, int64_t ldc, const FT *__restrict__ D,
     int64_t ldd, V *__restrict__ out, const int32_t *__restrict__ trow,
     const int32_t *__restrict__ tpos, int64_t npieces, int64_t stride) {
@@ -130,10 +133,22 @@ __global__ __launch_bounds__(kBlock) void k_sddmm_vec(
     const int tid = threadIdx.x, grp = tid / L, lane = tid % L;
     int64_t piece = static_cast<int64_t>(blockIdx.x) * stride;
     const int64_t piece_end = piece + stride < npieces ? piece + stride : npieces;
-    int64_t ci = trow[piece], cp = tpos[piece];
+    int64_t ci, cp, ei, ep;
+    if (own) {
+        const int64_t d0 = piece * CHUNK, d1 = d0 + CHUNK < own ? d0 + CHUNK : own;
+        const ChunkBounds b = own_bounds(pos, rows, d0, d1, s_next);
+        ci = b.ci, cp = b.cp, ei = b.ei, ep = b.ep;
+    } else {
+        ci = trow[piece];
+        cp = tpos[piece];
+    }
     while (piece < piece_end) {
+        int64_t next = piece + 1;
+        if (!own) {
+            ei = trow[piece + 1];
+            ep = tpos[piece + 1];
+        }
         // a piece that ends within this chunk needs no search
-        int64_t ei = trow[piece + 1], ep = tpos[piece + 1], next = piece + 1;
         if (ei + ep - ci - cp > CHUNK) {
             next = chunk_end(pos, trow, tpos, piece, ci, cp, CHUNK, s_next);
             ei = s_next[0];
@@ -261,11 +276,11 @@ int sddmm_vec_width(int ftype) { return ftype == SPL_F64 ? 2 : ftype == SPL_F32 
 
 namespace {
 template <typename V, typename FT, int VEC>
-hipError_t sddmm_vec(int lanes, dim3 grid, int64_t K, const int32_t *pos, const int32_t *crd,
+hipError_t sddmm_vec(int lanes, dim3 grid, int64_t rows, int64_t K, const int32_t *pos, const int32_t *crd,
                      const void *bv, const void *C, int64_t ldc, const void *D, int64_t ldd,
                      void *out, const Tiles &t, int64_t stride, hipStream_t s) {
     auto go = [&](auto kern) {
-        kern<<<grid, kBlock, 0, s>>>(K, pos, crd, static_cast<const V *>(bv),
+        kern<<<grid, kBlock, 0, s>>>(rows, t.own, K, pos, crd, static_cast<const V *>(bv),
                                      static_cast<const FT *>(C), ldc, static_cast<const FT *>(D),
                                      ldd, static_cast<V *>(out), t.row, t.pos, t.ntiles, stride);
         return hipGetLastError();
@@ -287,19 +302,19 @@ hipError_t sddmm_vec(int lanes, dim3 grid, int64_t K, const int32_t *pos, const 
 }
 }  // namespace
 
-hipError_t launch_sddmm(int vtype, int ftype, int variant, int vec_lanes, int64_t K,
+hipError_t launch_sddmm(int vtype, int ftype, int variant, int vec_lanes, int64_t rows, int64_t K,
                         const int32_t *pos, const int32_t *crd, const void *bv, const void *C,
                         int64_t ldc, const void *D, int64_t ldd, void *out, const Tiles &t,
                         int64_t stride, hipStream_t s) {
     dim3 grid(static_cast<unsigned>(ceil_div(t.ntiles, stride)));
     if (variant == 0 && vec_lanes > 0) {
         if (ftype == SPL_BF16)
-            return sddmm_vec<float, bf16, 8>(vec_lanes, grid, K, pos, crd, bv, C, ldc, D, ldd,
+            return sddmm_vec<float, bf16, 8>(vec_lanes, grid, rows, K, pos, crd, bv, C, ldc, D, ldd,
                                              out, t, stride, s);
         if (vtype == SPL_F64)
-            return sddmm_vec<double, double, 2>(vec_lanes, grid, K, pos, crd, bv, C, ldc, D, ldd,
+            return sddmm_vec<double, double, 2>(vec_lanes, grid, rows, K, pos, crd, bv, C, ldc, D, ldd,
                                                 out, t, stride, s);
-        return sddmm_vec<float, float, 4>(vec_lanes, grid, K, pos, crd, bv, C, ldc, D, ldd, out,
+        return sddmm_vec<float, float, 4>(vec_lanes, grid, rows, K, pos, crd, bv, C, ldc, D, ldd, out,
                                           t, stride, s);
     }
     if (ftype == SPL_BF16 && variant == 1) {

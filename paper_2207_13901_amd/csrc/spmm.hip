@@ -188,15 +188,19 @@ __global__ __launch_bounds__(kBlock) void k_spmm_tiles(
 // one iteration earlier still.  After the walk they are stored to the other
 // LDS buffer, so the loads of the next chunk never sit on the critical path.
 // The walk, the cross-group pass and the carries are those of k_spmm_tiles.
+// OWN: workgroups of one chunk of the `own` merged items, which find its bounds
+// by themselves instead of reading them from a partition kernel (a form of its
+// own: decided at run time, the FP32 kernel took 135 registers instead of 123
+// and a wave less per SIMD).
 // With int64 positions (PosT) the row ends are staged relative to the
 // chunk's first position (they lie in [0, chunk]), so the walk and the
 // searches stay 32-bit; int32 positions are staged as they are.
 template <int W, int ITEMS, int VEC, typename V, typename BT, typename OT, typename Acc,
-          typename PosT = int32_t, bool BUF = false>
+          typename PosT = int32_t, bool BUF = false, bool OWN = false>
 __global__ __launch_bounds__(kBlock) void k_spmm_pipe(
     int64_t n, int64_t N, const PosT *__restrict__ pos, const int32_t *__restrict__ crd,
     const V *__restrict__ vals, const BT *__restrict__ Bd, int64_t ldb, OT *__restrict__ Out,
-    int64_t ldo, const int32_t *__restrict__ trow, const PosT *__restrict__ tpos,
+    int64_t ldo, int32_t *__restrict__ trow, const PosT *__restrict__ tpos, int64_t own,
     int64_t npieces, int64_t stride, Acc *__restrict__ carry) {
     constexpr int G = kBlock / W;
     constexpr int kChunk = G * ITEMS;
@@ -226,8 +230,12 @@ __global__ __launch_bounds__(kBlock) void k_spmm_pipe(
     const int64_t col0 = lane_col<VEC>(vlane, N);
     const int64_t p0 = static_cast<int64_t>(blockIdx.x) * stride;
     const int64_t pend = p0 + stride < npieces ? p0 + stride : npieces;
-    auto bound_i = [&](int64_t c) { return static_cast<int64_t>(trow[c < pend ? c : pend]); };
-    auto bound_p = [&](int64_t c) { return static_cast<int64_t>(tpos[c < pend ? c : pend]); };
+    auto bound_i = [&](int64_t c) {
+        return OWN ? 0 : static_cast<int64_t>(trow[c < pend ? c : pend]);
+    };
+    auto bound_p = [&](int64_t c) {
+        return OWN ? 0 : static_cast<int64_t>(tpos[c < pend ? c : pend]);
+    };
 
     int r_end[kPer], r_crd[kPer];
     Acc r_val[kPer];
@@ -265,6 +273,13 @@ __global__ __launch_bounds__(kBlock) void k_spmm_pipe(
     int64_t ci = bound_i(p0), cp = bound_p(p0);
     int64_t ei = bound_i(p0 + 1), ep = bound_p(p0 + 1);
     int64_t ni = bound_i(p0 + 2), np2 = bound_p(p0 + 2);
+    if constexpr (OWN) {  // the fix-up reads the row open at its end
+        __shared__ int64_t s_row[2];
+        const int64_t d0 = p0 * kChunk, d1 = d0 + kChunk < own ? d0 + kChunk : own;
+        const ChunkBounds b = own_bounds(pos, n, d0, d1, s_row);
+        ci = b.ci, cp = b.cp, ei = b.ei, ep = b.ep;
+        if (tid == 0 && blockIdx.y == 0) trow[p0 + 1] = static_cast<int32_t>(ei);
+    }
     int nr = static_cast<int>(ei - ci), np = static_cast<int>(ep - cp);
     fetch(ci, cp, nr, np);
     stash(0, nr, np);
@@ -272,7 +287,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_pipe(
     int buf = 0;
     for (int64_t c = p0; c < pend; ++c) {
         __syncthreads();  // buffer `buf` holds chunk c; the previous pass is done
-        const bool more = c + 1 < pend;
+        const bool more = !OWN && c + 1 < pend;
         const int nnr = static_cast<int>(ni - ei), nnp = static_cast<int>(np2 - ep);
         const int64_t fi = bound_i(c + 3), fp = bound_p(c + 3);  // for the next iteration
         if (more) fetch(ei, ep, nnr, nnp);
@@ -448,17 +463,25 @@ struct SpmmTypes {
                                        : k_spmm_pipe<W, ITEMS, VEC, V, BT, OT, Acc, int64_t, false>;
             kern<<<grid, kBlock, 0, s>>>(
                 n, N, pos, crd, static_cast<const V *>(vals), static_cast<const BT *>(Bd), ldb,
-                static_cast<OT *>(Out), ldo, t.row, t.pos64, t.ntiles, stride,
+                static_cast<OT *>(Out), ldo, t.row, t.pos64, t.own, t.ntiles, stride,
                 static_cast<Acc *>(carry));
         } else {
             // pieces of exactly one chunk (merge split): the pipelined leaf
-            auto kern = !exact ? k_spmm_tiles<W, ITEMS, V, BT, OT, Acc>
+            if (!exact) {
+                k_spmm_tiles<W, ITEMS, V, BT, OT, Acc><<<grid, kBlock, 0, s>>>(
+                    n, N, pos, crd, static_cast<const V *>(vals), static_cast<const BT *>(Bd), ldb,
+                    static_cast<OT *>(Out), ldo, t.row, t.pos, t.ntiles, stride,
+                    static_cast<Acc *>(carry));
+                return hipGetLastError();
+            }
+            if (t.own && !(buf && kCanBuf)) return hipErrorInvalidValue;
+            auto kern = t.own ? k_spmm_pipe<W, ITEMS, VEC, V, BT, OT, Acc, int32_t, kCanBuf, kCanBuf>
                         : buf && kCanBuf
                             ? k_spmm_pipe<W, ITEMS, VEC, V, BT, OT, Acc, int32_t, kCanBuf>
                             : k_spmm_pipe<W, ITEMS, VEC, V, BT, OT, Acc, int32_t, false>;
             kern<<<grid, kBlock, 0, s>>>(n, N, pos, crd, static_cast<const V *>(vals),
                                          static_cast<const BT *>(Bd), ldb, static_cast<OT *>(Out),
-                                         ldo, t.row, t.pos, t.ntiles, stride,
+                                         ldo, t.row, t.pos, t.own, t.ntiles, stride,
                                          static_cast<Acc *>(carry));
         }
         return hipGetLastError();

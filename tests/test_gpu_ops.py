@@ -932,3 +932,25 @@ def test_spadd3_staged_shapes(n, m, deg, long, dtype):
     assert_close(host64(A.vals), rvals, rS, RTOL[dtype], "spadd3 staged")
     again = spl.spadd3(*ops, sched=spl.schedule("row", variant=1))
     assert torch.equal(A.vals, again.vals) and torch.equal(A.crd, again.crd)
+
+
+@pytest.mark.parametrize("K", [4, 33])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 65_536, 65_537])
+def test_sddmm_chunks_by_size(n, K):
+    """The leaf finds its own chunks of 512 rows and positions up to 2,048 of
+    them (65,536 rows of 15 are exactly that many), a partition kernel beyond.
+    Small integers: exact."""
+    spl = _spl()
+    dev = torch.device("cuda")
+    g = torch.Generator(device=dev)
+    g.manual_seed(n)
+    deg, m = 15, 600
+    crd = torch.randint(0, m // deg, (n, deg), generator=g, device=dev)
+    crd += torch.arange(deg, device=dev) * (m // deg)
+    pos = torch.arange(n + 1, device=dev, dtype=torch.int32) * deg
+    draw = lambda *s: torch.randint(-3, 4, s, generator=g, device=dev).float()  # noqa: E731
+    vals, C, D = draw(n * deg), draw(n, K), draw(m, K)
+    B = spl.CSR(pos, crd.reshape(-1).to(torch.int32), vals, (n, m))
+    A = spl.sddmm(B, C, D)
+    ref = torch.stack([(C * D[crd[:, j]]).sum(1) for j in range(deg)], 1) * vals.reshape(n, deg)
+    assert torch.equal(getattr(A, "vals", A).reshape(n, deg), ref)
