@@ -400,7 +400,8 @@ Pieces pieces_for(const Plan &p, int64_t rows, int64_t nnz, int64_t chunk) {
 // of 10, 32 FP32 columns: 17.9 -> 14.9 us a call, 40,000 rows, 860
 // workgroups: 18.7 -> 16.6; SDDMM of 2,000 rows of 8, K = 64: 15.5 -> 11.8,
 // 1e5 rows, 1,760 workgroups: 38.5 -> 37.3; at 2e5 rows, 3,500 workgroups,
-// 54.4 and 55.6, 69.3 and 68.5).
+// 54.4 and 55.6, 69.3 and 68.5.  SpMV, 1e5 rows of 4, FP32: 15.9 -> 13.5;
+// 4e5 rows of 10, FP64, 2,150 workgroups: 35.6 and 36.6).
 bool finds_own(const Plan &p, const Pieces &q, int64_t blocks) {
     return p.kind == SPL_MERGE && q.stride == 1 && q.count * blocks <= 2048;
 }
@@ -1274,8 +1275,11 @@ spl_status spl_spmv(spl_context *ctx, const spl_sparse *B, const spl_dense *c, s
                 "SpMV fix-up launch");
         return SPL_OK;
     }
-    SPL_HIP(spl::launch_tile_bounds(p.kind, n, B->pos[1], B->nnz, q.size, cv.tiles, s),
-            "tile bounds launch");
+    if (p.variant == 0 && finds_own(p, q, 1))
+        cv.tiles.own = n + B->nnz;
+    else
+        SPL_HIP(spl::launch_tile_bounds(p.kind, n, B->pos[1], B->nnz, q.size, cv.tiles, s),
+                "tile bounds launch");
     LeafTimer tm(ctx, SPL_OP_SPMV, s);
     SPL_HIP(spl::launch_spmv_tiles(B->vtype, p.items, n, B->pos[1], B->crd[1], B->vals, c->data,
                                    a->data, cv.tiles, q.stride, /*exact_chunks=*/p.kind == SPL_MERGE,
@@ -1540,8 +1544,11 @@ spl_status spl_spttv(spl_context *ctx, const spl_sparse *B, const spl_dense *c, 
     SPL_CHECK(get_workspace(ctx, workspace, workspace_bytes, spmv_ws(&v, p), &ws));
     const Pieces q = pieces_for(p, F, B->nnz, spmv_chunk(p));
     Carved cv = carve(ws, q.count);
-    SPL_HIP(spl::launch_tile_bounds(p.kind, F, v.pos[1], B->nnz, q.size, cv.tiles, s),
-            "tile bounds launch");
+    if (p.variant == 0 && finds_own(p, q, 1))
+        cv.tiles.own = F + B->nnz;
+    else
+        SPL_HIP(spl::launch_tile_bounds(p.kind, F, v.pos[1], B->nnz, q.size, cv.tiles, s),
+                "tile bounds launch");
     LeafTimer tm(ctx, SPL_OP_SPTTV, s);
     SPL_HIP(spl::launch_spmv_tiles(B->vtype, p.items, F, v.pos[1], v.crd[1], B->vals, c->data,
                                    A->data, cv.tiles, q.stride, /*exact_chunks=*/p.kind == SPL_MERGE,

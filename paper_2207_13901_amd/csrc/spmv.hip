@@ -667,11 +667,15 @@ __global__ __launch_bounds__(kBlock) void k_spmv_flag(
 // band of 2e7 rows (FP64, 8.8 GB): 2,795 -> 1,959 us, 4.5 TB/s.
 constexpr int kOnceLds = 21000;
 
-template <typename V, int ITEMS, typename P = int32_t, typename TP = int32_t>
+// OWN: the workgroup finds the bounds of its chunk of the `own` merged items by
+// itself (finds_own in abi.cpp) and leaves the row open at its end in trow for
+// the fix-up.
+template <typename V, int ITEMS, typename P = int32_t, typename TP = int32_t, bool OWN = false>
 __global__ __launch_bounds__(kBlock) void k_spmv_once(
     int64_t n, const P *__restrict__ pos, const int32_t *__restrict__ crd,
     const V *__restrict__ vals, const V *__restrict__ x, V *__restrict__ y,
-    const int32_t *__restrict__ trow, const TP *__restrict__ tpos, double *__restrict__ carry) {
+    int32_t *__restrict__ trow, const TP *__restrict__ tpos, int64_t own,
+    double *__restrict__ carry) {
     static_assert(ITEMS == 4 || ITEMS == 8, "flags are read as one 4- or 8-byte word");
     using Flags = typename std::conditional<ITEMS == 4, uint32_t, uint64_t>::type;
     constexpr int kChunk = kBlock * ITEMS;
@@ -683,8 +687,24 @@ __global__ __launch_bounds__(kBlock) void k_spmv_once(
     __shared__ double s_open;
     const int tid = threadIdx.x;
     const int64_t c = blockIdx.x;
-    const int64_t bi = trow[c], bp = tpos[c];
-    const int nr = static_cast<int>(trow[c + 1] - bi), np = static_cast<int>(tpos[c + 1] - bp);
+    ChunkBounds b;
+    if constexpr (OWN) {
+        __shared__ int64_t s_row[2];
+        const int64_t d0 = c * kChunk, d1 = d0 + kChunk < own ? d0 + kChunk : own;
+        b = own_bounds(pos, n, d0, d1, s_row);
+        // the same in every lane: as scalars, as the descriptors need them
+        auto scalar = [](int64_t w) {
+            const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(w));
+            const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(w >> 32));
+            return static_cast<int64_t>(static_cast<uint64_t>(hi) << 32 | lo);
+        };
+        b = {scalar(b.ci), scalar(b.cp), scalar(b.ei), scalar(b.ep)};
+        if (tid == 0) trow[c + 1] = static_cast<int32_t>(b.ei);
+    } else {
+        b = {trow[c], tpos[c], trow[c + 1], tpos[c + 1]};
+    }
+    const int64_t bi = b.ci, bp = b.cp;
+    const int nr = static_cast<int>(b.ei - bi), np = static_cast<int>(b.ep - bp);
     const auto rp = chunk_rsrc(pos + bi + 1, static_cast<int>(sizeof(P)) * nr);
     const auto rc = chunk_rsrc(crd + bp, 4 * np);
     const auto rv = chunk_rsrc(vals + bp, static_cast<int>(sizeof(V)) * np);
@@ -1079,14 +1099,16 @@ hipError_t spmv_tiles_dispatch(int items, int64_t n, const int32_t *pos, const i
         return hipGetLastError();
     }
     if (exact && variant == 0 && stride == 1) {
-        if (items <= 4)
-            k_spmv_once<V, 4><<<grid, kBlock, kOnceLds, s>>>(n, pos, crd, vals, x, y, t.row, t.pos,
-                                                              carry);
-        else
-            k_spmv_once<V, 8><<<grid, kBlock, kOnceLds, s>>>(n, pos, crd, vals, x, y, t.row, t.pos,
-                                                              carry);
-        return hipGetLastError();
+        auto go = [&](auto kern) {
+            kern<<<grid, kBlock, kOnceLds, s>>>(n, pos, crd, vals, x, y, t.row, t.pos, t.own, carry);
+            return hipGetLastError();
+        };
+        if (t.own)
+            return items <= 4 ? go(k_spmv_once<V, 4, int32_t, int32_t, true>)
+                              : go(k_spmv_once<V, 8, int32_t, int32_t, true>);
+        return items <= 4 ? go(k_spmv_once<V, 4>) : go(k_spmv_once<V, 8>);
     }
+    if (t.own) return hipErrorInvalidValue;  // the leaves below read the bounds
     if (exact && variant == 0) {
         if (items <= 4)
             k_spmv_flag<V, 4><<<grid, kBlock, 0, s>>>(n, pos, crd, vals, x, y, t.row, t.pos,
@@ -1201,10 +1223,10 @@ hipError_t launch_spmv_flag64(int dtype, int items, int64_t n, const int64_t *po
         if (stride == 1) {
             if (items <= 4)
                 k_spmv_once<V, 4, int64_t, int64_t><<<grid, kBlock, kOnceLds, s>>>(
-                    n, pos, crd, v, xx, yy, t.row, t.pos64, carry);
+                    n, pos, crd, v, xx, yy, t.row, t.pos64, 0, carry);
             else
                 k_spmv_once<V, 8, int64_t, int64_t><<<grid, kBlock, kOnceLds, s>>>(
-                    n, pos, crd, v, xx, yy, t.row, t.pos64, carry);
+                    n, pos, crd, v, xx, yy, t.row, t.pos64, 0, carry);
             return hipGetLastError();
         }
         if (items <= 4)

@@ -500,3 +500,25 @@ def test_spmm_default_by_size(dtype, N, rows):
     for k in range(deg):
         ref += vals.reshape(rows, deg)[:, k, None].double() * C[crd[:, k]].double()
     assert torch.equal(spl.spmm(B, C).double(), ref)
+
+
+# Workgroups that find their own chunks: 2,048 chunks of 2,048 items at most
+# (262,144 rows of 15), more columns than the one-launch leaf takes.  Small
+# integers: the sums are exact.
+@pytest.mark.parametrize("rows,deg", [(3, 40_000), (127, 15), (128, 15), (262_144, 15), (262_145, 15)])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_spmv_own_chunks(dtype, rows, deg):
+    spl = _spl()
+    g = torch.Generator(device=dev())
+    g.manual_seed(rows)
+    m = 1_200_000
+    crd = torch.randint(0, m // deg, (rows, deg), generator=g, device=dev())
+    crd += torch.arange(deg, device=dev()) * (m // deg)
+    pos = torch.arange(rows + 1, device=dev(), dtype=torch.int32) * deg
+    vals = torch.randint(-3, 4, (rows * deg,), generator=g, device=dev()).to(dtype)
+    x = torch.randint(-3, 4, (m,), generator=g, device=dev()).to(dtype)
+    B = spl.CSR(pos, crd.reshape(-1).to(torch.int32), vals, (rows, m))
+    ref = (vals.reshape(rows, deg).double() * x[crd].double()).sum(1)
+    for sc in (None, dict(kind="merge"), dict(kind="merge", tile=1024, items_per_lane=4)):
+        y = spl.spmv(B, x, sched=spl.schedule(**sc) if sc else None)
+        assert torch.equal(y.double(), ref), sc
