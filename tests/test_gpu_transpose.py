@@ -83,10 +83,11 @@ def test_transpose_full_size_power_law():
 
 
 @pytest.mark.parametrize("nnz,n,m,cols", [
-    # one tile of 4,096 entries and its edges; 16 tiles (offsets summed by the
-    # scatter) and 17 (by their own kernel); a ragged last tile
+    # one tile of 4,096 entries and its edges; 16 and 17 tiles, 64 (offsets
+    # summed by the scatter) and 65 (by their own kernel); a ragged last tile
     (4095, 500, 130, "any"), (4096, 500, 130, "any"), (4097, 500, 130, "any"),
     (65536, 9000, 2000, "any"), (65537, 9000, 2000, "any"), (200_003, 9000, 70_000, "any"),
+    (262_144, 9000, 2000, "any"), (262_145, 9000, 2000, "any"),
     # four passes and gaps of millions of columns; every entry in one column;
     # one row holding every entry; runs of thousands of empty rows in a tile
     (3000, 2900, 40_000_000, "any"), (70_000, 70_000, 300, "one"), (9000, 1, 70_000, "any"),
