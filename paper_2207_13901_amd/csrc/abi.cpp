@@ -674,8 +674,7 @@ size_t inner_ws(const spl_sparse *B) {
 }
 
 size_t spadd3_ws(int64_t n) {
-    const size_t blocks = static_cast<size_t>(spl::spadd3_blocks(n));
-    return align_up(blocks * 8) + align_up(blocks * 4);
+    return align_up(static_cast<size_t>(spl::spadd3_blocks(n)) * 8);
 }
 
 bool same_dims(const spl_sparse *a, const spl_sparse *b) {
@@ -1833,13 +1832,10 @@ spl_status spl_spadd3_symbolic(spl_context *ctx, const spl_sparse *B, const spl_
     const int64_t n = B->dims[0];
     void *ws = nullptr;
     SPL_CHECK(get_workspace(ctx, workspace, workspace_bytes, spadd3_ws(n), &ws));
-    int64_t *base = static_cast<int64_t *>(ws);
-    int32_t *block_sum = reinterpret_cast<int32_t *>(
-        static_cast<char *>(ws) + align_up(static_cast<size_t>(spl::spadd3_blocks(n)) * 8));
     LeafTimer tm(ctx, SPL_OP_SPADD3, s);
     SPL_HIP(spl::launch_spadd3_symbolic(n, B->nnz + C->nnz + D->nnz, B->pos[1], B->crd[1], C->pos[1],
-                                        C->crd[1], D->pos[1], D->crd[1], A_pos, base, block_sum,
-                                        ctx->readback, ctx->counted, s),
+                                        C->crd[1], D->pos[1], D->crd[1], A_pos,
+                                        static_cast<int64_t *>(ws), ctx->readback, ctx->counted, s),
             "SpAdd3 symbolic launch");
     tm.stop();
     SPL_HIP(hipEventSynchronize(ctx->counted), "hipEventSynchronize");

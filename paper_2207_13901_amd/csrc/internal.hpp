@@ -186,15 +186,14 @@ hipError_t launch_window_offsets(int64_t n, const int32_t *begin, const int32_t 
 // counted: recorded behind the scan (the total may go to pinned host memory).
 hipError_t launch_pos_scan(int64_t n, int32_t *apos, int64_t *tile_sum, int64_t *total,
                            hipStream_t s, hipEvent_t counted = nullptr);
-// Entries of base and of block_sum that the symbolic phase needs.
+// Entries of block_sum that the symbolic phase needs.
 int64_t spadd3_blocks(int64_t n);
 // nnz_in: the operands' entries together; total: pinned host memory, written,
 // as the positions are, when `counted` is reached.
 hipError_t launch_spadd3_symbolic(int64_t n, int64_t nnz_in, const int32_t *bp, const int32_t *bc,
                                   const int32_t *cp, const int32_t *cc, const int32_t *dp,
-                                  const int32_t *dc, int32_t *apos, int64_t *base,
-                                  int32_t *block_sum, int64_t *total, hipEvent_t counted,
-                                  hipStream_t s);
+                                  const int32_t *dc, int32_t *apos, int64_t *block_sum,
+                                  int64_t *total, hipEvent_t counted, hipStream_t s);
 hipError_t launch_spadd3_numeric(int vtype, int64_t n, int64_t nnz_in, const int32_t *bp, const int32_t *bc,
                                  const void *bv, const int32_t *cp, const int32_t *cc,
                                  const void *cv, const int32_t *dp, const int32_t *dc,

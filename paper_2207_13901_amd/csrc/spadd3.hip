@@ -22,6 +22,7 @@
 // lines open than the caches hold, and a window is filled only by the lanes
 // whose rows reach into it.
 #include "device.hpp"
+#include "group_scan.hpp"
 #include "internal.hpp"
 
 namespace spl {
@@ -324,37 +325,17 @@ __device__ __forceinline__ void walk_staged(const Csr3 &m, const Runs &R, int32_
     }
 }
 
-// Inclusive sum over the T lanes of the workgroup; *all gets the total.
-template <int T>
-__device__ __forceinline__ int32_t group_inclusive(int32_t v, int32_t *s_wave, int32_t *all) {
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int32_t u = __shfl_up(v, off);
-        v += lane >= off ? u : 0;
-    }
-    if (lane == kWave - 1) s_wave[wave] = v;
-    __syncthreads();
-    int32_t total = 0;
-#pragma unroll
-    for (int w = 0; w < T / kWave; ++w) {
-        v += w < wave ? s_wave[w] : 0;
-        total += s_wave[w];
-    }
-    *all = total;
-    return v;
-}
-
 // Symbolic phase (35 us on the operands described at k_spadd3_bits, whose
 // coordinates are 0.11 GB: bound by the walks' vector-ALU work as much as by
 // HBM): apos[i + 1] = entries of the workgroup's output rows up to
-// row i, block_sum = all of them (k_block_bases and k_add_bases then make
-// positions of them).
+// row i, block_sum = all of them in 64 bits (k_block_bases and k_add_bases
+// then make positions of them; a total past 32 bits is refused, and the
+// positions, wrapped then, are not used).
 template <int T>
 __global__ __launch_bounds__(T) void k_spadd3_count(int64_t n, Csr3 m, int room, int32_t *apos,
-                                                    int32_t *block_sum) {
+                                                    int64_t *block_sum) {
     extern __shared__ __align__(16) int32_t s_pool[];
-    __shared__ int32_t s_wave[T / kWave];
+    __shared__ int64_t s_wave[T / kWave];
     const int64_t r0 = static_cast<int64_t>(blockIdx.x) * T;
     const int64_t r1 = r0 + T < n ? r0 + T : n;
     const int64_t i = r0 + threadIdx.x;
@@ -367,19 +348,20 @@ __global__ __launch_bounds__(T) void k_spadd3_count(int64_t n, Csr3 m, int room,
     } else if (i < n) {
         k = union_count(m, Crd3{m.bc, m.cc, m.dc, 0, 0, 0}, i);
     }
-    int32_t all;
-    const int32_t upto = group_inclusive<T>(k, s_wave, &all);
-    if (i < n) apos[i + 1] = upto;
+    int64_t all;
+    const int64_t upto = group_inclusive<T>(k, s_wave, &all);
+    if (i < n) apos[i + 1] = static_cast<int32_t>(upto);
     if (threadIdx.x == 0) block_sum[blockIdx.x] = all;
 }
 
-// One workgroup: base[b] = sum of block_sum[0 .. b - 1]; the total to *total
-// (pinned host memory).  1,024 lanes, kBasePer consecutive blocks each a round.
+// One workgroup: block_sum[b] becomes the sum of block_sum[0 .. b - 1]; the
+// total to *total (pinned host memory).  1,024 lanes, kBasePer consecutive
+// blocks each a round.
 constexpr int kBaseLanes = 1024, kBasePer = 8;
 
 __global__ __launch_bounds__(kBaseLanes) void k_block_bases(int64_t blocks,
-                                                            const int32_t *__restrict__ block_sum,
-                                                            int64_t *__restrict__ base, int64_t *total) {
+                                                            int64_t *__restrict__ block_sum,
+                                                            int64_t *total) {
     __shared__ int64_t s_wave[kBaseLanes / kWave];
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     int64_t carry = 0;
@@ -405,7 +387,7 @@ __global__ __launch_bounds__(kBaseLanes) void k_block_bases(int64_t blocks,
         }
 #pragma unroll
         for (int j = 0; j < kBasePer; ++j) {
-            if (b + j < blocks) base[b + j] = run;
+            if (b + j < blocks) block_sum[b + j] = run;
             run += v[j];
         }
         carry += all;
@@ -415,20 +397,20 @@ __global__ __launch_bounds__(kBaseLanes) void k_block_bases(int64_t blocks,
 }
 
 // apos[i + 1] += base of row i's block of 2^log2rows rows; apos[0] = 0.
-// A workgroup takes 1,024 rows.  base == nullptr: it adds up the block sums
-// before its own by itself, which costs less than another launch while they
-// are few, and the last workgroup writes the total.
+// A workgroup takes 1,024 rows.  OWN: it adds up the block sums before its own
+// by itself, which costs less than another launch while they are few, and the
+// last workgroup writes the total; else k_block_bases has made bases of them.
 constexpr int kAddRows = 4;
 constexpr int64_t kOwnBases = 16384;  // blocks up to which it does
 
+template <bool OWN>
 __global__ __launch_bounds__(kBlock) void k_add_bases(int64_t n, int log2rows, int64_t blocks,
-                                                      const int64_t *__restrict__ base,
-                                                      const int32_t *__restrict__ block_sum,
+                                                      const int64_t *__restrict__ block_sum,
                                                       int32_t *__restrict__ apos, int64_t *total) {
     __shared__ int64_t s_sum[kBlock / kWave];
     const int64_t first = static_cast<int64_t>(blockIdx.x) * kBlock * kAddRows;
     int64_t before = 0;  // entries before the workgroup's first block
-    if (!base) {
+    if constexpr (OWN) {
         const int64_t fb = first >> log2rows;
 #pragma unroll 8
         for (int64_t b = threadIdx.x; b < fb; b += kBlock) before += block_sum[b];
@@ -449,10 +431,10 @@ __global__ __launch_bounds__(kBlock) void k_add_bases(int64_t n, int log2rows, i
         const int64_t i = first + threadIdx.x + j * kBlock;
         if (i >= n) continue;
         int64_t add = before;
-        if (base)
-            add = base[i >> log2rows];
-        else
+        if constexpr (OWN)
             for (int64_t b = first >> log2rows; b < i >> log2rows; ++b) add += block_sum[b];
+        else
+            add = block_sum[i >> log2rows];
         apos[i + 1] += static_cast<int32_t>(add);
     }
     if (first + threadIdx.x == 0) apos[0] = 0;
@@ -756,9 +738,8 @@ int64_t spadd3_blocks(int64_t n) { return ceil_div(n > 0 ? n : 1, 64); }
 
 hipError_t launch_spadd3_symbolic(int64_t n, int64_t nnz_in, const int32_t *bp, const int32_t *bc,
                                   const int32_t *cp, const int32_t *cc, const int32_t *dp,
-                                  const int32_t *dc, int32_t *apos, int64_t *base,
-                                  int32_t *block_sum, int64_t *total, hipEvent_t counted,
-                                  hipStream_t s) {
+                                  const int32_t *dc, int32_t *apos, int64_t *block_sum,
+                                  int64_t *total, hipEvent_t counted, hipStream_t s) {
     Csr3 m{bp, bc, cp, cc, dp, dc};
     const StageShape g = stage_rows(n ? 4.0 * static_cast<double>(nnz_in) / static_cast<double>(n) : 0, 1024);
     const int rows = g.rows ? g.rows : 64;
@@ -776,11 +757,11 @@ hipError_t launch_spadd3_symbolic(int64_t n, int64_t nnz_in, const int32_t *bp, 
     const dim3 add_grid(static_cast<unsigned>(ceil_div(n > 0 ? n : 1, kAddRows * kBlock)));
     const int log2rows = rows == 128 ? 7 : 6;
     if (blocks <= kOwnBases) {
-        k_add_bases<<<add_grid, kBlock, 0, s>>>(n, log2rows, blocks, nullptr, block_sum, apos, total);
+        k_add_bases<true><<<add_grid, kBlock, 0, s>>>(n, log2rows, blocks, block_sum, apos, total);
     } else {
-        k_block_bases<<<1, kBaseLanes, 0, s>>>(blocks, block_sum, base, total);
+        k_block_bases<<<1, kBaseLanes, 0, s>>>(blocks, block_sum, total);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        k_add_bases<<<add_grid, kBlock, 0, s>>>(n, log2rows, blocks, base, block_sum, apos, total);
+        k_add_bases<false><<<add_grid, kBlock, 0, s>>>(n, log2rows, blocks, block_sum, apos, total);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return hipEventRecord(counted, s);
