@@ -165,6 +165,15 @@ __global__ __launch_bounds__(kBlock) void k_radix_offsets(int64_t ntiles, int32_
     if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
+// Rows that a tile's entries span up to which the first pass marks every row's
+// start; in a tile of more rows (nearly all of them empty) every entry finds
+// its row by a search.  Marking takes one workgroup a step per 256 rows,
+// whatever the entries; a search log2(rows) steps of 16 loads a lane (4e5
+// entries in 4 / 8 / 64 / 256 times as many rows: marked 81 / 93 / 370 / 1,877
+// us a call, searched 80 / 82 / 109 / 131; 4,000 entries in 8e6 rows 9,099
+// and 157).
+constexpr int64_t kMarkRows = 4 * kRadixTile;
+
 // The row holding position p: the last i in [0, n) with pos[i] <= p, found by
 // one wave 64 probes at a time.
 __device__ __forceinline__ int64_t wave_row_of(const int32_t *__restrict__ pos, int64_t n, int64_t p) {
@@ -260,27 +269,48 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(
         for (int r = 0; r < kRounds; ++r) s_i32[r * kBlock + tid] = 0;
         __syncthreads();
         const int64_t r0 = s_rows[0], r1 = s_rows[1];
-        for (int64_t q = r0 + 1 + tid; q <= r1; q += kBlock)
-            atomicMax(&s_i32[pos[q] - base], static_cast<int32_t>(q - r0));
-        __syncthreads();
-        int32_t top = 0;
+        if (r1 - r0 <= kMarkRows) {
+            for (int64_t q = r0 + 1 + tid; q <= r1; q += kBlock)
+                atomicMax(&s_i32[pos[q] - base], static_cast<int32_t>(q - r0));
+            __syncthreads();
+            int32_t top = 0;
 #pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
-            row[r] = s_i32[e0 + r * kWave];
-            top = row[r] > top ? row[r] : top;
-        }
-        top = wave_inclusive_max(top);
-        if (lane == kWave - 1) s_tot[wave] = top;
-        __syncthreads();
-        int32_t run = 0;
+            for (int r = 0; r < kRounds; ++r) {
+                row[r] = s_i32[e0 + r * kWave];
+                top = row[r] > top ? row[r] : top;
+            }
+            top = wave_inclusive_max(top);
+            if (lane == kWave - 1) s_tot[wave] = top;
+            __syncthreads();
+            int32_t run = 0;
 #pragma unroll
-        for (int w = 0; w < kWaves - 1; ++w) run = w < wave && s_tot[w] > run ? s_tot[w] : run;
+            for (int w = 0; w < kWaves - 1; ++w) run = w < wave && s_tot[w] > run ? s_tot[w] : run;
 #pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
-            const int32_t m = wave_inclusive_max(row[r]);
-            row[r] = static_cast<int32_t>(r0) + (m > run ? m : run);
-            const int32_t last = __builtin_amdgcn_readlane(m, kWave - 1);
-            run = last > run ? last : run;
+            for (int r = 0; r < kRounds; ++r) {
+                const int32_t m = wave_inclusive_max(row[r]);
+                row[r] = static_cast<int32_t>(r0) + (m > run ? m : run);
+                const int32_t last = __builtin_amdgcn_readlane(m, kWave - 1);
+                run = last > run ? last : run;
+            }
+        } else {
+            const uint32_t span = static_cast<uint32_t>(r1 - r0);
+            const int32_t *first = pos + r0;
+            uint32_t at[kRounds];  // the last row found to start at or before the entry, from r0
+#pragma unroll
+            for (int r = 0; r < kRounds; ++r) at[r] = 0;
+            for (uint32_t step = 1u << (31 - __clz(span)); step > 0; step >>= 1) {
+                int32_t v[kRounds];
+#pragma unroll
+                for (int r = 0; r < kRounds; ++r)
+                    v[r] = first[step <= span - at[r] ? at[r] + step : span];
+#pragma unroll
+                for (int r = 0; r < kRounds; ++r) {
+                    const int64_t p = base + (e0 + r * kWave < cnt ? e0 + r * kWave : cnt - 1);
+                    at[r] += step <= span - at[r] && v[r] <= p ? step : 0;
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < kRounds; ++r) row[r] = static_cast<int32_t>(r0 + at[r]);
         }
     } else {
         const auto rr = span_rsrc(rows_in + base, 4u * static_cast<uint32_t>(cnt));

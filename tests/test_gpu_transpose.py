@@ -111,6 +111,55 @@ def test_transpose_tile_edges(nnz, n, m, cols, dtype):
     _check(spl, _csr(spl, pos, col, rs.uniform(-1, 1, nnz), (n, m), dtype), (nnz, n, m, dtype))
 
 
+def _spread(n, m, row, rs):
+    """The n x m pattern of the entries in rows `row` (sorted; of one row,
+    consecutive columns)."""
+    pos = np.zeros(n + 1, np.int64)
+    np.cumsum(np.bincount(row, minlength=n), out=pos[1:])
+    return pos, np.arange(row.size) - pos[row], rs.uniform(-1, 1, row.size)
+
+
+@pytest.mark.parametrize("span", [16_384, 16_385, 16_387, 65_536, 5_000_001])
+@pytest.mark.parametrize("where", ["ends", "even", "second tile"])
+def test_transpose_tiles_of_many_rows(span, where):
+    """Tiles whose entries span more rows than are marked one by one (up to
+    16,384), several entries to a row and long runs of empty rows among them;
+    in the last case behind a tile that spans few."""
+    spl = _spl()
+    rs = np.random.RandomState(span)
+    far = span + 7  # the last entry's row: `span` rows past the first's
+    row = np.array([7] * 3 + [far] * 2) if where == "ends" else \
+        np.sort(np.concatenate([np.linspace(7, far, 1500).astype(np.int64)] * 2))
+    if where == "second tile":
+        row = np.sort(np.concatenate([rs.randint(0, 8, 4096), row + 1]))
+    print(f"transpose span={span} {where}", flush=True)
+    for tail in (0, 100_000):  # empty rows at the end
+        n = int(row[-1]) + 1 + tail
+        _check(spl, _csr(spl, *_spread(n, 5000, row, rs), (n, 5000)), (span, where, tail))
+
+
+def test_transpose_hypersparse_time():
+    """Twenty million rows for 4,000 entries cost a search per entry, not a
+    walk over the rows by one workgroup (which took hundreds of times as
+    long as the same entries in 4,000 rows; the search takes about twice)."""
+    spl = _spl()
+    rs = np.random.RandomState(3)
+    us = []
+    for n in (4000, 20_000_000):
+        row = np.sort(rs.randint(0, n, 4000))
+        B = _csr(spl, *_spread(n, 300, row, rs), (n, 300))
+        _check(spl, B, n)
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(10):
+            spl.transpose(B)
+        b.record()
+        b.synchronize()
+        us.append(a.elapsed_time(b) * 100)
+    print(us, flush=True)
+    assert us[1] < 50 * us[0], us
+
+
 @pytest.mark.parametrize("kind", ["float", "int"])
 def test_csc_spmv(kind):
     # A (n x m) given by columns: its CSR comes from the transposition, then
