@@ -17,8 +17,9 @@
 // (rows spanning many tiles) are taken by the whole wave, one after
 // another: the run's end is found 64 tiles at a time with a ballot, and the
 // carries are summed with a fixed assignment of tiles to lanes and a fixed
-// reduction order.  Every order is fixed, so the result is bitwise
-// reproducible.
+// reduction order.  Runs of vector carries over kFixWave tiles and more are
+// left to the whole workgroup (fix_long_run).  Every order is fixed, so the
+// result is bitwise reproducible.
 #pragma once
 
 #include "device.hpp"
@@ -35,6 +36,66 @@ constexpr int kFixBatch = 8;    // carries one lane loads before adding them
 // 4.8 / 4.8).
 constexpr int kFixCols = 4;
 
+constexpr int kFixWave = kWave;  // runs of vector carries that a wave takes alone are shorter
+constexpr int kFixDeep = 16;     // carries one lane of a workgroup loads before adding them
+static_assert(kFixWave >= kFixBlock / kFixLanes, "at most one longer run starts in a workgroup");
+
+// The run of row r that starts at tile `us` (and holds at least kFixWave
+// tiles), by the workgroup: its end by a search of 64 probes a step, then a
+// lane a column in groups of 8, 16 or 32, each group a slice of the tiles.
+// What a run costs is rounds of dependent loads: 12,300 tiles of 64 FP32
+// columns on one row (an MTTKRP of one slice) made a call of 608 us when one
+// wave took 16 tiles a round, and 64 a round looking for the end; 201 so.
+template <typename OT, typename Acc, typename OpenRow>
+__device__ __forceinline__ void fix_long_run(const OpenRow &open_row, int64_t us, int32_t r,
+                                             int64_t ntiles, int64_t ncols, Acc *s_part,
+                                             const Acc *__restrict__ carry, OT *__restrict__ orow) {
+    const int tid = threadIdx.x, lane = tid % kWave;
+    // the same in every lane: as scalars, so that the carries' addresses take
+    // no vector registers
+    auto scalar = [](int64_t w) {
+        const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(w));
+        const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(w >> 32));
+        return static_cast<int64_t>(static_cast<uint64_t>(hi) << 32 | lo);
+    };
+    us = scalar(us);
+    int64_t lo = us + kFixWave - 1, end = ntiles;  // tile lo is open on r; tile `end` is not (or is past the last)
+    while (end - lo > 1) {
+        const int64_t step = (end - lo + kWave - 1) / kWave;
+        const int64_t at = lo + (lane + 1) * step;
+        const bool same = at < end && open_row(at) == r;
+        const int k = __popcll(__ballot(same));
+        end = lo + (k + 1) * step < end ? lo + (k + 1) * step : end;
+        lo += k * step;
+    }
+    end = scalar(end);
+    const int width = ncols > 16 ? 32 : ncols > 8 ? 16 : 8, slices = kFixBlock / width;
+    const int slice = tid / width, cc = tid % width;
+    for (int64_t c0 = 0; c0 < ncols; c0 += width) {
+        const int64_t col = c0 + cc;
+        Acc part = 0;
+        if (col < ncols) {
+            const uint32_t mine = static_cast<uint32_t>(slice * ncols + col);
+            int64_t v = us;
+            for (; v + kFixDeep * slices <= end; v += kFixDeep * slices) {
+                Acc t[kFixDeep];
+#pragma unroll
+                for (int k = 0; k < kFixDeep; ++k) t[k] = (carry + (v + k * slices) * ncols)[mine];
+#pragma unroll
+                for (int k = 0; k < kFixDeep; ++k) part += t[k];
+            }
+            for (v += slice; v < end; v += slices) part += carry[v * ncols + col];
+        }
+        s_part[tid] = part;
+        __syncthreads();
+        if (slice == 0 && col < ncols) {
+            for (int k = 1; k < slices; ++k) part += s_part[k * width + cc];
+            orow[col] = narrow<OT>(static_cast<Acc>(orow[col]) + part);
+        }
+        __syncthreads();
+    }
+}
+
 template <typename OT, typename Acc>
 __global__ __launch_bounds__(kFixBlock) void k_carry_fixup(int64_t rows, int64_t ncols,
                                                            const int32_t *__restrict__ trow,
@@ -43,6 +104,8 @@ __global__ __launch_bounds__(kFixBlock) void k_carry_fixup(int64_t rows, int64_t
                                                            const Acc *__restrict__ carry,
                                                            OT *__restrict__ out, int64_t ldo) {
     const int lane = threadIdx.x % kWave;
+    __shared__ Acc s_part[kFixBlock];
+    __shared__ int64_t s_first[kFixBlock / kWave];  // per wave: first tile of a run left to all, or -1
     // lanes per tile: 1 for a single column, else 8 (lane c takes columns c, c + 8, ...)
     const int per = ncols == 1 ? 1 : kFixLanes;
     const int c = lane % per;
@@ -100,6 +163,7 @@ __global__ __launch_bounds__(kFixBlock) void k_carry_fixup(int64_t rows, int64_t
 
     // long runs: the whole wave on each in turn (the mask is wave-uniform)
     uint64_t pending = __ballot(first && longrun && c == 0);
+    int64_t left = -1;
     while (pending) {
         const int src = __ffsll(static_cast<unsigned long long>(pending)) - 1;
         pending &= pending - 1;
@@ -114,6 +178,11 @@ __global__ __launch_bounds__(kFixBlock) void k_carry_fixup(int64_t rows, int64_t
                 e = v0 + cnt;
                 break;
             }
+            if (ncols > 1) break;
+        }
+        if (e == us) {  // (a run holds its first tile)
+            left = us;
+            continue;
         }
         OT *orow = out + static_cast<int64_t>(rr) * ldo;
         if (ncols == 1) {
@@ -153,6 +222,15 @@ __global__ __launch_bounds__(kFixBlock) void k_carry_fixup(int64_t rows, int64_t
             if (slice == 0 && col < ncols) orow[col] = narrow<OT>(static_cast<Acc>(orow[col]) + part);
         }
     }
+
+    if (ncols == 1) return;
+    if (lane == 0) s_first[threadIdx.x / kWave] = left;
+    __syncthreads();
+    for (int w = 0; w < kFixBlock / kWave; ++w) left = s_first[w] > left ? s_first[w] : left;
+    if (left < 0) return;
+    const int32_t lr = open_row(left);
+    fix_long_run(open_row, left, lr, ntiles, ncols, s_part, carry,
+                 out + static_cast<int64_t>(lr) * ldo);
 }
 
 template <typename OT, typename Acc>

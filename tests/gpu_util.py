@@ -37,6 +37,22 @@ def assert_close(got, ref, S, rtol, what=""):
     return float(np.max(err / np.where(S > 0, S, 1.0))) if err.size else 0.0
 
 
+def call_us(fn, reps=20):
+    """Time of one call of fn among `reps` of them, in microseconds: the
+    least of three runs."""
+    fn()
+    best = float("inf")
+    for _ in range(3):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(reps):
+            fn()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / reps)
+    return best
+
+
 # Unit roundoff of BF16: 8 significand bits, round to nearest even.
 BF16_U = 2.0 ** -8
 

@@ -13,7 +13,7 @@ import torch
 import oracle
 from paper_2207_13901_amd import _native as N
 from tests import tiny
-from tests.gpu_util import RTOL, assert_close, dev, host64, need_gpu
+from tests.gpu_util import RTOL, assert_close, call_us, dev, host64, need_gpu
 from workloads import configs
 
 pytestmark = pytest.mark.gpu
@@ -954,3 +954,61 @@ def test_sddmm_chunks_by_size(n, K):
     A = spl.sddmm(B, C, D)
     ref = torch.stack([(C * D[crd[:, j]]).sum(1) for j in range(deg)], 1) * vals.reshape(n, deg)
     assert torch.equal(getattr(A, "vals", A).reshape(n, deg), ref)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("N", [2, 8, 9, 16, 17, 33, 70])
+def test_carries_of_rows_over_many_tiles(N, dtype):
+    """Rows open over 8 and 9 tiles of 32 merged items (a lane and a wave of
+    the fix-up), 63 to 65 (a wave and the workgroup), and up to 4,100 of them,
+    beside short ones.  Small integers: exact."""
+    spl = _spl()
+    g = torch.Generator(device=dev())
+    g.manual_seed(N)
+    m = 140_000
+    deg = [3, 0, 5]
+    for tiles in (7, 8, 9, 10, 62, 63, 64, 65, 66, 127, 129, 191, 500, 4100):
+        deg += [32 * tiles - 11, 2, 0, 32 * tiles + 1]
+    deg = torch.tensor(deg + [1] * 9, device=dev())
+    pos = torch.zeros(deg.numel() + 1, dtype=torch.int64, device=dev())
+    torch.cumsum(deg, 0, out=pos[1:])
+    row = torch.repeat_interleave(torch.arange(deg.numel(), device=dev()), deg)
+    crd = torch.arange(row.numel(), device=dev()) - pos[row]
+    draw = lambda *s: torch.randint(-3, 4, s, generator=g, device=dev()).to(dtype)  # noqa: E731
+    vals, C = draw(row.numel()), draw(m, N)
+    B = spl.CSR(pos.to(torch.int32), crd.to(torch.int32), vals, (deg.numel(), m))
+    sched = spl.schedule("merge", col_tile=64, items_per_lane=8, tile=1, variant=1)
+    upto = torch.zeros(row.numel() + 1, N, dtype=torch.float64, device=dev())
+    torch.cumsum(vals.double()[:, None] * C.double()[crd], 0, out=upto[1:])
+    ref = upto[pos[1:]] - upto[pos[:-1]]
+    for s in (sched, None):
+        assert torch.equal(spl.spmm(B, C, sched=s).double(), ref)
+
+
+def _csf_of_slices(spl, I, F, per):
+    """F fibers of `per` entries spread over I slices, FP32."""
+    g = torch.Generator(device=dev())
+    g.manual_seed(F)
+    J, K = 2 * F // I, 20_000
+    fib = torch.unique(torch.randint(0, I * J, (F,), generator=g, device=dev()))
+    pos1 = torch.searchsorted(fib, torch.arange(I + 1, device=dev()) * J).to(torch.int32)
+    pos2 = torch.arange(fib.numel() + 1, device=dev(), dtype=torch.int32) * per
+    crd2 = torch.randint(0, K // per, (fib.numel(), per), generator=g, device=dev())
+    crd2 += torch.arange(per, device=dev()) * (K // per)
+    vals = torch.ones(fib.numel() * per, device=dev())
+    return spl.CSF(pos1, (fib % J).to(torch.int32), pos2, crd2.reshape(-1).to(torch.int32), vals,
+                   (I, J, K))
+
+
+def test_mttkrp_carries_of_one_slice_time():
+    """A tensor of one slice has every workgroup's carry added to one row,
+    which must not cost several times the product itself (the same fibers in
+    200 slices)."""
+    spl = _spl()
+    us = []
+    for I in (200, 1):
+        B = _csf_of_slices(spl, I, 1_000_000, 2)
+        C, D = (torch.rand(d, 64, device=dev()) for d in B.shape[1:])
+        us.append(call_us(lambda: spl.mttkrp(B, C, D)))
+    print(us, flush=True)
+    assert us[1] < 4 * us[0], us
