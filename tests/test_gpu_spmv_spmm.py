@@ -12,7 +12,7 @@ import torch
 
 import oracle
 from tests import tiny
-from tests.gpu_util import RTOL, assert_close, dev, host64, need_gpu
+from tests.gpu_util import RTOL, assert_close, call_us, dev, host64, need_gpu
 from workloads import configs
 
 pytestmark = pytest.mark.gpu
@@ -522,3 +522,46 @@ def test_spmv_own_chunks(dtype, rows, deg):
     for sc in (None, dict(kind="merge"), dict(kind="merge", tile=1024, items_per_lane=4)):
         y = spl.spmv(B, x, sched=spl.schedule(**sc) if sc else None)
         assert torch.equal(y.double(), ref), sc
+
+
+@pytest.mark.parametrize("size", [64, 1000])
+def test_tile_bounds_of_rows_over_many_tiles(size):
+    """The sweep's bounds in rows of 3 to 6 tiles (a lane writes up to 4) and
+    of many (the wave), two such rows side by side, first and last ones."""
+    spl = _spl()
+    deg = np.full(6000, 2)
+    for at, tiles in ((0, 70), (1, 5), (2, 3), (63, 4), (64, 4), (700, 6), (701, 300), (5999, 65)):
+        deg[at] = tiles * size - 1
+    pos = np.zeros(deg.size + 1, np.int64)
+    np.cumsum(deg, out=pos[1:])
+    crd = np.arange(pos[-1]) - np.repeat(pos[:-1], deg)
+    n, m = deg.size, int(deg.max())
+    print(f"tile bounds size={size} nnz={pos[-1]}", flush=True)
+    B = spl.CSR(torch.as_tensor(pos.astype(np.int32)).to(dev()),
+                torch.as_tensor(crd.astype(np.int32)).to(dev()),
+                torch.ones(int(pos[-1]), device=dev()), (n, m))
+    tr, tp = spl.tile_bounds(B, spl.schedule("merge", tile=size))
+    assert tr.numel() - 1 < n  # few enough tiles for the sweep
+    rr, rp = oracle.merge_split(pos.astype(np.int32), size)
+    assert np.array_equal(tr.cpu().numpy(), rr) and np.array_equal(tp.cpu().numpy(), rp)
+
+
+def test_spmm_one_long_row_time():
+    """Three million of a matrix's entries in one row, against as many rows of
+    ten: the row's tile bounds and carries must not cost more than the product."""
+    spl = _spl()
+    us = []
+    for n, long in ((500_000, 10), (200_000, 3_000_000)):
+        deg = torch.full((n,), 10, device=dev())
+        deg[n // 2] = long
+        pos = torch.zeros(n + 1, dtype=torch.int64, device=dev())
+        torch.cumsum(deg, 0, out=pos[1:])
+        row = torch.repeat_interleave(torch.arange(n, device=dev()), deg)
+        crd = torch.arange(row.numel(), device=dev()) - pos[row]
+        crd += torch.where(deg[row] == 10, row * 7919 % 2_900_000, 0)
+        C = torch.rand(3_000_000, 32, device=dev()).to(torch.bfloat16)
+        B = spl.CSR(pos.to(torch.int32), crd.to(torch.int32),
+                    torch.rand(row.numel(), device=dev()).to(torch.bfloat16), (n, 3_000_000))
+        us.append(call_us(lambda: spl.spmm(B, C)))
+    print(us, flush=True)
+    assert us[1] < 2 * us[0], us
