@@ -173,13 +173,13 @@ __device__ __forceinline__ int32_t union_count(const Csr3 &m, const Crd3 &x, int
 constexpr int kFillCap = 2048;
 
 // The workgroup's rows [r0, r1) merged a lane per row into output windows
-// of kWin entries in LDS (w_crd, w_val), each window written with coalesced
+// of `win` entries in LDS (w_crd, w_val), each window written with coalesced
 // stores.
-template <typename V, int kWin, int T = kBlock>
+template <typename V, int T = kBlock>
 __device__ __forceinline__ void fill_windows(int64_t n, const Csr3 &m, const Crd3 &x,
                                              const Vals3<V> &vv, const int32_t *apos,
                                              int32_t *acrd, V *aval, int64_t r0, int64_t r1,
-                                             int32_t *w_crd, V *w_val) {
+                                             int win, int32_t *w_crd, V *w_val) {
     const int64_t i = r0 + threadIdx.x;
     const int64_t base = apos[r0];
     const int64_t total = apos[r1] - base;
@@ -187,8 +187,8 @@ __device__ __forceinline__ void fill_windows(int64_t n, const Csr3 &m, const Crd
     int64_t k = mine ? apos[i] - base : 0;
     const int64_t hi = mine ? apos[i + 1] - base : 0;
     Merge3 mg(m, x, mine ? i : r0);
-    for (int64_t w = 0; w < total; w += kWin) {
-        const int64_t we = w + kWin < total ? w + kWin : total;
+    for (int64_t w = 0; w < total; w += win) {
+        const int64_t we = w + win < total ? w + win : total;
         for (; k < hi && k < we; ++k) {
             V sum;
             const int32_t c = mg.next<true, V>(x, vv, sum);
@@ -232,17 +232,17 @@ __global__ __launch_bounds__(kBlock) void k_spadd3_fill(int64_t n, Csr3 m, const
                 for (int X = 0; X < 3; ++X)
                     for (int k = threadIdx.x; k < nv[X]; k += kBlock) s_v[X][k] = src[X][k];
                 __syncthreads();
-                fill_windows<V, kWin>(n, m, x, Vals3<V>{s_v[0], s_v[1], s_v[2], f[0], f[1], f[2]},
-                                      apos, acrd, aval, r0, r1, s_crd, s_val);
+                fill_windows<V>(n, m, x, Vals3<V>{s_v[0], s_v[1], s_v[2], f[0], f[1], f[2]}, apos,
+                                acrd, aval, r0, r1, kWin, s_crd, s_val);
             } else {
-                fill_windows<V, kWin>(n, m, x, Vals3<V>{bv, cv, dv, 0, 0, 0}, apos, acrd, aval,
-                                      r0, r1, s_crd, s_val);
+                fill_windows<V>(n, m, x, Vals3<V>{bv, cv, dv, 0, 0, 0}, apos, acrd, aval, r0, r1,
+                                kWin, s_crd, s_val);
             }
             return;
         }
     }
-    fill_windows<V, kWin>(n, m, Crd3{m.bc, m.cc, m.dc, 0, 0, 0}, Vals3<V>{bv, cv, dv, 0, 0, 0},
-                          apos, acrd, aval, r0, r1, s_crd, s_val);
+    fill_windows<V>(n, m, Crd3{m.bc, m.cc, m.dc, 0, 0, 0}, Vals3<V>{bv, cv, dv, 0, 0, 0}, apos,
+                    acrd, aval, r0, r1, kWin, s_crd, s_val);
 }
 
 // ---- count and default fill: rows staged in dynamic LDS -------------------
@@ -467,7 +467,6 @@ __device__ __forceinline__ double buf_load(const double *, __amdgpu_buffer_rsrc_
 // (its counts of 64-bit masks and searches kept the vector ALUs busy).  Ten
 // words in flight: 131 us with two, 119 with four, 111 with eight, 127 with 16.
 constexpr int kFillWords = 10;   // words of 64 entries in flight per wave
-constexpr int kFillWin = 512;    // output window of the walk in HBM
 
 template <typename V, int T>
 __global__ __launch_bounds__(T) void k_spadd3_bits(int64_t n, Csr3 m, int room, const V *bv,
@@ -484,9 +483,10 @@ __global__ __launch_bounds__(T) void k_spadd3_bits(int64_t n, Csr3 m, int room, 
     const int count = apos[r1] - out0;
     if (runs_bytes(R) + count > room) {
         V *w_val = reinterpret_cast<V *>(s_pool);
-        fill_windows<V, kFillWin, T>(n, m, Crd3{m.bc, m.cc, m.dc, 0, 0, 0},
-                                     Vals3<V>{bv, cv, dv, 0, 0, 0}, apos, acrd, aval, r0, r1,
-                                     reinterpret_cast<int32_t *>(w_val + kFillWin), w_val);
+        const int win = room / static_cast<int>(4 + sizeof(V));
+        fill_windows<V, T>(n, m, Crd3{m.bc, m.cc, m.dc, 0, 0, 0}, Vals3<V>{bv, cv, dv, 0, 0, 0},
+                           apos, acrd, aval, r0, r1, win, reinterpret_cast<int32_t *>(w_val + win),
+                           w_val);
         return;
     }
     int32_t *const x[3] = {s_pool, s_pool + R.n[0] + 1, s_pool + R.n[0] + R.n[1] + 2};
@@ -560,13 +560,25 @@ __global__ __launch_bounds__(T) void k_spadd3_bits(int64_t n, Csr3 m, int room, 
 // Rows per workgroup (128 or 64; 0: not even 64 mean rows fit) and LDS bytes
 // for rows of `per_row` bytes on average.  (On the operands above 64 rows take
 // 5 us more in count and fill together; at half of kMost a CU still holds
-// five workgroups of 128 rows.)
+// five workgroups of 128 rows.)  Rows of a power law do not average out over
+// a workgroup, so that it gets at least `least` bytes, with which a CU still
+// holds as many workgroups as its registers let it (in blocks of 1,280 of its
+// 163,840 bytes, less the static part: 16 workgroups of the count, 10 of the
+// FP32 fill and 8 of the FP64 one); a workgroup that walks in HBM all the same
+// has the wider output windows of it.  Operands of 1e6 rows whose lengths
+// are a power law of mean 4 up to 100, FP32: with mean rows' bytes alone 333
+// us a call, 625 with the long rows the same in all operands, so 192 and 383;
+// Poisson rows of mean 4 112 and 113.
 struct StageShape {
     int rows;
     unsigned bytes;
 };
+constexpr unsigned kCountRoom = 8 * 1280 - 64;
+template <typename V>
+constexpr unsigned kFillRoom = (sizeof(V) == 8 ? 16 : 12) * 1280 - 64;
+
 StageShape stage_rows(double per_row, unsigned least) {
-    constexpr double kSpread = 1.07;  // runs of 64 and more rows vary less than their mean
+    constexpr double kSpread = 1.07;  // Poisson runs of 64 and more rows vary less than their mean
     constexpr unsigned kSlack = 512, kMost = 65536;
     for (int rows : {128, 64}) {
         const double need = per_row * rows * kSpread + kSlack;
@@ -741,7 +753,8 @@ hipError_t launch_spadd3_symbolic(int64_t n, int64_t nnz_in, const int32_t *bp, 
                                   const int32_t *dc, int32_t *apos, int64_t *block_sum,
                                   int64_t *total, hipEvent_t counted, hipStream_t s) {
     Csr3 m{bp, bc, cp, cc, dp, dc};
-    const StageShape g = stage_rows(n ? 4.0 * static_cast<double>(nnz_in) / static_cast<double>(n) : 0, 1024);
+    const StageShape g = stage_rows(n ? 4.0 * static_cast<double>(nnz_in) / static_cast<double>(n) : 0,
+                                    kCountRoom);
     const int rows = g.rows ? g.rows : 64;
     const int64_t blocks = ceil_div(n, rows);
     if (n > 0) {
@@ -780,7 +793,7 @@ hipError_t spadd3_fill(int stage, int64_t n, int64_t nnz_in, const Csr3 &m, cons
     if (stage == 3) {
         // coordinates in, and at most as many bytes out
         const StageShape g = stage_rows(5.0 * static_cast<double>(nnz_in) / static_cast<double>(n),
-                                        kFillWin * (4 + sizeof(V)));
+                                        kFillRoom<V>);
         const int room = static_cast<int>(g.bytes);
         auto bits = [&](auto kern, int rows) {
             kern<<<dim3(static_cast<unsigned>(ceil_div(n, rows))), rows, g.bytes, s>>>(

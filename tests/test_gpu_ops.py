@@ -934,6 +934,60 @@ def test_spadd3_staged_shapes(n, m, deg, long, dtype):
     assert torch.equal(A.vals, again.vals) and torch.equal(A.crd, again.crd)
 
 
+@pytest.mark.parametrize("entries", [2541, 2542, 3056, 3057, 4080, 4081, 9000])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_spadd3_one_full_workgroup(entries, dtype):
+    """All entries in one workgroup's 128 rows of 1,280, as many as its stage
+    holds (count, FP32 fill, FP64 fill) and one more, all of them kept in the
+    output, one row of them long.  Small integers: exact."""
+    spl = _spl()
+    rs = np.random.RandomState(entries)
+    n, m = 1280, 40_000
+    col = rs.permutation(m)[:entries]  # no coordinate twice
+    row = np.where(rs.rand(entries) < 0.2, 300, rs.randint(256, 384, entries))
+    row[:2] = 256, 383
+    op = rs.randint(0, 3, entries)
+    host, ops = [], []
+    for k in range(3):
+        key = np.sort(row[op == k].astype(np.int64) * m + col[op == k])
+        pos = np.zeros(n + 1, np.int32)
+        np.cumsum(np.bincount(key // m, minlength=n), out=pos[1:])
+        host.append((pos, (key % m).astype(np.int32), rs.randint(-9, 9, key.size).astype(float)))
+        ops.append(spl.CSR(_t(pos), _t(host[k][1]), _t(host[k][2], dtype), (n, m)))
+    print(f"spadd3 one workgroup of {entries} {dtype}", flush=True)
+    rpos, rcrd, rvals, _, _ = oracle.spadd3(*host)
+    A = spl.spadd3(*ops)
+    assert np.array_equal(A.pos.cpu().numpy(), rpos) and np.array_equal(A.crd.cpu().numpy(), rcrd)
+    assert np.array_equal(host64(A.vals), rvals)
+
+
+@pytest.mark.parametrize("rows", ["power law", "clustered"])
+def test_spadd3_skewed_rows_time(rows):
+    """Operands whose long rows fill some workgroups' stages (a power law up
+    to 400 entries of mean 2; 20,000 rows of 60 before 980,000 of one): the
+    default must beat the merge that reads its inputs directly."""
+    spl = _spl()
+    n, ops = 1_000_000, []
+    for k in range(3):
+        g = torch.Generator(device=dev())
+        g.manual_seed(k)
+        if rows == "clustered":
+            deg = torch.ones(n, dtype=torch.int64, device=dev())
+            deg[:20_000] = 60
+        else:
+            u = (torch.arange(n, device=dev(), dtype=torch.float64) + 0.5) / n
+            deg = torch.clamp(torch.ceil(0.22 / (1.0 - u)), 1, 400).to(torch.int64)
+            deg = deg[torch.randperm(n, generator=g, device=dev())]
+        row = torch.repeat_interleave(torch.arange(n, device=dev()), deg)
+        key = torch.unique(row * n + torch.randint(0, n, row.shape, generator=g, device=dev()))
+        pos = torch.searchsorted(key, torch.arange(n + 1, device=dev()) * n)
+        ops.append(spl.CSR(pos.to(torch.int32), (key % n).to(torch.int32),
+                           torch.rand(key.numel(), generator=g, device=dev()), (n, n)))
+    us = [call_us(lambda: spl.spadd3(*ops, sched=s)) for s in (None, spl.schedule("row", variant=1))]
+    print(rows, us, flush=True)
+    assert us[0] < 0.85 * us[1], us
+
+
 @pytest.mark.parametrize("K", [4, 33])
 @pytest.mark.parametrize("n", [1, 31, 32, 33, 65_536, 65_537])
 def test_sddmm_chunks_by_size(n, K):
