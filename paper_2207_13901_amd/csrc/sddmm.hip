@@ -114,10 +114,16 @@ __global__ __launch_bounds__(kBlock) void k_sddmm_valu(
 // values read and results stored by one lane per group, inside the loop 0.85
 // and 0.42.  K = 100, BF16: 0.39 ms, 0.85 with one element per lane.
 //
+// BF16 lanes hold as many registers as 7 waves per SIMD allow: left to itself
+// the compiler takes 77, six waves, and the 1,760 workgroups of 1e5 rows of 8
+// need a second round of them (K = 128: 44.0 us a call, 37.4 so; K = 144: 64.0
+// and 48.8; 8e6 positions 331.2 and 332.0).
+//
 // own (rows + positions, else 0): workgroups of one chunk that find its bounds
 // by themselves.
 template <typename V, typename FT, typename Acc, int CHUNK, int L, int VEC, int P, bool RAG>
-__global__ __launch_bounds__(kBlock) void k_sddmm_vec(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
+    sizeof(FT) == 2 ? 7 : 1, sizeof(FT) == 2 ? 7 : 8))) void k_sddmm_vec(
     int64_t rows, int64_t own, int64_t K, const int32_t *__restrict__ pos, const int32_t *__restrict__ crd,
     const V *__restrict__ bv, const FT *__restrict__ C, int64_t ldc, const FT *__restrict__ D,
     int64_t ldd, V *__restrict__ out, const int32_t *__restrict__ trow,

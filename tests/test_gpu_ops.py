@@ -1100,3 +1100,25 @@ def test_mttkrp_tiles_by_size(F, dtype):
         print(f"mttkrp tiles F={F} R={R} {dtype}", flush=True)
         want = spl.mttkrp(B, C, D, sched=spl.schedule("nnz", tile=300))
         assert torch.equal(spl.mttkrp(B, C, D), want)
+
+
+def _sddmm_us(n, K, dtype):
+    """One SDDMM call on n rows of about 8 positions, n columns."""
+    spl = _spl()
+    g = torch.Generator(device=dev())
+    g.manual_seed(n)
+    key = torch.unique(torch.randint(0, n * n, (8 * n,), generator=g, device=dev()))
+    pos = torch.searchsorted(key, torch.arange(n + 1, device=dev()) * n)
+    vdt = torch.float64 if dtype == torch.float64 else torch.float32
+    B = spl.CSR(pos.to(torch.int32), (key % n).to(torch.int32),
+                torch.ones(key.numel(), device=dev(), dtype=vdt), (n, n))
+    C, D = (torch.rand(n, K, generator=g, device=dev()).to(dtype) for _ in range(2))
+    return call_us(lambda: spl.sddmm(B, C, D))
+
+
+def test_sddmm_bf16_time():
+    """1e5 rows of 8, as many workgroups as the chip holds at seven waves per
+    SIMD: BF16 rows must not take longer than FP32 rows of the same bytes."""
+    us = [_sddmm_us(100_000, 128, torch.bfloat16), _sddmm_us(100_000, 64, torch.float32)]
+    print(us, flush=True)
+    assert us[0] < 1.1 * us[1], us
