@@ -1776,12 +1776,16 @@ spl_status spl_sddmm(spl_context *ctx, const spl_sparse *B, const spl_dense *C,
     // alignment: the leaf shifts a row's last vector): as many lanes a
     // position as its row has vectors, 4 to 32, rounded up (K = 33 on 1e5
     // rows, FP32: 31.7 us with 16 lanes, 32.9 with 8; BF16: 24.0 and 25.7
-    // with 8 and 4)
+    // with 8 and 4).  FP64 rows of 17 to 24 vectors take 16 lanes, whose second
+    // round idles half of them at most, rather than 32 with as many idle (1e5
+    // rows of 8, K = 34: 50.9 us against 61.5, K = 48 54.7 and 61.4, K = 56 67.6
+    // and 71.9; BF16, K = 144 49 and 51 with 32 lanes and 16)
     int vec_lanes = 0;
     if (variant == 0) {
         const int v = spl::sddmm_vec_width(C->dtype);
         const int64_t nv = (K + v - 1) / v;
-        if (K >= v) vec_lanes = nv > 16 ? 32 : nv > 8 ? 16 : nv > 4 ? 8 : 4;
+        const int64_t wide = C->dtype == SPL_F64 ? 24 : 16;
+        if (K >= v) vec_lanes = nv > wide ? 32 : nv > 8 ? 16 : nv > 4 ? 8 : 4;
     }
     if (vec_lanes > 0 && finds_own(p, q, 1))
         cv.tiles.own = n + B->nnz;

@@ -1122,3 +1122,26 @@ def test_sddmm_bf16_time():
     us = [_sddmm_us(100_000, 128, torch.bfloat16), _sddmm_us(100_000, 64, torch.float32)]
     print(us, flush=True)
     assert us[0] < 1.1 * us[1], us
+
+
+def test_sddmm_f64_lanes_time():
+    """FP64 rows of 17 vectors, one more than 16 lanes take at once: not as
+    long as two rounds would be."""
+    us = [_sddmm_us(100_000, 34, torch.float64), _sddmm_us(100_000, 32, torch.float64)]
+    print(us, flush=True)
+    assert us[0] < 1.5 * us[1], us
+
+
+@pytest.mark.parametrize("K", [32, 34, 47, 48, 49, 50])
+def test_sddmm_f64_lane_edges(K):
+    """16 lanes a position up to 24 vectors of FP64, 32 beyond.  Small
+    integers: exact."""
+    spl = _spl()
+    rs = np.random.RandomState(K)
+    pos, crd, _ = tiny.csr(rs, 90, 70, 0.1, empty_rows={0, 50, 89}, full_rows={3, 4})
+    vals, C, D = (rs.randint(-4, 5, s).astype(float) for s in (crd.size, (90, K), (70, K)))
+    ref, _ = oracle.sddmm(pos, crd, vals, C, D)
+    A = spl.sddmm(spl.CSR(_t(pos), _t(crd), _t(vals, torch.float64), (90, 70)),
+                  _t(C, torch.float64), _t(D, torch.float64))
+    print(f"sddmm f64 K={K}", flush=True)
+    assert np.array_equal(host64(A), ref)
