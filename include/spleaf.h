@@ -343,7 +343,8 @@ spl_status spl_spmv_window(spl_context *ctx, const spl_sparse *B, const int32_t 
  * 8 BF16 consecutive columns (16 bytes of C) with one vector access when N is
  * at least v, col_tile leaves 4 to 32 lanes per group and items_per_lane is 8
  * or 16 (otherwise one column per lane, as for F64 columns that fill three
- * quarters of such lanes without being a multiple of v); with int64 positions
+ * quarters of such lanes without being a multiple of v, and by default for
+ * BF16 columns that are no multiple of v over rows that are mostly empty); with int64 positions
  * N, C->ld, A->ld and the C and A pointers must be multiples of v; 1 = one
  * column per lane; 2 (BF16 only) = 4 BF16 columns (8 bytes) per lane when N
  * and the others are multiples of that.

@@ -212,6 +212,7 @@ spl_status resolve_spmm(spl_context *ctx, const spl_sparse *B, int64_t N, const 
         return fail(ctx, SPL_ERR_ARG, "unknown schedule kind %d", s->kind);
     int ct = s->col_tile;
     p.items = s->items_per_lane ? s->items_per_lane : 16;
+    bool one = false;  // one column per lane, though vectors would do
     if (!ct) {
         ct = 8;
         // the fewest columns that leave vector lanes a group of four, when
@@ -220,7 +221,16 @@ spl_status resolve_spmm(spl_context *ctx, const spl_sparse *B, int64_t N, const 
         // 278 us against 309, 16 columns 294 against 491; FP32, 1e5 rows: 8
         // columns 31.6 against 38.5)
         const int v = spl::spmm_vec_width(B->vtype);
-        const bool vectors = p.kind == SPL_MERGE && s->variant == 0 && p.items <= 16 && N >= v;
+        // Where most rows are empty the stores are what a call costs, and BF16
+        // lanes, 8 FP32 columns each, store uneven rows in pieces: one column
+        // per lane from 48 MB of output on (1e6 rows with 1e5 entries, 15 / 31 /
+        // 100 columns: 58 / 85 / 259 us against 77 / 119 / 368; 5e5 entries 72 /
+        // 100 / 274 and 76 / 121 / 332; 7e5 entries 94 / 120 / 299 and 77 / 120 /
+        // 320; 3e5 rows with 1.5e5, 15 columns, 41 and 29).
+        one = p.kind == SPL_MERGE && s->variant == 0 && B->vtype == SPL_BF16 && N % v != 0 &&
+              B->pos_type == SPL_I32 && 2 * B->nnz < B->dims[0] &&
+              static_cast<double>(B->dims[0]) * static_cast<double>(N) * 4.0 >= 48e6;
+        const bool vectors = p.kind == SPL_MERGE && s->variant == 0 && p.items <= 16 && N >= v && !one;
         if (vectors && B->pos_type == SPL_I32) ct = 4 * v;
         while (ct < 64 && ct < N) ct <<= 1;
         // Vector lanes with nothing else asked for.  Groups of four lanes
@@ -257,7 +267,7 @@ spl_status resolve_spmm(spl_context *ctx, const spl_sparse *B, int64_t N, const 
                     "(8-byte BF16 lanes)");
     if (s->variant == 2 && B->vtype != SPL_BF16)
         return fail(ctx, SPL_ERR_ARG, "SpMM variant 2 (8-byte lanes) is for BF16 values");
-    p.variant = s->variant;
+    p.variant = one ? 1 : s->variant;
     return SPL_OK;
 }
 

@@ -565,3 +565,43 @@ def test_spmm_one_long_row_time():
         us.append(call_us(lambda: spl.spmm(B, C)))
     print(us, flush=True)
     assert us[1] < 2 * us[0], us
+
+
+def _hypersparse(n, m, nnz, dtype):
+    """nnz ones in distinct random rows of n, one each."""
+    spl = _spl()
+    g = torch.Generator(device=dev())
+    g.manual_seed(nnz)
+    has = torch.zeros(n, dtype=torch.int64, device=dev())
+    has[torch.randperm(n, generator=g, device=dev())[:nnz]] = 1
+    pos = torch.zeros(n + 1, dtype=torch.int32, device=dev())
+    pos[1:] = torch.cumsum(has, 0)
+    crd = torch.randint(0, m, (nnz,), generator=g, device=dev(), dtype=torch.int32)
+    return spl.CSR(pos, crd, torch.ones(nnz, device=dev(), dtype=dtype), (n, m)), has
+
+
+@pytest.mark.parametrize("n,nnz,N", [(400_000, 199_999, 31), (400_000, 200_000, 31),
+                                     (387_095, 30_000, 31), (387_097, 30_000, 31),
+                                     (400_000, 0, 33), (400_000, 30_000, 32), (130_000, 9, 100)])
+def test_spmm_bf16_mostly_empty_rows(n, nnz, N):
+    """Around the line from which BF16 columns that are no multiple of eight go
+    one to a lane: an entry to two rows, 48 MB of output."""
+    spl = _spl()
+    B, has = _hypersparse(n, 5000, nnz, torch.bfloat16)
+    C = torch.randint(-3, 4, (5000, N), device=dev()).to(torch.bfloat16)
+    A = torch.full((n, N), float("nan"), device=dev())
+    print(f"spmm bf16 n={n} nnz={nnz} N={N}", flush=True)
+    spl.spmm(B, C, A)
+    ref = torch.zeros(n, N, device=dev())
+    ref[has == 1] = C.float()[B.crd.long()]
+    assert torch.equal(A, ref)
+
+
+def test_spmm_bf16_mostly_empty_rows_time():
+    """The default must not fall behind one column per lane there."""
+    spl = _spl()
+    B, _ = _hypersparse(1_000_000, 100_000, 100_000, torch.bfloat16)
+    C = torch.rand(100_000, 31, device=dev()).to(torch.bfloat16)
+    us = [call_us(lambda: spl.spmm(B, C, sched=s)) for s in (None, spl.schedule("merge", variant=1))]
+    print(us, flush=True)
+    assert us[0] < 1.15 * us[1], us
