@@ -394,8 +394,8 @@ spl_status spl_spttv(spl_context *ctx, const spl_sparse *B, const spl_dense *c,
  * LDS than 8, so more waves per SIMD.  0 (default) takes 5 for 4-column
  * lanes at col_tile 32 (4 with int64 positions or variant 3), 3 for
  * 8-column BF16 lanes at col_tile 32, 4 for the other vector lanes and 8
- * for one column per lane; tile 0 (default) takes 64 to 800 merged
- * items with vector lanes, by their number and the fibers' mean length.  The workspace query returns the largest size over the
+ * for one column per lane; tile 0 (default) takes 64 to 512 merged
+ * items with vector lanes, the more the more there are.  The workspace query returns the largest size over the
  * lane widths the call may take.  A
  * (Dense, Dense, Compressed) B is accepted: its middle level's pos/crd
  * (I + 1 and I * J int32) are written into the workspace, counted by the

@@ -574,21 +574,15 @@ int64_t mttkrp_chunk(const Plan &p) {
 // (5 for 8 lanes of 4 columns, 3 for 4 lanes of 8 BF16 columns -- each the
 // most merged items whose registers still leave 4 waves per SIMD; 4 for the
 // other vector lanes and for variant 3; 8 for one column per lane) and the
-// tile (64 to 800 merged items with vector lanes, four 256-thread chunks
-// otherwise).  A workgroup walks its tile's chunks one after another, so short
-// tiles spread `total` merged items over more of them, and long ones save
-// carries and run ends.  Fibers of at most four entries leave a chunk little
-// work beside that: the longest tile that still fills the chip once (2,000
-// workgroups of two waves; 8 fit a CU) is taken between 128 and 800 items.
-// FP32, 2e4 slices, fibers of two, in us at tiles of 64 / 512 / so: 2.7e5 items R = 32
-// 27.3 / 49.2 / 25.7, R = 64 43.3 / 85.0 / 39.2; 1.0e6 items 61.0 / 58.0 / 58.0
-// and 108 / 101 / 101; 1.6e6 items 86.6 / 92.3 / 77.9 and 157 / 171 / 147.
-// Longer fibers, and more items, keep the short tile up to 20,000 workgroups
-// (8 waves on every SIMD four times over), then grow it: 1e6 fibers of 8 or 20,
-// R = 32, at 64 / 256 / 512: 152 / 158 / 166 and 370 / 386 / 460; power-law
-// slices, 19e6 items: 1,003 / 842 / 827.  (FP32 with int64 positions, for tensors
-// past 2^31 of them, keeps 512.)  With int64 positions the 4-column leaf
-// takes 4 items: 5 would need one register more than 4 waves per SIMD allow.
+// tile (64 to 512 merged items with vector lanes, four 256-thread chunks
+// otherwise).  A workgroup walks its tile's chunks one after another, so
+// short tiles spread `total` merged items over more of them, and long ones
+// save carries once there are enough: up to 20,000 workgroups (8 waves on
+// every SIMD four times over) before the tile grows.  FP32, R = 32, in us at
+// tiles of 64 / 256 / 512: 16,134 items 22.7 / 42 / 60, 1.2e6 76 / 90 / 115,
+// 5.1e6 254 / 216 / 231, 19e6 1,003 / 842 / 827.  (FP32 with int64 positions,
+// for tensors past 2^31 of them, keeps 512.)  With int64 positions the 4-column leaf takes 4 items: 5 would
+// need one register more than 4 waves per SIMD allow.
 void finish_mttkrp(Plan &p, const spl_sparse *B) {
     const bool pos64 = B->pos_type == SPL_I64;
     const int64_t total = B->dims[0] + B->nfibers;
@@ -607,14 +601,9 @@ void finish_mttkrp(Plan &p, const spl_sparse *B) {
         p.tile = p.kind == SPL_ROW ? 64 : p.kind == SPL_NNZ ? 2048
                  : p.vec > 1     ? 64
                                  : 4 * mttkrp_chunk(p);
-        if (p.kind == SPL_MERGE && p.vec > 1) {
-            if (pos64 && B->vtype == SPL_F32)
-                p.tile = 512;
-            else if (B->nnz <= 4 * B->nfibers && total > 2000 * 128 && total <= 2000 * 800)
-                p.tile = (total + 1999) / 2000;
-            else
-                while (p.tile < 512 && p.tile * 20000 < total) p.tile *= 2;
-        }
+        if (p.kind == SPL_MERGE && p.vec > 1)
+            while (p.tile < 512 && (p.tile * 20000 < total || (pos64 && B->vtype == SPL_F32)))
+                p.tile *= 2;
     }
 }
 

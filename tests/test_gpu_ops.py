@@ -1068,40 +1068,6 @@ def test_mttkrp_carries_of_one_slice_time():
     assert us[1] < 4 * us[0], us
 
 
-@pytest.mark.parametrize("I,R", [(1, 32), (1, 64), (20_000, 64)])
-def test_mttkrp_default_tile_time(I, R):
-    """The default tile against fixed ones on 8e5 to 1e6 short fibers, where
-    tiles of 64 items lost up to 1.7 times by their carries."""
-    spl = _spl()
-    B = _csf_of_slices(spl, I, 1_000_000, 2)
-    C, D = (torch.rand(d, R, device=dev()) for d in B.shape[1:])
-    us = [call_us(lambda: spl.mttkrp(B, C, D, sched=s))
-          for s in (None, spl.schedule("merge", tile=64), spl.schedule("merge", tile=512))]
-    print(I, R, us, flush=True)
-    assert us[0] < 1.2 * min(us), us
-
-
-@pytest.mark.parametrize("F", [323_000, 328_000, 2_020_000, 2_045_000])
-@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-def test_mttkrp_tiles_by_size(F, dtype):
-    """Sizes around the ends of the rule for short fibers (256,000 and
-    1,600,000 slices and fibers), every lane width, against the same sums over
-    a non-zero split.  Small integers: exact."""
-    spl = _spl()
-    B = _csf_of_slices(spl, 300, F, 2)
-    total = 300 + B.nfibers
-    assert (total > 256_000) == (F > 325_000) and (total > 1_600_000) == (F > 2_030_000), total
-    B = B.with_vals(B.vals.to(dtype))
-    for R in (4, 16, 33, 64):
-        g = torch.Generator(device=dev())
-        g.manual_seed(R)
-        C, D = (torch.randint(-2, 3, (d, R), generator=g, device=dev()).to(dtype)
-                for d in B.shape[1:])
-        print(f"mttkrp tiles F={F} R={R} {dtype}", flush=True)
-        want = spl.mttkrp(B, C, D, sched=spl.schedule("nnz", tile=300))
-        assert torch.equal(spl.mttkrp(B, C, D), want)
-
-
 def _sddmm_us(n, K, dtype):
     """One SDDMM call on n rows of about 8 positions, n columns."""
     spl = _spl()
