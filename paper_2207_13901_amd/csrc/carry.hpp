@@ -84,7 +84,18 @@ __device__ __forceinline__ void fix_long_run(const OpenRow &open_row, int64_t us
 #pragma unroll
                 for (int k = 0; k < kFixDeep; ++k) part += t[k];
             }
-            for (v += slice; v < end; v += slices) part += carry[v * ncols + col];
+            // what is left in rounds of half as many (past the end: the last
+            // tile's, not added)
+            for (v += slice; v < end; v += kFixDeep / 2 * slices) {
+                Acc t[kFixDeep / 2];
+#pragma unroll
+                for (int k = 0; k < kFixDeep / 2; ++k) {
+                    const int64_t at = v + k * slices < end ? v + k * slices : end - 1;
+                    t[k] = carry[at * ncols + col];
+                }
+#pragma unroll
+                for (int k = 0; k < kFixDeep / 2; ++k) part += v + k * slices < end ? t[k] : Acc(0);
+            }
         }
         s_part[tid] = part;
         __syncthreads();
