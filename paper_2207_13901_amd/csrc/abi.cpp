@@ -578,11 +578,17 @@ int64_t mttkrp_chunk(const Plan &p) {
 // otherwise).  A workgroup walks its tile's chunks one after another, so
 // short tiles spread `total` merged items over more of them, and long ones
 // save carries once there are enough: up to 20,000 workgroups (8 waves on
-// every SIMD four times over) before the tile grows.  FP32, R = 32, in us at
-// tiles of 64 / 256 / 512: 16,134 items 22.7 / 42 / 60, 1.2e6 76 / 90 / 115,
-// 5.1e6 254 / 216 / 231, 19e6 1,003 / 842 / 827.  (FP32 with int64 positions,
-// for tensors past 2^31 of them, keeps 512.)  With int64 positions the 4-column leaf takes 4 items: 5 would
-// need one register more than 4 waves per SIMD allow.
+// every SIMD four times over) before the tile grows.  FP32, R = 32, power-law
+// slices, in us at tiles of 64 / 256 / 512: 16,134 items 22.7 / 42 / 60, 1.2e6
+// 76 / 90 / 115, 5.1e6 254 / 216 / 231, 19e6 1,003 / 842 / 827.  Where a mean
+// slice would span more than 2,000 tiles the tile grows too, since their
+// carries are added up by one workgroup: 8e5 fibers of two in one slice 96 / 68
+// / 61 us, R = 64 200 / 134 / 109; in five, R = 64, 124 / 116 / 111.  (Slices of
+// equal length lose a little by short tiles at 1e6 fibers of two, R = 64 101
+// us against 95 with 512, where power-law ones gain: 118 against 166 with 700.
+// FP32 with int64 positions, for tensors past 2^31 of them, keeps 512.)  With
+// int64 positions the 4-column leaf takes 4 items: 5 would need one register
+// more than 4 waves per SIMD allow.
 void finish_mttkrp(Plan &p, const spl_sparse *B) {
     const bool pos64 = B->pos_type == SPL_I64;
     const int64_t total = B->dims[0] + B->nfibers;
@@ -602,7 +608,8 @@ void finish_mttkrp(Plan &p, const spl_sparse *B) {
                  : p.vec > 1     ? 64
                                  : 4 * mttkrp_chunk(p);
         if (p.kind == SPL_MERGE && p.vec > 1)
-            while (p.tile < 512 && (p.tile * 20000 < total || (pos64 && B->vtype == SPL_F32)))
+            while (p.tile < 512 && (p.tile * std::min<int64_t>(20000, 2000 * B->dims[0]) < total ||
+                                    (pos64 && B->vtype == SPL_F32)))
                 p.tile *= 2;
     }
 }

@@ -1111,3 +1111,36 @@ def test_sddmm_f64_lane_edges(K):
                   _t(C, torch.float64), _t(D, torch.float64))
     print(f"sddmm f64 K={K}", flush=True)
     assert np.array_equal(host64(A), ref)
+
+
+@pytest.mark.parametrize("R", [32, 64])
+def test_mttkrp_one_slice_tile_time(R):
+    """The default tile against fixed ones on 8e5 fibers of one slice, whose
+    carries cost more than the sums with tiles of 64 items."""
+    spl = _spl()
+    B = _csf_of_slices(spl, 1, 1_000_000, 2)
+    C, D = (torch.rand(d, R, device=dev()) for d in B.shape[1:])
+    us = [call_us(lambda: spl.mttkrp(B, C, D, sched=s))
+          for s in (None, spl.schedule("merge", tile=64), spl.schedule("merge", tile=512))]
+    print(R, us, flush=True)
+    assert us[0] < 1.2 * min(us), us
+
+
+@pytest.mark.parametrize("I,F", [(1, 162_000), (1, 163_500), (1, 326_000), (1, 1_400_000),
+                                 (9, 1_460_000), (9, 1_475_000), (10, 1_630_000)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_mttkrp_tiles_of_few_slices(I, F, dtype):
+    """Around the lines from which mean slices of more than 2,000 tiles take
+    longer ones, every lane width, against the same sums over a non-zero
+    split.  Small integers: exact."""
+    spl = _spl()
+    B = _csf_of_slices(spl, I, F, 2)
+    B = B.with_vals(B.vals.to(dtype))
+    print(f"mttkrp I={I} fibers={B.nfibers} {dtype}", flush=True)
+    for R in (4, 16, 33, 64):
+        g = torch.Generator(device=dev())
+        g.manual_seed(R)
+        C, D = (torch.randint(-1, 2, (d, R), generator=g, device=dev()).to(dtype)
+                for d in B.shape[1:])
+        want = spl.mttkrp(B, C, D, sched=spl.schedule("nnz", tile=300))
+        assert torch.equal(spl.mttkrp(B, C, D), want), R
