@@ -106,24 +106,24 @@ __global__ __launch_bounds__(kBlock) void k_merge_sweep(int64_t rows, const P *p
         trow[t] = static_cast<int32_t>(rows);
         tpos[t] = static_cast<TP>(nnz);
     }
-    // row i's tiles [t0, t1): a few by its lane, more by the whole wave
-    int64_t t0 = 0, t1 = 0;
+    // the tiles that start in row i: the first by its lane, the rest of many by
+    // the whole wave
+    int64_t t = 0, hi = -1;
     if (i < rows) {
-        t0 = tiles_to(i + static_cast<int64_t>(pos[i]));
-        t1 = tiles_to(i + static_cast<int64_t>(pos[i + 1]) + 1);
-    }
-    const bool wide = t1 - t0 > kSweepTiles;
-    if (!wide)
-        for (int64_t t = t0; t < t1; ++t) {
+        const int64_t lo = i + static_cast<int64_t>(pos[i]);
+        hi = i + static_cast<int64_t>(pos[i + 1]);
+        t = tiles_to(lo);
+        for (int own = kSweepTiles; t * M <= hi && own > 0; ++t, --own) {
             trow[t] = static_cast<int32_t>(i);
             tpos[t] = static_cast<TP>(t * M - i);
         }
-    for (uint64_t todo = __ballot(wide); todo; todo &= todo - 1) {
+    }
+    for (uint64_t todo = __ballot(t * M <= hi); todo; todo &= todo - 1) {
         const int src = __ffsll(static_cast<unsigned long long>(todo)) - 1;
-        const int64_t row = __shfl(i, src), end = __shfl(t1, src);
-        for (int64_t t = __shfl(t0, src) + threadIdx.x % kWave; t < end; t += kWave) {
-            trow[t] = static_cast<int32_t>(row);
-            tpos[t] = static_cast<TP>(t * M - row);
+        const int64_t row = __shfl(i, src), end = __shfl(hi, src);
+        for (int64_t k = __shfl(t, src) + threadIdx.x % kWave; k * M <= end; k += kWave) {
+            trow[k] = static_cast<int32_t>(row);
+            tpos[k] = static_cast<TP>(k * M - row);
         }
     }
 }
