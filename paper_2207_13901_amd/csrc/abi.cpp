@@ -27,8 +27,9 @@ struct spl_context {
     int64_t *flags = nullptr;  // 2 x int64 device scratch for spl_validate
     // pinned host slot for the counts read back to the host: an output's
     // nonzero count, which the scan's kernel writes there itself (no copy;
-    // `counted` tells the host), and spl_validate's flags, copied.  Calls on one context are not meant to overlap across host
-    // threads (the error string is shared too).
+    // `counted` tells the host), and spl_validate's flags, copied.  Calls on
+    // one context are not meant to overlap across host threads (the error
+    // string is shared too).
     int64_t *readback = nullptr;  // 2 x int64
     hipEvent_t counted = nullptr;
     // leaf-kernel timing (spl_timing_enable / spl_timing_read)
@@ -1808,7 +1809,6 @@ spl_status spl_sddmm(spl_context *ctx, const spl_sparse *B, const spl_dense *C,
 }
 
 namespace {
-// The numeric phase's default form (0 direct, 1 coordinates staged, 2
 // The numeric phase's default form (0 direct, 1 coordinates staged, 2
 // coordinates and values staged, 3 coordinates staged and entries counted).
 constexpr int kSpadd3DefaultStage = 3;

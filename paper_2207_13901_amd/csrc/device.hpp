@@ -56,9 +56,11 @@ __device__ __forceinline__ void store_stream(T *p, T v) {
 // Rows of a dense operand read and written VEC consecutive elements per lane
 // (VEC > 1: one vector access of VEC elements, 16 bytes except for 4 BF16,
 // whose address must be 8-byte aligned).
-// The vectors below may sit at any element's address (the compiler's 16-byte
-// global accesses need no more), so rows of any column count and leading
-// dimension are read whole vectors at a time (lane_col).
+// The vectors below may sit at any element's address, down to 2 bytes for BF16:
+// global memory instructions run in unaligned access mode, in which a 16-byte
+// access may start at any byte.  So rows of any column count and leading
+// dimension are read whole vectors at a time (lane_col).  Gathers through a
+// buffer descriptor need 4-byte aligned rows (dword_rows in abi.cpp).
 typedef float vf32x4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef double vf64x2 __attribute__((ext_vector_type(2), aligned(8)));
 typedef uint32_t vu32x4 __attribute__((ext_vector_type(4), aligned(2)));  // 8 BF16

@@ -660,11 +660,13 @@ __global__ __launch_bounds__(kBlock) void k_spmv_flag(
 // matrix, bound by its stream, would take up to eight, but with every
 // workgroup more in flight the streamed lines leave less of L2 to the
 // gathered vector (2e6-row power law, FP64: 24.0e6 gather misses of 32e6 with
-// eight, 23.5e6 with three).  Whole calls in us, start (pipelined leaf) / 8 /
-// 4 / 3 workgroups: FP64 band of 2e6 rows 284 / 184 / 195 / 221, power law
-// 460 / 471 / 465 / 464, SpTTV on 1e8 nonzeros 855 / 716 / 652 / 646; FP32
-// 177 / 116 / 154 / 182, 313 / 316 / 308 / 305 and 598 / 569 / 531 / 549.  The
-// band of 2e7 rows (FP64, 8.8 GB): 2,795 -> 1,959 us, 4.5 TB/s.
+// eight, 23.5e6 with three).  Whole calls in us, pipelined leaf / 8 / 4 / 3
+// workgroups: FP64 band of 2e6 rows 284 / 184 / 195 / 221, power law 460 / 471
+// / 465 / 464, SpTTV on 1e8 nonzeros 855 / 716 / 652 / 646; FP32 177 / 116 /
+// 154 / 182, 313 / 316 / 308 / 305 and 598 / 569 / 531 / 549.  The band of 2e7
+// rows (FP64, 8.8 GB): 2,795 -> 1,959 us, 4.5 TB/s.  Random columns into an FP64
+// vector of 16 MB lose: the power law above 1 to 2%, 2e6 rows of 40 1,135 and
+// 1,152; sizes do not tell them from a band.
 constexpr int kOnceLds = 21000;
 
 // OWN: the workgroup finds the bounds of its chunk of the `own` merged items by
@@ -753,7 +755,8 @@ __global__ __launch_bounds__(kBlock) void k_spmv_once(
 // room for of the last one; the rest of that row is summed by the whole
 // workgroup, kSmallDeep positions a lane at a time.  For calls so small that
 // the launches (partition, leaf, fix-up) are what they cost: 4,096 rows of 10
-// FP64 entries take 9.7 us a call against 16.4 (host included).
+// FP64 entries took 9.7 us a call against 16.4, host included (6.6 with the
+// arguments packed by the binding).
 constexpr int kSmallItems = 4;
 constexpr int kSmallChunk = kBlock * kSmallItems;
 constexpr int kSmallDeep = 16;

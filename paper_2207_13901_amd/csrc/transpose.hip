@@ -19,10 +19,11 @@
 // only, no order-dependent atomics: the result is deterministic and
 // bit-exact.  k_transpose_pos then writes B^T's pos from the sorted columns.
 //
-// What bounds it: HBM.  At 32e6 FP32 entries and 2e6 columns (three passes of
-// 7 bits) the scatters take 186 + 2 x 171 us, each moving 20 or 24 bytes an
-// entry at about 4.4 TB/s (a plain copy: 4.76), the counts 32 us each, the
-// offsets 6 each and pos 31: 0.67 ms a call.  Sorting (column, source
+// What bounds it: HBM, but for the first pass.  At 32e6 FP32 entries and 2e6
+// columns (three passes of 7 bits) the later scatters take 171 us each, 24 bytes
+// an entry at 4.5 TB/s (a plain copy: 4.76), the first 188, 20 bytes an entry at
+// 3.4 TB/s: every tile looks up and marks its rows before it can scatter.  The
+// counts take 32 us each, the offsets 6 each and pos 31: 0.66 ms a call.  Sorting (column, source
 // position) pairs with scatters that stored each round directly, then finding
 // every entry's row by a binary search in pos and gathering its value, took
 // 4.26 ms (scatters 536 us each, the last step 2,441).
