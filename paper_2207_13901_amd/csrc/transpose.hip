@@ -20,9 +20,9 @@
 // bit-exact.  k_transpose_pos then writes B^T's pos from the sorted columns.
 //
 // What bounds it: HBM, but for the first pass.  At 32e6 FP32 entries and 2e6
-// columns (three passes of 7 bits) the later scatters take 171 us each, 24 bytes
-// an entry at 4.5 TB/s (a plain copy: 4.76), the first 188, 20 bytes an entry at
-// 3.4 TB/s: every tile looks up and marks its rows before it can scatter.  The
+// columns (three passes of 7 bits) the later scatters take 169 us each, 24 bytes
+// an entry at 4.5 TB/s (a plain copy: 4.76), the first 193, 20 bytes an entry at
+// 3.3 TB/s: every tile looks up and marks its rows before it can scatter.  The
 // counts take 32 us each, the offsets 6 each and pos 31: 0.66 ms a call.  Sorting (column, source
 // position) pairs with scatters that stored each round directly, then finding
 // every entry's row by a binary search in pos and gathering its value, took
